@@ -525,10 +525,11 @@ __device__ int draft_levels(const TrieView& t, Pool& P, int lane, uint32_t u_hea
       uint32_t c = P.first[i];
       unsigned long long total = 0;
       while (c != kNone) {
-        const uint32_t nx = t.next[c];
-        const uint32_t cn = t.count[c];
-        const int32_t tk = static_cast<int32_t>(t.keys[c] & 0xFFFFFFFFull);
-        const uint32_t f = t.first[c];
+        const Slot sl = *t.slot(c);
+        const uint32_t nx = *t.next(c);
+        const uint32_t cn = sl.count + kCountBias;
+        const int32_t tk = static_cast<int32_t>(sl.key & 0xFFFFFFFFull);
+        const uint32_t f = sl.first;
         const uint32_t slot = atomicAdd(&P.m, 1u);
         if (slot >= static_cast<uint32_t>(kPool)) break;
         P.num[slot] = cn;
@@ -652,10 +653,11 @@ __device__ inline int gather_children(const TrieView& t, Smem& sm, int lane) {
     uint32_t c = sm.cursor;
     int k = 0;
     while (c != kNone && k < kChildBuf) {
-      const uint32_t nx = t.next[c];
-      sm.c_count[k] = t.count[c];
-      sm.c_tok[k] = static_cast<int32_t>(t.keys[c] & 0xFFFFFFFFull);
-      sm.c_first[k] = t.first[c];
+      const Slot sl = *t.slot(c);
+      const uint32_t nx = *t.next(c);
+      sm.c_count[k] = sl.count + kCountBias;
+      sm.c_tok[k] = static_cast<int32_t>(sl.key & 0xFFFFFFFFull);
+      sm.c_first[k] = sl.first;
       ++k;
       c = nx;
     }
@@ -795,6 +797,7 @@ __global__ __launch_bounds__(64) void draft_kernel(const void* ws, const int32_t
     Smem seq;
     Pool pool;
   } shared;
+  __shared__ int32_t s_tail[SRT_WAVE];
   const TrieView t = trie_view_dev(ws);
   const int D = t.depth;
   const int b = blockIdx.x;
@@ -804,19 +807,22 @@ __global__ __launch_bounds__(64) void draft_kernel(const void* ws, const int32_t
   const int tlen = max(ctx_len[b], 0);
   const int p = prompt_ids[b];
   const bool pvalid = p >= 0 && p < t.hdr->n_prompts;
-  const int32_t root_tok = tlen >= 1 ? tail[Q - 1] : -1;
-
-  // Longest suffix with a continuation: lane q-1 tries length q.
+  // Longest suffix with a continuation: lane q-1 tries length q.  The tail is
+  // staged in LDS first, so that a step of the walk is one memory round trip
+  // (a lookup, which also returns the node's list head).
+  if (lane < Q) s_tail[lane] = tail[lane];
+  __syncthreads();
+  const int32_t root_tok = tlen >= 1 ? s_tail[Q - 1] : -1;
   const int qlim = pvalid ? min(min(tlen, Q), D - 1) : 0;
   const int q = lane + 1;
-  uint32_t node = kNone, head = kNone;
+  uint32_t head = kNone;
   if (q <= qlim) {
-    node = t.roots[p];
+    uint32_t node = t.roots[p];
     for (int i = 0; i < q && node != kNone; ++i) {
-      const int32_t x = tail[Q - q + i];
-      node = x < 0 ? kNone : trie_lookup(t, node, static_cast<uint32_t>(x));
+      const int32_t x = s_tail[Q - q + i];
+      node = x < 0 ? kNone : trie_lookup(t, node, static_cast<uint32_t>(x), head);
     }
-    if (node != kNone) head = t.first[node];
+    if (node == kNone) head = kNone;
   }
   const uint64_t ballot = __ballot(head != kNone);
   const int qstar = ballot ? 64 - __clzll(static_cast<long long>(ballot)) : 0;

@@ -7,9 +7,9 @@
 // of occurrences.  Appending token x at index j of a stream adds one
 // occurrence to each suffix ending at j.
 //
-// GPU design: one workgroup per inserted segment; its threads walk
-// independent chains, one per start position k of a substring that ends in
-// the new segment.  A stream remembers its active nodes -- the nodes of its
+// GPU design: threads walk independent chains, one per start position k of a
+// substring that ends in the new segment; a workgroup takes a short segment,
+// or a slice of a long one.  A stream remembers its active nodes -- the nodes of its
 // suffixes of length 1 .. D-1 -- so a chain that starts j tokens before the
 // segment starts at the active node of length j instead of walking from the
 // root; a chain that starts inside the segment starts at the prompt's root.
@@ -32,7 +32,7 @@ namespace {
 struct Layout {
   uint64_t slots;
   int32_t stream_stride;
-  uint64_t off_roots, off_streams, off_keys, off_count, off_first, off_next, total;
+  uint64_t off_roots, off_streams, off_table, total;
 };
 
 uint64_t align256(uint64_t x) { return (x + 255) & ~uint64_t(255); }
@@ -56,14 +56,8 @@ bool make_layout(const srt_trie_config& c, Layout* L) {
   off = align256(off + sizeof(uint32_t) * static_cast<uint64_t>(c.n_prompts));
   L->off_streams = off;
   off = align256(off + sizeof(int32_t) * static_cast<uint64_t>(c.max_streams) * L->stream_stride);
-  L->off_keys = off;
-  off = align256(off + sizeof(uint64_t) * slots);
-  L->off_count = off;
-  off = align256(off + sizeof(uint32_t) * slots);
-  L->off_first = off;
-  off = align256(off + sizeof(uint32_t) * slots);
-  L->off_next = off;
-  off = align256(off + sizeof(uint32_t) * slots);
+  L->off_table = off;
+  off = align256(off + slots / kGroupSlots * kGroupBytes);
   L->total = off;
   return true;
 }
@@ -78,7 +72,9 @@ __global__ void fill_u32_kernel(uint32_t* p, uint64_t n, uint32_t v) {
     p[i] = v;
 }
 
-__global__ void fill_u64_kernel(unsigned long long* p, uint64_t n, unsigned long long v) {
+// 16-byte stores: n pieces of all ones.
+__global__ __launch_bounds__(256) void fill_ones_kernel(uint4* p, uint64_t n) {
+  const uint4 v = make_uint4(~0u, ~0u, ~0u, ~0u);
   for (uint64_t i = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; i < n; i += uint64_t(gridDim.x) * blockDim.x)
     p[i] = v;
 }
@@ -87,18 +83,96 @@ __global__ void write_header_kernel(WsHeader* dst, WsHeader h) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *dst = h;
 }
 
+// Nodes created by a workgroup (or thread) are counted against the capacity once.
+__device__ inline void charge(const TrieView& t, uint32_t created) {
+  if (!created) return;
+  const unsigned long long n = atomicAdd(&t.hdr->used, static_cast<unsigned long long>(created));
+  if (n + created > t.hdr->node_limit) set_flag(t, SRT_FLAG_CAPACITY);
+}
+
 __global__ void create_roots_kernel(void* ws, int32_t n_prompts) {
   const TrieView t = trie_view_dev(ws);
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n_prompts) t.roots[p] = trie_get_or_create(t, kRootParent, static_cast<uint32_t>(p));
+  if (p >= n_prompts) return;
+  bool created;
+  t.roots[p] = trie_find_or_create(t, node_key(kRootParent, static_cast<uint32_t>(p)), created, [] {});
+  if (created) charge(t, 1u);
 }
 
+// Checks entry `entry` of an insertion and binds its stream; false (with the
+// sticky flag set) if the entry is to be skipped.  m = active nodes of the
+// stream (lengths 1 .. m).
+__device__ inline bool bind_entry(const TrieView& t, int p, int sid, int len, int32_t stride, int32_t*& rec, int& m) {
+  if (t.hdr->flags & SRT_FLAG_CAPACITY) return false;
+  if (p < 0 || p >= t.hdr->n_prompts) {
+    set_flag(t, SRT_FLAG_PROMPT);
+    return false;
+  }
+  if (sid < 0 || sid >= t.hdr->max_streams || len < 0 || len > stride) {
+    set_flag(t, SRT_FLAG_STREAM);
+    return false;
+  }
+  rec = t.streams + static_cast<int64_t>(sid) * t.hdr->stream_stride;
+  if (rec[0] == -1) {
+    rec[0] = p;
+    rec[1] = 0;
+  } else if (rec[0] != p) {
+    set_flag(t, SRT_FLAG_STREAM);
+    return false;
+  }
+  m = min(rec[1], t.depth - 1);
+  return true;
+}
+
+// The record of stream sid if both ids are in range and it is bound to p.
+__device__ inline bool rec_of(const TrieView& t, int p, int sid, int32_t*& rec) {
+  if (p < 0 || p >= t.hdr->n_prompts || sid < 0 || sid >= t.hdr->max_streams) return false;
+  rec = t.streams + static_cast<int64_t>(sid) * t.hdr->stream_stride;
+  return rec[0] == p;
+}
+
+// One chain: descends from `node` (a string of `depth` tokens) along tokens
+// tok[j .. len-1], creating nodes on demand and counting each node reached,
+// until the segment or the depth limit ends; returns the number of nodes
+// created.  The child-list push of a node created in one step is issued
+// together with the next step's probe.  A chain that consumed the whole
+// segment with fewer than D tokens ends at the new active node of its length.
+__device__ inline uint32_t walk_chain(const TrieView& t, const int32_t* __restrict__ tok, int len, int j,
+                                      uint32_t node, int depth, int32_t* rec) {
+  const int D = t.depth;
+  uint32_t link = kNone, link_parent = 0, made = 0;
+  for (; j < len && depth < D && node != kNone; ++j, ++depth) {
+    const uint64_t key = node_key(node, static_cast<uint32_t>(tok[j]));
+    bool created;
+    uint32_t prev = kNone;
+    const uint32_t at = trie_find_or_create(t, key, created, [&]() {
+      if (link != kNone) prev = atomicExch(&t.slot(link_parent)->first, link);
+    });
+    if (prev != kNone) *t.next(link) = prev;  // an only child's next is still the fill value
+    link = kNone;
+    if (created) {
+      if (depth > 0) link = at;
+      link_parent = node;
+      ++made;
+    } else if (at != kNone) {
+      atomicAdd(&t.slot(at)->count, 1u);  // a created node starts at count 1
+    }
+    node = at;
+  }
+  if (link != kNone) {
+    const uint32_t prev = atomicExch(&t.slot(link_parent)->first, link);
+    if (prev != kNone) *t.next(link) = prev;
+  }
+  if (j == len && depth < D && depth >= 1) rec[kStreamHead + depth - 1] = static_cast<int32_t>(node);
+  return made;
+}
+
+// Short segments (the step's emitted tokens): one workgroup per entry.
 __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* __restrict__ prompt_ids,
                                                      const int32_t* __restrict__ stream_ids,
                                                      const int32_t* __restrict__ tokens,
                                                      const int32_t* __restrict__ lengths, int32_t stride) {
   const TrieView t = trie_view_dev(ws);
-  const int D = t.depth;
   const int entry = blockIdx.x;
   __shared__ int s_ok, s_m;
   __shared__ uint32_t s_act[64];
@@ -111,28 +185,9 @@ __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* _
   const int32_t* tok = tokens + static_cast<int64_t>(entry) * stride;
 
   if (threadIdx.x == 0) {
-    int ok = 1, m = 0;
+    int m = 0;
     int32_t* rec = nullptr;
-    if (t.hdr->flags & SRT_FLAG_CAPACITY) {
-      ok = 0;
-    } else if (p < 0 || p >= t.hdr->n_prompts) {
-      set_flag(t, SRT_FLAG_PROMPT);
-      ok = 0;
-    } else if (sid < 0 || sid >= t.hdr->max_streams || len < 0 || len > stride) {
-      set_flag(t, SRT_FLAG_STREAM);
-      ok = 0;
-    } else {
-      rec = t.streams + static_cast<int64_t>(sid) * t.hdr->stream_stride;
-      if (rec[0] == -1) {
-        rec[0] = p;
-        rec[1] = 0;
-      } else if (rec[0] != p) {
-        set_flag(t, SRT_FLAG_STREAM);
-        ok = 0;
-      }
-      if (ok) m = min(rec[1], D - 1);
-    }
-    s_ok = ok;
+    s_ok = bind_entry(t, p, sid, len, stride, rec, m);
     s_m = m;
     s_rec = rec;
     s_created = 0;
@@ -159,54 +214,117 @@ __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* _
   const int chains = m + len;
   for (int c = threadIdx.x; c < chains; c += blockDim.x) {
     const int k = c - m;  // start of the substring, relative to the segment
-    uint32_t node = k < 0 ? s_act[-k - 1] : root;
-    int depth = k < 0 ? -k : 0;
-    int j = k < 0 ? 0 : k;
-    // Each step is one round trip: the probe is the CAS itself (a failed
-    // CAS returns the slot's key), and the child-list push of a node created
-    // in the previous step is issued together with this step's probe.
-    uint32_t link = kNone, link_parent = 0;
-    for (; j < len && depth < D && node != kNone; ++j, ++depth) {
-      const uint64_t key = node_key(node, static_cast<uint32_t>(tok[j]));
-      uint64_t h = mix64(key) & t.mask;
-      uint32_t prev = kNone;
-      if (link != kNone) prev = atomicExch(&t.first[link_parent], link);
-      unsigned long long old = atomicCAS(&t.keys[h], kEmptyKey, (unsigned long long)key);
-      if (link != kNone) t.next[link] = prev;
-      uint64_t probes = 1;
-      while (old != kEmptyKey && old != key && probes <= t.mask) {
-        h = (h + 1) & t.mask;
-        old = atomicCAS(&t.keys[h], kEmptyKey, (unsigned long long)key);
-        ++probes;
-      }
-      if (old != kEmptyKey && old != key) {  // every slot taken
-        set_flag(t, SRT_FLAG_CAPACITY);
-        node = kNone;
-        link = kNone;
-        break;
-      }
-      if (old == kEmptyKey) {
-        link = static_cast<uint32_t>(h);
-        link_parent = node;
-        atomicAdd(&s_created, 1u);
-      } else {
-        link = kNone;
-      }
-      node = static_cast<uint32_t>(h);
-      atomicAdd(&t.count[node], 1u);
-    }
-    if (link != kNone) t.next[link] = atomicExch(&t.first[link_parent], link);
-    // A chain that consumed the whole segment with fewer than D tokens ends
-    // at the new active node of its length.
-    if (j == len && depth < D && depth >= 1) rec[kStreamHead + depth - 1] = static_cast<int32_t>(node);
+    const uint32_t made = walk_chain(t, tok, len, max(k, 0), k < 0 ? s_act[-k - 1] : root, k < 0 ? -k : 0, rec);
+    if (made) atomicAdd(&s_created, made);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     rec[1] = rec[1] + len;
-    // Nodes created by this segment are counted against the capacity once.
-    const unsigned long long n = atomicAdd(&t.hdr->used, static_cast<unsigned long long>(s_created));
-    if (n + s_created > t.hdr->node_limit) set_flag(t, SRT_FLAG_CAPACITY);
+    charge(t, s_created);
   }
+}
+
+// Long segments (rollouts), two kernels.  The first checks and binds each
+// entry (one workgroup), walks the chains that start before the segment --
+// the only readers of the stream's old active nodes -- and leaves its verdict
+// in the record's spare word; the second spreads the chains that start inside
+// the segments over the whole GPU, a slice of a segment per workgroup, and
+// its last chains write the new active nodes.
+// What bounds it: atomics on random slots, which run at memory (every one of
+// the 2.4 a step takes leaves the L2): a step of one CAS and one exchange
+// alone runs at 11.7 G/s on a 671 MB table, this kernel at about 9 G/s.  The
+// slices keep the longest rollout from setting the time (one workgroup per
+// rollout: 7.4 ms for 512 rollouts of 16 to 16384 tokens, 32 caches, and
+// 2.0 ms for the 32 running sequences after them; now 2.9 and 0.25 ms, the
+// table's layout and the skipped links included).  128 threads: rollouts of
+// one prompt meet at the same nodes, and 256-thread workgroups took 4.0 ms
+// for the same build against 3.4 (64-thread ones 3.3, but 10-20% more where
+// every stream has a prompt of its own).
+// kShortStride: up to there one 1024-thread workgroup walks an entry's chains
+// in one round, in one launch.  At 512 tokens and 8 to 64 entries it takes
+// 132-136 us for new streams and 173-209 us for continued ones, the two
+// kernels 101-118 and 213-242; at 1024 tokens, two rounds, 137-221 and
+// 253-366 against 85-187 and 238-327.
+constexpr int kShortStride = 960;
+constexpr int64_t kBodyGrid = 32768;  // workgroups aimed at; more tokens loop
+constexpr int kHeadThreads = 512;
+constexpr int kBodyThreads = 128;
+
+__global__ __launch_bounds__(kHeadThreads) void insert_head_kernel(void* ws, const int32_t* __restrict__ prompt_ids,
+                                                                   const int32_t* __restrict__ stream_ids,
+                                                                   const int32_t* __restrict__ tokens,
+                                                                   const int32_t* __restrict__ lengths,
+                                                                   int32_t stride) {
+  const TrieView t = trie_view_dev(ws);
+  const int entry = blockIdx.x;
+  __shared__ int s_ok, s_m;
+  __shared__ int32_t* s_rec;
+  __shared__ uint32_t s_created;
+  const int p = prompt_ids[entry];
+  const int len = lengths[entry];
+  const int32_t* tok = tokens + static_cast<int64_t>(entry) * stride;
+  if (threadIdx.x == 0) {
+    int m = 0;
+    int32_t* rec = nullptr;
+    s_ok = bind_entry(t, p, stream_ids[entry], len, stride, rec, m);
+    s_m = m;
+    s_rec = rec;
+    s_created = 0;
+    // What the second kernel cannot see by itself (a full table) is recorded
+    // too; an entry with an id out of range touches no record.
+    if (!s_ok && rec_of(t, p, stream_ids[entry], rec)) rec[kStreamHead + t.depth - 1] = 0;
+  }
+  __syncthreads();
+  if (!s_ok) return;
+  int bad = 0;
+#pragma unroll 8
+  for (int j = threadIdx.x; j < len; j += kHeadThreads) bad |= tok[j] < 0;
+  bad = __syncthreads_or(bad);
+  int32_t* rec = s_rec;
+  const int m = s_m;
+  uint32_t act = kNone;
+  if (!bad && static_cast<int>(threadIdx.x) < m) act = static_cast<uint32_t>(rec[kStreamHead + threadIdx.x]);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (bad) set_flag(t, SRT_FLAG_STREAM);
+    rec[kStreamHead + t.depth - 1] = bad ? 0 : 1;
+    if (!bad) rec[1] = rec[1] + len;
+  }
+  if (bad) return;
+  if (static_cast<int>(threadIdx.x) < m) {
+    const uint32_t made = walk_chain(t, tok, len, 0, act, threadIdx.x + 1, rec);
+    if (made) atomicAdd(&s_created, made);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) charge(t, s_created);
+}
+
+__global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, const int32_t* __restrict__ prompt_ids,
+                                                                   const int32_t* __restrict__ stream_ids,
+                                                                   const int32_t* __restrict__ tokens,
+                                                                   const int32_t* __restrict__ lengths,
+                                                                   int32_t stride, int32_t parts) {
+  const int entry = blockIdx.x / parts, part = blockIdx.x - entry * parts;
+  const int len = lengths[entry];
+  if (part * kBodyThreads >= len) return;
+  const TrieView t = trie_view_dev(ws);
+  // A cache that filled up in the meantime takes no more (its streams take no
+  // later insert either, so slices left out here are never built upon).
+  if (t.hdr->flags & SRT_FLAG_CAPACITY) return;
+  const int p = prompt_ids[entry];
+  int32_t* rec = nullptr;
+  if (len > stride || !rec_of(t, p, stream_ids[entry], rec) || rec[kStreamHead + t.depth - 1] != 1) return;
+  const int32_t* tok = tokens + static_cast<int64_t>(entry) * stride;
+  const uint32_t root = t.roots[p];
+  uint32_t made = 0;
+  for (int k = part * kBodyThreads + threadIdx.x; k < len; k += parts * kBodyThreads)
+    made += walk_chain(t, tok, len, k, root, 0, rec);
+  __shared__ uint32_t s_created;
+  if (threadIdx.x == 0) s_created = 0;
+  __syncthreads();
+  if (made) atomicAdd(&s_created, made);
+  __syncthreads();
+  if (threadIdx.x == 0) charge(t, s_created);
 }
 
 __global__ void reset_streams_kernel(void* ws, int32_t n, const int32_t* __restrict__ ids) {
@@ -234,7 +352,7 @@ __global__ void export_level1_kernel(const void* ws, uint32_t root, int64_t max_
   const uint64_t slots = t.mask + 1;
   for (uint64_t h = blockIdx.x * uint64_t(blockDim.x) + threadIdx.x; h < slots;
        h += uint64_t(gridDim.x) * blockDim.x) {
-    const unsigned long long key = t.keys[h];
+    const unsigned long long key = t.slot(h)->key;
     if (key != kEmptyKey && static_cast<uint32_t>(key >> 32) == root) {
       const unsigned long long idx = atomicAdd(&t.hdr->export_n, 1ull);
       if (static_cast<int64_t>(idx) < max_nodes) {
@@ -260,17 +378,17 @@ __global__ __launch_bounds__(1024) void export_bfs_kernel(const void* ws, int64_
   while (lo < hi) {
     for (long long r = lo + threadIdx.x; r < hi; r += blockDim.x) {
       const uint32_t slot = count[r];
-      for (uint32_t c = t.first[slot]; c != kNone; c = t.next[c]) {
+      for (uint32_t c = t.slot(slot)->first; c != kNone; c = *t.next(c)) {
         const unsigned long long idx = atomicAdd(&t.hdr->export_n, 1ull);
         if (static_cast<int64_t>(idx) < max_nodes) {
           parent[idx] = static_cast<int32_t>(r);
-          token[idx] = static_cast<int32_t>(t.keys[c] & 0xFFFFFFFFull);
+          token[idx] = static_cast<int32_t>(t.slot(c)->key & 0xFFFFFFFFull);
           count[idx] = c;
         }
       }
     }
     __syncthreads();
-    for (long long r = lo + threadIdx.x; r < hi; r += blockDim.x) count[r] = t.count[count[r]];
+    for (long long r = lo + threadIdx.x; r < hi; r += blockDim.x) count[r] = t.slot(count[r])->count + kCountBias;
     __syncthreads();
     if (threadIdx.x == 0) s_hi = static_cast<long long>(min<unsigned long long>(
                               atomicAdd(&t.hdr->export_n, 0ull), static_cast<unsigned long long>(max_nodes)));
@@ -317,10 +435,7 @@ int srt_trie_init(void* ws, size_t ws_bytes, const srt_trie_config* cfg, void* s
   h.node_limit = static_cast<uint64_t>(cfg->node_capacity) + cfg->n_prompts;
   h.off_roots = L.off_roots;
   h.off_streams = L.off_streams;
-  h.off_keys = L.off_keys;
-  h.off_count = L.off_count;
-  h.off_first = L.off_first;
-  h.off_next = L.off_next;
+  h.off_table = L.off_table;
   h.total_bytes = L.total;
   h.node_capacity = cfg->node_capacity;
 
@@ -331,14 +446,8 @@ int srt_trie_init(void* ws, size_t ws_bytes, const srt_trie_config* cfg, void* s
       reinterpret_cast<uint32_t*>(base + L.off_roots), cfg->n_prompts, kNone);
   fill_u32_kernel<<<grid_for(n_stream_words, 256), 256, 0, s>>>(
       reinterpret_cast<uint32_t*>(base + L.off_streams), n_stream_words, 0xFFFFFFFFu);
-  fill_u64_kernel<<<grid_for(L.slots, 256), 256, 0, s>>>(
-      reinterpret_cast<unsigned long long*>(base + L.off_keys), L.slots, kEmptyKey);
-  fill_u32_kernel<<<grid_for(L.slots, 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(base + L.off_count),
-                                                          L.slots, 0u);
-  fill_u32_kernel<<<grid_for(L.slots, 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(base + L.off_first),
-                                                          L.slots, kNone);
-  fill_u32_kernel<<<grid_for(L.slots, 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(base + L.off_next),
-                                                          L.slots, kNone);
+  const uint64_t pieces = L.slots / kGroupSlots * kGroupBytes / sizeof(uint4);
+  fill_ones_kernel<<<grid_for(pieces, 256), 256, 0, s>>>(reinterpret_cast<uint4*>(base + L.off_table), pieces);
   create_roots_kernel<<<grid_for(cfg->n_prompts, 256), 256, 0, s>>>(ws, cfg->n_prompts);
   return launch_status();
 }
@@ -348,12 +457,20 @@ int srt_trie_insert(void* ws, int32_t n, const int32_t* prompt_ids, const int32_
   if (!ws || n < 0 || stride < 1) return SRT_ERR_INVALID;
   if (n == 0) return SRT_OK;
   if (!prompt_ids || !stream_ids || !tokens || !lengths) return SRT_ERR_INVALID;
+  hipStream_t s = as_stream(stream);
+  if (stride > kShortStride) {
+    const int64_t slices = (static_cast<int64_t>(stride) + kBodyThreads - 1) / kBodyThreads;
+    const int32_t parts = static_cast<int32_t>(std::min<int64_t>(slices, std::max<int64_t>(1, kBodyGrid / n)));
+    insert_head_kernel<<<n, kHeadThreads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
+    insert_body_kernel<<<static_cast<unsigned>(static_cast<int64_t>(n) * parts), kBodyThreads, 0, s>>>(
+        ws, prompt_ids, stream_ids, tokens, lengths, stride, parts);
+    return launch_status();
+  }
   // one thread per substring start (up to 63 starts before the segment plus
-  // one per token), so a segment of up to ~960 tokens walks its chains in
-  // a single round of at most D dependent steps
+  // one per token)
   const int64_t starts = static_cast<int64_t>(stride) + 63;
   const unsigned threads = static_cast<unsigned>(std::min<int64_t>(1024, (starts + 63) / 64 * 64));
-  insert_kernel<<<n, threads, 0, as_stream(stream)>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
+  insert_kernel<<<n, threads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
   return launch_status();
 }
 

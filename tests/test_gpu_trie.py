@@ -155,3 +155,42 @@ def test_segments_longer_than_a_workgroup():
     c.insert([0, 0], ids, [s0, s1[200:]])
     assert c.status()["flags"] == 0
     check_prompt(c, 0, [s0, s1], D)
+
+
+@pytest.mark.parametrize("D,width", [(1, 961), (2, 1089), (20, 960), (20, 961), (20, 2500), (64, 1500)])
+def test_long_segments_beside_short_and_rejected_ones(D, width):
+    # Segments above 960 tokens go to several workgroups each: a new stream,
+    # one that continues, short and empty entries of the same call, an entry
+    # rejected for its last token and one of a prompt out of range.  Every
+    # stream then grows by a few tokens (the short path reads the active
+    # nodes that the long one left), then by a long segment again.
+    rng = np.random.default_rng(1000 * D + width)
+    base = rng.integers(0, 40, size=2 * width + 200)
+    draw = lambda n: np.where(rng.random(n) < 0.1, rng.integers(0, 40, n), base[:n])
+    c = Caches.create(2, 16, D, 40 * width * D)
+    ids = np.arange(6, dtype=np.int32)
+    prompts = [0, 0, 0, 1, 0, 1]
+    have = [list(draw(n)) for n in (0, 70, 0, 3, 130, 0)]
+    say(f"cache: long segments D={D} width={width}")
+    c.insert(prompts, ids, [np.array(h, dtype=np.int64) for h in have])
+    for lens in ((width, width - 1, 5, 129, 0, 128), (3, 1, 4, 0, 2, 7), (1, width, 127, width, 64, D)):
+        segs = [draw(n) for n in lens]
+        bad = np.concatenate([draw(width - 1), [-5]]) if lens[0] == width else np.array([4, -1])
+        c.insert(prompts + [0, 2], np.concatenate([ids, [7, 8]]).astype(np.int32), segs + [bad, draw(width)])
+        for h, s in zip(have, segs):
+            h.extend(s)
+        st = c.status()
+        assert st["flags"] == srt.SRT_FLAG_STREAM | srt.SRT_FLAG_PROMPT
+        for p in range(2):
+            check_prompt(c, p, [np.array(h) for h, q in zip(have, prompts) if q == p], D)
+
+
+def test_long_segment_after_overflow_is_dropped():
+    D = 8
+    c = Caches.create(1, 4, D, 200)
+    say("cache: long segment into a full cache")
+    c.insert([0], np.array([0], np.int32), [np.arange(100)])
+    before = c.status()
+    assert before["flags"] & srt.SRT_FLAG_CAPACITY
+    c.insert([0, 0], np.array([0, 1], np.int32), [np.arange(1200), np.arange(1200)])
+    assert c.status()["nodes"] == before["nodes"]
