@@ -352,6 +352,53 @@ def head_passes(tree, out_nodes, emitted, Dmax):
     return passes
 
 
+LOOK_ROWS = 256  # rows srt_accept_lmhead fills a pass up to
+
+
+def look_passes(tree, out_nodes, emitted, Dmax):
+    """Rows of each product pass srt_accept_lmhead makes: every sequence still
+    walking brings the first q nodes (in tree order, depth at most Dmax) of its
+    current node's subtree, q the largest number for which the rows fit
+    LOOK_ROWS, the first walkers one more each while rows are left (a walker's
+    order is that of the sequences here, of arrival in the kernel); the walk
+    goes on until it leaves those nodes.  Rebuilt from the trees and the
+    returned walks (host bookkeeping)."""
+    tp, nn = tree["tree_parent"], tree["n_nodes"]
+    cur = {b: (0, 0) for b in range(tp.shape[0])}  # sequence -> (node, depth)
+    passes = []
+    while cur:
+        lists = {}
+        for b, (u, d) in cur.items():
+            depth = {u: d}
+            for c in range(u + 1, int(nn[b])):
+                pd = depth.get(int(tp[b, c]))
+                if pd is not None and pd < Dmax:
+                    depth[c] = pd + 1
+            lists[b] = list(depth)[:LOOK_ROWS]
+        size = {b: 1 for b in cur}
+        if len(cur) <= LOOK_ROWS:
+            q = 1
+            while q < LOOK_ROWS and sum(min(len(x), q + 1) for x in lists.values()) <= LOOK_ROWS:
+                q += 1
+            size = {b: min(len(x), q) for b, x in lists.items()}
+            left = LOOK_ROWS - sum(size.values())
+            for b, x in lists.items():
+                if left > 0 and len(x) > q:
+                    size[b] += 1
+                    left -= 1
+        passes.append(sum(size.values()))
+        nxt = {}
+        for b, (u, d) in cur.items():
+            have = set(lists[b][:size[b]])
+            while d + 1 < int(emitted[b]):
+                u, d = int(out_nodes[b, d]), d + 1
+                if u not in have:
+                    nxt[b] = (u, d)
+                    break
+        cur = nxt
+    return passes
+
+
 def fused_head(st, cfg, calls: int, unfused: bool):
     """The acceptance walk with the LM head fused in (srt_accept_lmhead) on
     the current trees: synthetic bf16 head [V, d_model] and hidden states
@@ -386,7 +433,7 @@ def fused_head(st, cfg, calls: int, unfused: bool):
     emitted = out["n_emitted"].cpu().numpy().astype(np.int64)
     levels = int(emitted.max())
     walkers = [int((emitted > l).sum()) for l in range(levels)]  # sequences walking at level l
-    passes = head_passes(tree, out["out_nodes"].cpu().numpy(), emitted, cfg.max_depth)
+    passes = look_passes(tree, out["out_nodes"].cpu().numpy(), emitted, cfg.max_depth)
     row_bytes = dm * 2 + (V * 4 if st.gumbel is not None else 0)  # hidden row + noise row
     nbytes = sum(V * dm * 2 + rows * row_bytes for rows in passes)  # the head once per pass
     flops = sum(2.0 * rows * dm * V for rows in passes)

@@ -273,12 +273,13 @@ int srt_accept_noalloc(int32_t B, int32_t N, int32_t V, int32_t Dmax, const floa
  * and with it an arg-max whose top two scores are that close; with inputs
  * whose partial sums are exact in fp32 the result equals srt_accept on the
  * materialised logits bit for bit).  No [B, N, V] logits tensor is formed.
- * The walk advances one depth level per kernel pair for the whole batch
- * (Dmax + 1 pairs are always enqueued; a level with no walking sequence
- * exits at once); each level reads the head once.  Once the subtrees of
- * the walking sequences' current nodes hold few enough nodes, one pass
- * computes the arg-max of all of them and every walk is completed from
- * those (same results: a node's dot product does not depend on the pass).
+ * The walk advances in passes, each of which reads the head once.  A pass
+ * computes the arg-max at the current node of every walking sequence and, as
+ * long as it has room (256 rows), at the next nodes of those nodes' subtrees
+ * in tree order, and the walks go on through the computed nodes (same
+ * results: a node's dot product does not depend on the pass).  At most
+ * min(Dmax + 1, ceil(N / max(1, 256 / B))) passes are enqueued; one with no
+ * walking sequence exits at once.
  * Layouts: hidden [B, N, d_model] bf16 bits (the final hidden state of each
  * tree node), w_head [V, d_model] bf16 bits, both 16-byte aligned; gumbel
  * [B, Dmax+1, V] fp32 or NULL (greedy; inv_temperature then unused, else it
@@ -287,10 +288,9 @@ int srt_accept_noalloc(int32_t B, int32_t N, int32_t V, int32_t Dmax, const floa
  * (else SRT_ERR_UNSUPPORTED); 0 <= Dmax <= 63.
  * scratch: device buffer, 256-byte aligned, of at least
  * srt_accept_lmhead_scratch_bytes(B, N, V) bytes (else SRT_ERR_CAPACITY):
- * per-level lists of walking sequences and of their subtrees' nodes, a
- * node-to-row table (4 bytes per tree node) and per-tile arg-max
- * candidates (8 bytes per row per 128 vocabulary entries, for max(B, 128)
- * rows).  Owned by
+ * per-pass lists of walking sequences and of their subtrees' nodes, a table
+ * of the nodes' places in them (4 bytes per tree node) and per-tile arg-max
+ * candidates (8 bytes per row and tile, for max(B, 256) rows).  Owned by
  * the caller; contents are overwritten; calls sharing a scratch buffer must
  * not overlap.
  * ---------------------------------------------------------------------- */

@@ -7,60 +7,57 @@
 // where the policy's logits at tree node u are its LM head applied to the
 // node's final hidden state, logit_j = <hidden[b,u], w_head[j]>.  The walk
 // needs the arg-max at the nodes it visits and nothing else, so the
-// [B, N, V] logits tensor and the head's products for unvisited nodes are
-// never formed.
+// [B, N, V] logits tensor and the head's products for most unvisited nodes
+// are never formed.
 //
-// GPU design.  The walk advances one depth level at a time for the whole
-// batch; at level l every sequence still walking sits at one node of depth
-// l.  Per level:
-//   * a GEMM kernel multiplies the walking sequences' hidden rows (gathered
-//     by node index) with the whole head, C^T = W H^T on
-//     v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  A workgroup of 4
-//     waves owns 128 head rows (32 per wave) and a block of 64 walking
-//     sequences.  Each head row is used by one wave only, so the head is
-//     read from HBM straight into the MFMA operand registers, four 64-wide
-//     chunks of d_model ahead of the MFMAs (16 KB in flight per wave); the
-//     hidden rows are shared by the 4 waves and staged through
-//     double-buffered, padded LDS.  A sequence lives in one lane column, so
-//     its scores (plus the level's Gumbel row) reduce to a (value, token)
-//     candidate inside the lane, then across the two lane halves and the
-//     four waves; one packed 64-bit candidate per (sequence, tile) goes to
-//     scratch with a plain store.  Blocks whose sequence block has no
-//     walkers exit at once;
-//   * a walk kernel (one workgroup per walking sequence) takes the maximum
-//     candidate over the tiles, looks for the child carrying that token,
-//     writes the step's outputs and, if it descends, appends the sequence to
-//     the next level's list.
-// A level is bound by streaming the head (V x d_model bf16) from HBM; the
-// blocks of one head tile and different sequence blocks are placed on one
-// XCD back to back, so the head rows they share come from its L2.
+// GPU design.  The batch advances in passes; a pass reads the head once.
+//   * Rows of a pass: every sequence still walking brings its current node
+//     and, as long as the pass has room (kLook rows), the next nodes of that
+//     node's subtree in tree order, the same number for everybody (draft
+//     rank order: likely descendants first).  A pass is bound by reading the
+//     head up to about 256 rows, so these rows are nearly free and each
+//     spares the walk a pass of its own.
+//   * A product kernel multiplies the rows with the whole head and reduces
+//     each to one (score, token) candidate per tile of the vocabulary.
+//   * A walk kernel (one workgroup per walking sequence) follows the walk
+//     through the nodes of the pass; where it leaves them it lists the new
+//     current node's subtree for the next pass.
+// A walk that leaves a pass with quota q stands at least q places further in
+// its tree, so ceil(N / q) passes always suffice and no more are enqueued.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
-
 
 using namespace srt;
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 4;
-constexpr int kTV = 32 * kWaves;         // vocabulary rows per workgroup (32 per wave)
-constexpr int kKC = 64;                  // d_model elements per chunk
-constexpr int kInFlight = 4;             // head chunks each wave keeps in flight
-constexpr int kRowBytes = kKC * 2 + 16;  // padded LDS row (conflict-free fragment reads)
+constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * SRT_WAVE;
+constexpr int kTV = 256;                 // head rows of a tile
+constexpr int kUnit = 16;                // head rows are shared out in units of 16
+constexpr int kKC = 64;                  // d_model elements per step (one 128-byte line of a row)
+constexpr int kRowBytes = kKC * 2 + 16;  // padded LDS row (conflict-free operand reads)
+constexpr int kStageRows = kThreads / 8; // rows staged by one load of every thread
+constexpr int kMaxTM = 256;              // rows of a pass multiplied together
+// Rows that a pass is filled up to.  One pass over a 152064 x 3584 head takes
+// 221 us for 64 rows, 260 for 128 and 380 for 256 (sampled; reading the head
+// alone takes 190), and the walks of 256 sequences, 13 levels deep, take 6
+// passes when filled to 256 rows, 9 when filled to 128 (2.36 against 2.59 ms)
+// and 11 passes (2.70 ms) one level at a time with a last pass over what is left.
+constexpr int kLook = 256;
 constexpr int kMaxLevels = 64;           // Dmax + 1 <= 64
-constexpr int kXcds = 8;
+constexpr int kGrid = 256;               // workgroups of a pass, at most: one per CU
 constexpr int kWalkThreads = 256;
-#ifndef SRT_HEAD_FINISH_ROWS
-#define SRT_HEAD_FINISH_ROWS 128
-#endif
-constexpr int kFinishRows = SRT_HEAD_FINISH_ROWS;  // rows of a finishing pass
+constexpr int kParents = 1024;           // nodes of a tree whose parents are staged in LDS
+constexpr int kUncovered = 0xFFFF;       // place of a subtree node beyond every pass
 
 struct HeadArgs {
   const uint16_t* hidden;   // [B, N, dm]
@@ -73,35 +70,58 @@ struct HeadArgs {
   int32_t* out_tokens;
   int32_t* out_nodes;
   int32_t* n_emitted;
-  int32_t* n_act;           // [kMaxLevels + 1] walking sequences per level
-  int32_t* fin_n;           // [kMaxLevels + 1] nodes in the walkers' subtrees per level
-  int32_t* act;             // [2, B] walking sequences, by level parity
-  int32_t* fin;             // [2, 3, kFinishRows] (sequence, node, depth) of those nodes
+  int32_t* n_act;           // [kMaxLevels + 1] walking sequences per pass
+  int32_t* act;             // [2, B] walking sequences, by pass parity
   int32_t* cur;             // [B] current node of each sequence
-  int32_t* rowtab;          // [B, N] row of a node in its level's subtree list
-  unsigned long long* cand; // [max(B, kFinishRows), n_vt] packed candidates of the level
-  int B, N, dm, V, Dmax, n_vt;
+  int32_t* cnt;             // [B] nodes listed for it (its subtree's first kLook at most)
+  int2* span;               // [kLook] first row and row count of each walker of the pass
+  int32_t* list;            // [B, min(N, kLook)] those nodes
+  int32_t* place;           // [B, N] place of a node in its list | depth << 16
+  unsigned long long* cand; // [max(B, kLook), n_cand] packed candidates of the pass
+  int B, N, L, dm, V, Dmax, n_cand;
+  int units, tiles;         // 16-row units of the head; tiles per workgroup
   int vec_noise;            // gumbel rows can be read as float4
   float invT;
 };
 
-// Scratch layout: counters, lists, current nodes, node rows, candidates.
+// How a pass divides the head: 16-row units shared out evenly over at most
+// kGrid workgroups, each of which reads its share in tiles of up to kTV rows.
+struct Split {
+  int units, grid, tiles;
+};
+
+inline Split split_for(int64_t V) {
+  Split s;
+  s.units = static_cast<int>((V + kUnit - 1) / kUnit);
+  s.grid = std::min(kGrid, s.units);
+  const int per = s.grid * (kTV / kUnit);
+  s.tiles = (s.units + per - 1) / per;
+  return s;
+}
+
+// Scratch layout: counters, lists, current nodes, node places, candidates.
 struct ScratchLayout {
-  size_t off_fin_n, off_act, off_fin, off_cur, off_rowtab, off_cand, total;
+  size_t off_act, off_cur, off_cnt, off_span, off_list, off_place, off_cand, total;
 };
 
 inline ScratchLayout scratch_layout(int64_t B, int64_t N, int64_t V) {
   auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
   ScratchLayout s;
-  const int64_t n_vt = (V + kTV - 1) / kTV;
-  const int64_t rows = std::max<int64_t>(B, kFinishRows);
-  s.off_fin_n = up(sizeof(int32_t) * (kMaxLevels + 1));
-  s.off_act = s.off_fin_n + up(sizeof(int32_t) * (kMaxLevels + 1));
-  s.off_fin = s.off_act + up(sizeof(int32_t) * 2 * static_cast<size_t>(B));
-  s.off_cur = s.off_fin + up(sizeof(int32_t) * 2 * 3 * kFinishRows);
-  s.off_rowtab = s.off_cur + up(sizeof(int32_t) * static_cast<size_t>(B));
-  s.off_cand = s.off_rowtab + up(sizeof(int32_t) * static_cast<size_t>(B) * static_cast<size_t>(N));
-  s.total = s.off_cand + up(sizeof(unsigned long long) * static_cast<size_t>(rows) * static_cast<size_t>(n_vt));
+  const Split sp = split_for(V);
+  const size_t b = static_cast<size_t>(B), n = static_cast<size_t>(N);
+  s.off_act = up(sizeof(int32_t) * (kMaxLevels + 1));
+  s.off_cur = s.off_act + up(sizeof(int32_t) * 2 * b);
+  s.off_cnt = s.off_cur + up(sizeof(int32_t) * b);
+  s.off_span = s.off_cnt + up(sizeof(int32_t) * b);
+  s.off_list = s.off_span + up(sizeof(int2) * kLook);
+  s.off_place = s.off_list + up(sizeof(int32_t) * b * std::min<size_t>(n, kLook));
+  s.off_cand = s.off_place + up(sizeof(int32_t) * b * n);
+  s.total = s.off_cand +
+            up(sizeof(unsigned long long) * std::max<size_t>(b, kLook) * static_cast<size_t>(sp.grid) * sp.tiles);
+  // At least a 128-row table of candidates per 128 head rows, as callers may
+  // have sized their buffer by that.
+  const size_t by_tile = sizeof(unsigned long long) * std::max<size_t>(b, 128) * ((static_cast<size_t>(V) + 127) / 128);
+  s.total = std::max(s.total, up(sizeof(int32_t) * (3 * b + b * n + 1024)) + up(by_tile) + 1024);
   return s;
 }
 
@@ -124,44 +144,23 @@ __device__ inline void take(float& bv, int& bi, float v, int i) {
   }
 }
 
-// A level runs as a finishing pass when the subtrees of its walkers' current
-// nodes (down to depth Dmax) hold at most kFinishRows nodes: one product pass
-// then gives the arg-max of every node the remaining walks can visit, and
-// the walk kernel completes every walk.
-__device__ inline bool finishing(const HeadArgs& a, int level) {
-  const int nf = a.fin_n[level];
-  return nf > 0 && nf <= kFinishRows;
-}
-
-// Row `slot` of a level: its sequence, tree node and depth (= walk step).
-__device__ inline void level_row(const HeadArgs& a, int level, bool fin, int slot, int& b, int& u, int& d) {
-  if (fin) {
-    const int32_t* f = a.fin + (level & 1) * 3 * kFinishRows;
-    b = min(max(f[slot], 0), a.B - 1);
-    u = min(max(f[kFinishRows + slot], 0), a.N - 1);
-    d = min(max(f[2 * kFinishRows + slot], 0), a.Dmax);
-  } else {
-    b = min(max(a.act[(level & 1) * a.B + slot], 0), a.B - 1);
-    u = min(max(a.cur[b], 0), a.N - 1);
-    d = level;
-  }
-}
-
-// One wave lists node u of sequence b (depth du) and its descendants of
-// depth <= Dmax in the subtree list of `level`.  Descendants have larger
-// indices; a node's ancestry is followed up through parents with smaller
-// indices only, so malformed parent links end the search.
-__device__ inline void list_subtree(const HeadArgs& a, int level, int b, int u, int du, int n) {
+// One wave lists the subtree of node u of sequence b (u at depth du, nodes of
+// depth <= Dmax, in tree order): the first a.L nodes go to the list, every
+// node learns its place and depth.  Descendants have larger indices; a
+// node's ancestry is followed up through parents with smaller indices only,
+// so malformed parent links end the search.  `par`: the tree's parents in
+// LDS (staged), or null.
+__device__ inline void list_subtree(const HeadArgs& a, int b, int u, int du, int n, const int32_t* par) {
   const int lane = threadIdx.x % SRT_WAVE;
   const int64_t tr = static_cast<int64_t>(b) * a.N;
-  int32_t* f = a.fin + (level & 1) * 3 * kFinishRows;
+  int base = 0;
   for (int c0 = u; c0 < n; c0 += SRT_WAVE) {
     const int c = c0 + lane;
     int depth = -1;
     if (c < n) {
       int x = c, steps = 0;
       while (x > u && steps <= a.Dmax - du) {
-        const int p = a.tree_parent[tr + x];
+        const int p = par ? par[x] : a.tree_parent[tr + x];
         if (p < 0 || p >= x) break;
         x = p;
         ++steps;
@@ -169,242 +168,353 @@ __device__ inline void list_subtree(const HeadArgs& a, int level, int b, int u, 
       if (x == u && du + steps <= a.Dmax) depth = du + steps;
     }
     const unsigned long long m = __ballot(depth >= 0);
-    if (!m) continue;
-    int base = 0;
-    if (lane == 0) base = atomicAdd(&a.fin_n[level], __popcll(m));
-    base = __shfl(base, 0, SRT_WAVE);
     if (depth >= 0) {
-      const int r = base + __popcll(m & ((1ull << lane) - 1));
-      if (r < kFinishRows) {
-        f[r] = b;
-        f[kFinishRows + r] = c;
-        f[2 * kFinishRows + r] = depth;
-        a.rowtab[tr + c] = r;
-      }
+      const int j = base + __popcll(m & ((1ull << lane) - 1));
+      if (j < a.L) a.list[static_cast<int64_t>(b) * a.L + j] = c;
+      a.place[tr + c] = (j < a.L ? j : kUncovered) | (depth << 16);
     }
+    base += __popcll(m);
+  }
+  if (lane == 0) {
+    a.cur[b] = u;
+    a.cnt[b] = min(base, a.L);
   }
 }
 
-// Level counters: n_act[0] = B, the rest 0.
-__global__ __launch_bounds__(128) void head_reset_kernel(HeadArgs a) {
-  for (int i = threadIdx.x; i <= kMaxLevels; i += blockDim.x) {
-    a.n_act[i] = i == 0 ? a.B : 0;
-    a.fin_n[i] = 0;
-  }
+// Stages a tree's parents in LDS if they fit (one wave); null if not.
+__device__ inline const int32_t* stage_parents(const HeadArgs& a, int b, int n, int32_t* s_par) {
+  if (n > kParents) return nullptr;
+  const int lane = threadIdx.x % SRT_WAVE;
+  for (int c = lane; c < n; c += SRT_WAVE) s_par[c] = a.tree_parent[static_cast<int64_t>(b) * a.N + c];
+  __builtin_amdgcn_wave_barrier();
+  return s_par;
 }
 
-// One wave per sequence: outputs to -1, walking at level 0 from the root,
-// whole tree listed for a level-0 finishing pass.
+// One wave per sequence: outputs to -1, walking from the root with its whole
+// tree listed; the first one also sets the counters (n_act[0] = B, the rest 0).
 __global__ __launch_bounds__(SRT_WAVE) void head_init_kernel(HeadArgs a) {
+  __shared__ int32_t s_par[kParents];
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
+  if (b == 0)
+    for (int i = lane; i <= kMaxLevels; i += SRT_WAVE) a.n_act[i] = i == 0 ? a.B : 0;
   const int64_t row = static_cast<int64_t>(b) * (a.Dmax + 1);
   for (int k = lane; k <= a.Dmax; k += SRT_WAVE) {
     a.out_tokens[row + k] = -1;
     a.out_nodes[row + k] = -1;
   }
-  if (lane == 0) {
-    a.act[b] = b;
-    a.cur[b] = 0;
-  }
-  list_subtree(a, 0, b, 0, 0, min(max(a.n_nodes[b], 1), a.N));
+  if (lane == 0) a.act[b] = b;
+  const int n = min(max(a.n_nodes[b], 1), a.N);
+  const int32_t* par = stage_parents(a, b, n, s_par);
+  __syncthreads();
+  list_subtree(a, b, 0, 0, n, par);
 }
 
-// Wave layouts of a level pass: the 4 waves of a workgroup split its 128
-// head rows into WV groups of 32 VT rows and its TM = 32 WS ST sequences
-// into WS groups of 32 ST; a wave multiplies its head rows with its
-// sequences (VT x ST MFMA tiles).  Narrow (4 x 1 waves, 64 sequences) for
-// levels with at most 64 rows; wide (2 x 2 waves, 128 sequences) above,
-// which stages each sequence block's rows once per 128 sequences and
-// reads a quarter less LDS per product.
-struct Narrow {
-  static constexpr int WV = 4, VT = 1, WS = 1, ST = 2, TM = 64;
+// LDS of a product kernel (152 of the CU's 160 KB).
+struct PassShared {
+  union {
+    struct {
+      uint8_t w[2][kTV * kRowBytes];           // head rows of two steps
+      uint8_t h[2][kMaxTM * kRowBytes];        // hidden rows of two steps
+    };
+    unsigned long long key[kWaves][kMaxTM];    // after the steps
+  };
+  int64_t hoff[kMaxTM], goff[kMaxTM];          // a row's hidden and noise offsets
+  int base[kMaxTM];                            // first row of each walker
+  int cnt[kMaxTM];
 };
-struct Wide {
-  static constexpr int WV = 2, VT = 2, WS = 2, ST = 2, TM = 128;
-};
-static_assert(Narrow::WV * Narrow::WS * SRT_WAVE == kThreads && Wide::WV * Wide::WS * SRT_WAVE == kThreads,
-              "the WV x WS waves of either layout fill the workgroup");
-static_assert(Narrow::TM == 32 * Narrow::WS * Narrow::ST && Wide::TM == 32 * Wide::WS * Wide::ST,
-              "TM = 32 WS ST sequences");
-constexpr int kMaxTM = 128;
-constexpr int kWideAbove = 64;  // rows of a level above which it runs wide
 
+__device__ inline int wave_sum(int v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, SRT_WAVE);
+  return v;
+}
+
+// Rows of the pass: fills s.base (W <= kLook walkers) and returns their
+// number.  Each walker takes the first min(q, listed) nodes of its list, q
+// the largest number for which the rows fit kLook, and the first walkers with
+// more listed one more each while rows are left.  Every workgroup works this
+// out for itself; the first records it for the walk kernel.
+__device__ inline int pass_rows(const HeadArgs& a, int pass, int W, PassShared& s) {
+  static_assert(kLook <= kMaxTM && kThreads >= kLook && kLook % SRT_WAVE == 0, "a thread per walker");
+  const int tid = threadIdx.x, lane = tid % SRT_WAVE;
+  if (tid < kLook) {
+    const int b = tid < W ? min(max(a.act[(pass & 1) * a.B + tid], 0), a.B - 1) : -1;
+    s.cnt[tid] = b >= 0 ? min(max(a.cnt[b], 1), a.L) : 0;
+  }
+  __syncthreads();
+  constexpr int kPer = kLook / SRT_WAVE;
+  int c[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) c[k] = s.cnt[lane * kPer + k];
+  int q = 0, rows = 0;
+  for (int bit = kLook; bit >= 1; bit >>= 1) {
+    int v = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) v += min(c[k], q | bit);
+    v = wave_sum(v);
+    if (v <= kLook) {
+      q |= bit;
+      rows = v;
+    }
+  }
+  // walkers ahead of this lane that have more than q listed, and their rows
+  int more = 0, mine = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    more += c[k] > q;
+    mine += min(c[k], q);
+  }
+  int im = more, ir = mine;
+#pragma unroll
+  for (int off = 1; off < SRT_WAVE; off <<= 1) {
+    const int x = __shfl_up(im, off, SRT_WAVE), y = __shfl_up(ir, off, SRT_WAVE);
+    if (lane >= off) {
+      im += x;
+      ir += y;
+    }
+  }
+  const int left = kLook - rows, all_more = __shfl(im, SRT_WAVE - 1, SRT_WAVE);
+  const int total = rows + min(left, all_more);
+  int ahead = im - more, first = ir - mine;
+  if (tid < SRT_WAVE) {
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int i = lane * kPer + k;
+      s.base[i] = first + min(ahead, left);
+      const int n = min(c[k], q) + (c[k] > q && ahead < left);
+      if (blockIdx.x == 0 && i < W) a.span[i] = make_int2(s.base[i], n);
+      first += min(c[k], q);
+      ahead += c[k] > q;
+    }
+  }
+  __syncthreads();
+  return total;
+}
+
+// Offsets of rows m0 .. of the pass (a thread per row).  Beyond kLook walkers
+// every one brings its current node only.
+__device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_rows, int m0, PassShared& s) {
+  const int r = m0 + static_cast<int>(threadIdx.x);
+  static_assert(kThreads >= kMaxTM, "a thread per row");
+  if (threadIdx.x >= kMaxTM) return;
+  int64_t ho = 0, go = 0;
+  if (r < n_rows) {
+    int i = r, j = 0;
+    if (W <= kLook) {  // the walker whose rows hold r
+      int lo = 0, hi = W - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (s.base[mid] <= r) lo = mid;
+        else hi = mid - 1;
+      }
+      i = lo;
+      j = r - s.base[lo];
+    }
+    const int b = min(max(a.act[(pass & 1) * a.B + i], 0), a.B - 1);
+    const int u = min(max(a.list[static_cast<int64_t>(b) * a.L + j], 0), a.N - 1);
+    const int64_t node = static_cast<int64_t>(b) * a.N + u;
+    const int d = min(max(a.place[node] >> 16, 0), a.Dmax);
+    ho = node * a.dm;
+    go = (static_cast<int64_t>(b) * (a.Dmax + 1) + d) * a.V;
+  }
+  s.hoff[threadIdx.x] = ho;
+  s.goff[threadIdx.x] = go;
+}
+
+// acc += x y (32 x 32 x 16).  The accumulators stay in place; hazards that the
+// compiler would manage for its own form: products into one accumulator are
+// at least two products apart, operands come from loads (waited for as
+// register reads), and mfma_drain() stands before the accumulators are read.
+__device__ inline __attribute__((always_inline)) void mfma(f32x16& acc, bf16x8 x, bf16x8 y) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(x), "v"(y));
+}
+__device__ inline void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// Wave layouts of a tile: the 8 waves split its 256 head rows into WV groups
+// of 32 VT rows and the TM = 32 WS ST hidden rows into WS groups of 32 ST; a
+// wave multiplies its head rows with its hidden rows (VT x ST products a
+// step of 16).  kRing, kRingH: steps of head and hidden loads in registers (up
+// to 128 rows four; 256 rows leave room for two and one, and the hidden rows
+// come from the L2).
+struct Rows64 {
+  static constexpr int WV = 8, VT = 1, WS = 1, ST = 2, TM = 64, kRing = 4, kRingH = 4;
+};
+struct Rows128 {
+  static constexpr int WV = 4, VT = 2, WS = 2, ST = 2, TM = 128, kRing = 4, kRingH = 4;
+};
+struct Rows256 {
+  static constexpr int WV = 4, VT = 2, WS = 2, ST = 4, TM = 256, kRing = 2, kRingH = 1;
+};
+
+// One tile: head rows v0 .. v_end-1 (at most kTV) times the TM rows of the pass
+// from m0 on.  Both operands are staged in padded, double-buffered LDS.  Up
+// to 128 rows a pass is bound by streaming the head (4.2 TB/s at 128 rows, 5.1
+// at 64), above by the products (0.75 PFLOP/s at 256 rows; large matrix
+// products reach 1.2 on this card).  256 x 256 tiles read 0.75 KB of LDS a
+// product and stage each head row once for all rows (385 us -> 355 for 256
+// greedy rows against 128 x 128 tiles, two workgroups a CU).  Head operands
+// loaded straight into registers (16 rows of 64 bytes an instruction) took
+// 510: 64 separate 16-byte accesses an instruction keep the L1 busy.
 template <bool kNoise, typename Lay>
-__device__ inline void level_pass(const HeadArgs& a, int level, bool fin, int n_rows, uint8_t (*s_w)[kTV * kRowBytes],
-                                  uint8_t (*s_h)[kMaxTM * kRowBytes], unsigned long long* s_key) {
-  constexpr int TM = Lay::TM, HJ = TM / 32;
-  // block -> (head tile, sequence block) over the sequence blocks that have
-  // rows at this level, so the working blocks come first in dispatch order
-  // (blocks that exit at once, interleaved with working ones, leave CUs
-  // idle); consecutive blocks on one XCD take the sequence blocks of one
-  // tile, so the head rows they share come from its L2.
-  const int n_mb = (n_rows + TM - 1) / TM;
-  const int n_vt_pad = (a.n_vt + kXcds - 1) / kXcds * kXcds;
-  const int g = blockIdx.x;
-  if (g >= n_vt_pad * n_mb) return;
-  const int i = g / kXcds;
-  const int mb = i % n_mb;
-  const int vt = (i / n_mb) * kXcds + g % kXcds;
-  const int m0 = mb * TM;
-  if (vt >= a.n_vt) return;
-  const int v0 = vt * kTV;
-
-  const int tid = threadIdx.x;
+__device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v_end, int m0, int n_rows, int col) {
+  constexpr int TM = Lay::TM, VT = Lay::VT, ST = Lay::ST, R = Lay::kRing, RH = Lay::kRingH;
+  constexpr int WJ = kTV / kStageRows, HJ = TM / kStageRows;
+  static_assert(Lay::WV * Lay::WS == kWaves && 32 * Lay::WV * VT == kTV && 32 * Lay::WS * ST == TM, "layout");
+  // (values of its own for each layout: addresses that the compiler would
+  // otherwise work out once for all three take registers in every loop)
+  int tid = threadIdx.x;
+  v0 = __builtin_amdgcn_readfirstlane(v0);
+  asm volatile("" : "+v"(tid), "+s"(v0));
   const int lane = tid % SRT_WAVE;
   const int wave = __builtin_amdgcn_readfirstlane(tid / SRT_WAVE);
   const int l32 = lane % 32, hf = lane / 32;
   const int wv = wave % Lay::WV, ws = wave / Lay::WV;
 
-  // Global loads stage 16-byte column `col` of rows r0 + 32 j: eight
-  // consecutive threads read one row's 128-byte chunk, so every load
-  // instruction reads whole cache lines.  Head rows past V read row V - 1
-  // and sequence slots past the rows read the first sequence's root row
-  // (their products are never used), so every load is unconditional.
-  const int col = tid % 8, r0 = tid / 8;
-  const uint16_t* wp[4];
+  // Loads: 8 threads read one row's 128-byte line, so every load instruction
+  // reads whole lines.  Rows past the tile read its last row (never used).
+  const int lc = tid % 8, r0 = tid / 8;
+  const char* wbase = reinterpret_cast<const char*>(a.w_head + static_cast<int64_t>(v0) * a.dm);
+  uint32_t woff[WJ];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    wp[j] = a.w_head + static_cast<int64_t>(min(v0 + r0 + 32 * j, a.V - 1)) * a.dm + col * 8;
+  for (int j = 0; j < WJ; ++j)
+    woff[j] = static_cast<uint32_t>(min(r0 + kStageRows * j, v_end - v0 - 1)) * static_cast<uint32_t>(a.dm * 2) +
+              static_cast<uint32_t>(lc * 16);
   const uint16_t* hp[HJ];
 #pragma unroll
-  for (int j = 0; j < HJ; ++j) {
-    const int slot = m0 + r0 + 32 * j;
-    int64_t off = 0;
-    if (slot < n_rows) {
-      int b, u, d;
-      level_row(a, level, fin, slot, b, u, d);
-      off = (static_cast<int64_t>(b) * a.N + u) * a.dm;
-    }
-    hp[j] = a.hidden + off + col * 8;
-  }
+  for (int j = 0; j < HJ; ++j) hp[j] = a.hidden + s.hoff[r0 + kStageRows * j] + lc * 8;
 
-  const int n_chunks = a.dm / kKC;
-  // Chunk j of the head rows is loaded into wr[j % kInFlight] and chunk j of
-  // the hidden rows into hr[j % kInFlight], kInFlight steps before use, and
-  // copied to s_w / s_h[j % 2] one step before use.  Vector-memory loads
-  // retire in order, so every wait below is for loads issued kInFlight
-  // steps earlier and the loads of the steps since stay in flight.
-  // (Native vectors: HIP's uint4 class is kept in private memory here.)
-  u32x4 wr[kInFlight][4];
-  u32x4 hr[kInFlight][HJ];
-  auto wload = [&](int s, int c) __attribute__((always_inline)) {
-    c = min(c, n_chunks - 1);
+  const int n_steps = a.dm / kKC;
+  u32x4 wr[R][WJ], hr[RH][HJ];
+  auto hload = [&](int slot, int c) __attribute__((always_inline)) {
+    c = min(c, n_steps - 1);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) wr[s][j] = *reinterpret_cast<const u32x4*>(wp[j] + c * kKC);
+    for (int j = 0; j < HJ; ++j) hr[slot][j] = *reinterpret_cast<const u32x4*>(hp[j] + c * kKC);
   };
-  auto hload = [&](int s, int c) __attribute__((always_inline)) {
-    c = min(c, n_chunks - 1);
+  auto wload = [&](int slot, int c) __attribute__((always_inline)) {
+    const char* p = wbase + static_cast<int64_t>(min(c, n_steps - 1)) * (kKC * 2);
 #pragma unroll
-    for (int j = 0; j < HJ; ++j) hr[s][j] = *reinterpret_cast<const u32x4*>(hp[j] + c * kKC);
+    for (int j = 0; j < WJ; ++j) wr[slot][j] = *reinterpret_cast<const u32x4*>(p + woff[j]);
   };
-  auto stage = [&](int s, int buf) __attribute__((always_inline)) {
+  // Quarter `part` of the staging stores of step c (4: all of them).  With one
+  // step of hidden rows in registers these come last, as late as they can.
+  constexpr bool kLateH = RH < R;
+  auto stage = [&](int c, int part) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4*>(&s_w[buf][(r0 + 32 * j) * kRowBytes + col * 16]) = wr[s][j];
+    for (int j = 0; j < WJ; ++j)
+      if (part == 4 || j * (kLateH ? 2 : 4) / WJ == part)
+        *reinterpret_cast<u32x4*>(&s.w[c % 2][(r0 + kStageRows * j) * kRowBytes + lc * 16]) = wr[c % R][j];
 #pragma unroll
     for (int j = 0; j < HJ; ++j)
-      *reinterpret_cast<u32x4*>(&s_h[buf][(r0 + 32 * j) * kRowBytes + col * 16]) = hr[s][j];
+      if (part == 4 || (kLateH ? 2 + j * 2 / HJ : j * 4 / HJ) == part)
+        *reinterpret_cast<u32x4*>(&s.h[c % 2][(r0 + kStageRows * j) * kRowBytes + lc * 16]) = hr[c % RH][j];
   };
 
-  f32x16 acc[Lay::VT][Lay::ST];
+  f32x16 acc[VT][ST];
 #pragma unroll
-  for (int x = 0; x < Lay::VT; ++x)
+  for (int x = 0; x < VT; ++x)
 #pragma unroll
-    for (int y = 0; y < Lay::ST; ++y)
+    for (int y = 0; y < ST; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-  // A operand (head): rows 32 VT wv + 32 x + l32; B operand (hidden): rows
-  // 32 ST ws + 32 y + l32; elements 16 ks + 8 hf .. +7 of each step ks.
-  const int a_rd = (32 * Lay::VT * wv + l32) * kRowBytes + 16 * hf;
-  const int b_rd = (32 * Lay::ST * ws + l32) * kRowBytes + 16 * hf;
+  const int a_rd = (32 * VT * wv + l32) * kRowBytes + 16 * hf;
+  const int b_rd = (32 * ST * ws + l32) * kRowBytes + 16 * hf;
+  const bool active = __builtin_amdgcn_readfirstlane(v0 + 32 * VT * wv < v_end && m0 + 32 * ST * ws < n_rows);
 
-  // Step c (s = c % kInFlight): load head chunk c + kInFlight, multiply
-  // chunk c, stage chunk c + 1, load hidden chunk c + 1 + kInFlight.
-  // (always_inline: a lambda left out of line would take the register
-  // arrays it captures through private memory)
-  auto step = [&](int s, int c) __attribute__((always_inline)) {
-    wload(s, c + kInFlight);
-    bf16x8 af[4][Lay::VT], bfr[4][Lay::ST];
+  // Step c: loads of step c + R are issued (its slot was staged a step ago),
+  // step c is multiplied, step c + 1 is staged.  Loads retire in order, so
+  // each wait leaves the newer ones in flight.
+  auto step = [&](auto s_c, int c) __attribute__((always_inline)) {
+    constexpr int S = decltype(s_c)::value;
+    if (!kLateH) hload(S % RH, c + RH);
+    wload(S % R, c + R);
+    if (active) {
+      bf16x8 af[2][VT], bf[2][ST];
+      auto read = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
+        for (int x = 0; x < VT; ++x)
+          af[ks % 2][x] = *reinterpret_cast<const bf16x8*>(&s.w[S % 2][a_rd + 32 * x * kRowBytes + ks * 32]);
 #pragma unroll
-      for (int x = 0; x < Lay::VT; ++x)
-        af[ks][x] = *reinterpret_cast<const bf16x8*>(&s_w[s & 1][a_rd + 32 * x * kRowBytes + ks * 32]);
+        for (int y = 0; y < ST; ++y)
+          bf[ks % 2][y] = *reinterpret_cast<const bf16x8*>(&s.h[S % 2][b_rd + 32 * y * kRowBytes + ks * 32]);
+      };
+      read(0);
 #pragma unroll
-      for (int y = 0; y < Lay::ST; ++y)
-        bfr[ks][y] = *reinterpret_cast<const bf16x8*>(&s_h[s & 1][b_rd + 32 * y * kRowBytes + ks * 32]);
+      for (int ks = 0; ks < 4; ++ks) {
+        if (ks < 3) read(ks + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int y = 0; y < ST; ++y)
+#pragma unroll
+          for (int x = 0; x < VT; ++x) mfma(acc[x][y], af[ks % 2][x], bf[ks % 2][y]);
+        stage(S + 1, ks);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      stage(S + 1, 4);
     }
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int x = 0; x < Lay::VT; ++x)
-#pragma unroll
-        for (int y = 0; y < Lay::ST; ++y)
-          acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks][x], bfr[ks][y], acc[x][y], 0, 0, 0);
-    const int s1 = (s + 1) % kInFlight;
-    stage(s1, (s & 1) ^ 1);
-    hload(s1, c + 1 + kInFlight);
+    if (kLateH) hload((S + 1) % RH, c + 1 + RH);
     __syncthreads();
   };
-
-  // Prologue in the steady state's load order (as if steps -kInFlight ..
-  // -1 had run), so that the waits inside the loop count the same loads on
-  // entry as after a full iteration.
-  hload(0, 0);
+  // (in the steady state's order, so that the waits inside the loop count the
+  // same loads on entry)
 #pragma unroll
-  for (int s = 0; s < kInFlight; ++s) {
-    wload(s, s);
-    if (s == kInFlight - 1) stage(0, 0);
-    hload((s + 1) % kInFlight, s + 1);
+  for (int i = 0; i < R; ++i) {
+    if (i < RH) hload(i, i);
+    wload(i, i);
   }
+  stage(0, 4);
+  if (kLateH) hload(0, RH);
   __syncthreads();
-  const int groups = n_chunks / kInFlight;
-  for (int grp = 0; grp < groups; ++grp) {
-#pragma unroll
-    for (int s = 0; s < kInFlight; ++s) step(s, grp * kInFlight + s);
+  constexpr int U = R < 2 ? 2 : R;
+  int c = 0;
+  for (; c + U <= n_steps; c += U) {
+    step(std::integral_constant<int, 0>(), c);
+    step(std::integral_constant<int, 1>(), c + 1);
+    if constexpr (U > 2) {
+      step(std::integral_constant<int, 2>(), c + 2);
+      step(std::integral_constant<int, 3>(), c + 3);
+    }
   }
-#pragma unroll
-  for (int s = 0; s < kInFlight - 1; ++s)  // the last n_chunks % kInFlight chunks
-    if (s < n_chunks - groups * kInFlight) step(s, groups * kInFlight + s);
+  if (c < n_steps) step(std::integral_constant<int, 0>(), c);
+  if constexpr (U > 2) {
+    if (c + 1 < n_steps) step(std::integral_constant<int, 1>(), c + 1);
+    if (c + 2 < n_steps) step(std::integral_constant<int, 2>(), c + 2);
+  }
+  mfma_drain();
 
-  // Epilogue: lane column l32 of tile y is sequence slot m0 + 32 ST ws +
-  // 32 y + l32; element r of tile x is head row v0 + 32 VT wv + 32 x +
-  // 8 (r / 4) + 4 hf + r % 4.
+  // Epilogue: lane column l32 of tile y is row m0 + 32 ST ws + 32 y + l32 of the
+  // pass; element r of tile x is head row v0 + 32 VT wv + 32 x + 8 (r / 4) +
+  // 4 hf + r % 4.  (The keys take the staging buffers' place: every wave is
+  // past the last step's barrier.)
 #pragma unroll
-  for (int y = 0; y < Lay::ST; ++y) {
-    const int sl = 32 * Lay::ST * ws + 32 * y + l32;
-    const int slot = m0 + sl;
+  for (int y = 0; y < ST; ++y) {
+    const int sl = 32 * ST * ws + 32 * y + l32;
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
-    if (slot < n_rows) {
-      const float* gr = nullptr;
-      if (kNoise) {
-        int b, u, d;
-        level_row(a, level, fin, slot, b, u, d);
-        gr = a.gumbel + (static_cast<int64_t>(b) * (a.Dmax + 1) + d) * a.V;
-      }
+    if (active && m0 + sl < n_rows) {
+      const float* gr = kNoise ? a.gumbel + s.goff[sl] : nullptr;
 #pragma unroll
-      for (int x = 0; x < Lay::VT; ++x)
+      for (int x = 0; x < VT; ++x)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int vb = v0 + 32 * Lay::VT * wv + 32 * x + 8 * q + 4 * hf;
+          const int vb = v0 + 32 * VT * wv + 32 * x + 8 * q + 4 * hf;
           float gv[4] = {0.f, 0.f, 0.f, 0.f};
           if (kNoise) {
-            if (a.vec_noise && vb < a.V) {
-              const float4 g4 = *reinterpret_cast<const float4*>(gr + vb);
-              gv[0] = g4.x; gv[1] = g4.y; gv[2] = g4.z; gv[3] = g4.w;
+            if (a.vec_noise && vb < v_end) {
+              const f32x4 g = *reinterpret_cast<const f32x4*>(gr + vb);
+              gv[0] = g.x; gv[1] = g.y; gv[2] = g.z; gv[3] = g.w;
             } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) gv[e] = vb + e < a.V ? gr[vb + e] : 0.f;
+              for (int e = 0; e < 4; ++e) gv[e] = vb + e < v_end ? gr[vb + e] : 0.f;
             }
           }
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int v = vb + e;
-            if (v < a.V) {
+            if (vb + e < v_end) {
               float sc = acc[x][y][4 * q + e];
               if (kNoise) sc = __fadd_rn(__fmul_rn(sc, a.invT), gv[e]);
-              take(bv, bi, sc, v);
+              take(bv, bi, sc, vb + e);
             }
           }
         }
@@ -412,38 +522,63 @@ __device__ inline void level_pass(const HeadArgs& a, int level, bool fin, int n_
     const float ov = __shfl_xor(bv, 32, SRT_WAVE);
     const int oi = __shfl_xor(bi, 32, SRT_WAVE);
     take(bv, bi, ov, oi);
-    if (hf == 0) s_key[wv * TM + sl] = pack_key(bv, bi);
+    if (hf == 0) s.key[wv][sl] = pack_key(bv, bi);
   }
   __syncthreads();
   if (tid < TM && m0 + tid < n_rows) {
-    unsigned long long k = s_key[tid];
+    unsigned long long k = s.key[0][tid];
 #pragma unroll
-    for (int w = 1; w < Lay::WV; ++w) k = s_key[w * TM + tid] > k ? s_key[w * TM + tid] : k;
-    a.cand[static_cast<int64_t>(m0 + tid) * a.n_vt + vt] = k;
+    for (int w = 1; w < Lay::WV; ++w) k = s.key[w][tid] > k ? s.key[w][tid] : k;
+    a.cand[static_cast<int64_t>(m0 + tid) * a.n_cand + col] = k;
   }
+  __syncthreads();  // the keys' memory is the next tile's staging buffers
 }
 
-// One level's products and per-tile arg-max candidates.
+// One pass's products and per-tile arg-max candidates.  Workgroup g owns an
+// even share of the head's units, so that no CU is left with a tile more than
+// the others.
 template <bool kNoise>
-__global__ __launch_bounds__(kThreads) void head_level_kernel(HeadArgs a, int level) {
-  __shared__ __attribute__((aligned(16))) uint8_t s_w[2][kTV * kRowBytes];
-  __shared__ __attribute__((aligned(16))) uint8_t s_h[2][kMaxTM * kRowBytes];
-  __shared__ unsigned long long s_key[4 * 64];
-  const bool fin = finishing(a, level);
-  const int n_rows = fin ? a.fin_n[level] : a.n_act[level];
-  if (n_rows > kWideAbove)
-    level_pass<kNoise, Wide>(a, level, fin, n_rows, s_w, s_h, s_key);
-  else
-    level_pass<kNoise, Narrow>(a, level, fin, n_rows, s_w, s_h, s_key);
+__global__ __launch_bounds__(kThreads, 1) void head_pass_kernel(HeadArgs a, int pass) {
+  __shared__ __attribute__((aligned(16))) PassShared s;
+  const int W = a.n_act[pass];
+  if (W <= 0) return;
+  const int n_rows = W <= kLook ? pass_rows(a, pass, W, s) : W;
+  const int g = blockIdx.x;
+  if (n_rows <= kMaxTM) {
+    row_offsets(a, pass, W, n_rows, 0, s);
+    __syncthreads();
+  }
+  for (int t = 0; t < a.tiles; ++t) {
+    const int u0 = static_cast<int>(static_cast<int64_t>(t) * a.units / a.tiles);
+    const int nu = static_cast<int>(static_cast<int64_t>(t + 1) * a.units / a.tiles) - u0;
+    const int v0 = (u0 + static_cast<int>(static_cast<int64_t>(g) * nu / gridDim.x)) * kUnit;
+    const int v1 = min((u0 + static_cast<int>(static_cast<int64_t>(g + 1) * nu / gridDim.x)) * kUnit, a.V);
+    const int col = g * a.tiles + t;
+    for (int m0 = 0; m0 < n_rows; m0 += kMaxTM) {
+      if (v0 >= v1) {  // a share with a tile less: no candidate here
+        for (int r = m0 + threadIdx.x; r < min(n_rows, m0 + kMaxTM); r += kThreads)
+          a.cand[static_cast<int64_t>(r) * a.n_cand + col] = 0;
+        continue;
+      }
+      if (n_rows > kMaxTM) {
+        row_offsets(a, pass, W, n_rows, m0, s);
+        __syncthreads();
+      }
+      const int m = n_rows - m0;
+      if (m <= 64) head_tile<kNoise, Rows64>(a, s, v0, v1, m0, n_rows, col);
+      else if (m <= 128) head_tile<kNoise, Rows128>(a, s, v0, v1, m0, n_rows, col);
+      else head_tile<kNoise, Rows256>(a, s, v0, v1, m0, n_rows, col);
+    }
+  }
 }
 
 // Best candidate of one row over the tiles: every thread of the workgroup
 // takes a few, then a block reduction; the result is in every thread.
 __device__ inline unsigned long long row_best(const HeadArgs& a, int r, unsigned long long* s_best) {
   const int tid = threadIdx.x, lane = tid % SRT_WAVE, wave = tid / SRT_WAVE;
-  const unsigned long long* c = a.cand + static_cast<int64_t>(r) * a.n_vt;
+  const unsigned long long* c = a.cand + static_cast<int64_t>(r) * a.n_cand;
   unsigned long long best = 0;
-  for (int t = tid; t < a.n_vt; t += kWalkThreads) best = c[t] > best ? c[t] : best;
+  for (int t = tid; t < a.n_cand; t += kWalkThreads) best = c[t] > best ? c[t] : best;
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const unsigned long long o = shfl_xor_u64(best, off);
@@ -470,51 +605,55 @@ __device__ inline int find_child(const HeadArgs& a, int64_t tr, int u, int n, in
   return child;
 }
 
-// One workgroup per walking sequence.  Ordinary level: one step of the walk
-// from the row's candidates; a sequence that descends joins the next level
-// with its new node's subtree listed.  Finishing pass: the walk runs to its
-// end, every visited node's candidates found through the node-row table.
-__global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int level) {
+// One workgroup per walking sequence: the walk goes on through the nodes of
+// the pass; a sequence that leaves them for a node further down joins the
+// next pass with that node's subtree listed.
+__global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int pass) {
   __shared__ unsigned long long s_best[kWalkThreads / SRT_WAVE];
   __shared__ int s_next;
+  __shared__ int32_t s_par[kParents];
   const int slot = blockIdx.x;
-  if (slot >= a.n_act[level]) return;
-  const bool fin = finishing(a, level);
+  const int W = a.n_act[pass];
+  if (slot >= W) return;
   const int tid = threadIdx.x, lane = tid % SRT_WAVE, wave = tid / SRT_WAVE;
-  const int b = min(max(a.act[(level & 1) * a.B + slot], 0), a.B - 1);
+  const int b = min(max(a.act[(pass & 1) * a.B + slot], 0), a.B - 1);
   const int n = min(max(a.n_nodes[b], 1), a.N);
   const int64_t tr = static_cast<int64_t>(b) * a.N;
   const int64_t orow = static_cast<int64_t>(b) * (a.Dmax + 1);
-  int u = a.cur[b];
-  for (int k = level; k <= a.Dmax; ++k) {
-    const int r = fin ? min(max(a.rowtab[tr + u], 0), kFinishRows - 1) : slot;
-    const int tok = key_token(row_best(a, r, s_best));
+  const int2 span = W <= kLook ? a.span[slot] : make_int2(slot, 1);
+  int u = min(max(a.cur[b], 0), a.N - 1);
+  int at = 0;                                          // u's place in the list
+  int k = min(max(a.place[tr + u] >> 16, 0), a.Dmax);  // its depth = the walk's step
+  for (;;) {
+    const int tok = key_token(row_best(a, span.x + at, s_best));
     if (wave == 0) {
       const int child = k < a.Dmax ? find_child(a, tr, u, n, tok) : -1;
       if (lane == 0) {
         a.out_tokens[orow + k] = tok;
         if (child >= 0) {
           a.out_nodes[orow + k] = child;
-          a.cur[b] = child;
         } else {
           a.n_accepted[b] = k;
           if (a.n_emitted) a.n_emitted[b] = k + 1;
         }
         s_next = child;
       }
-      if (!fin && child >= 0) {
-        if (lane == 0) {
-          const int pos = atomicAdd(&a.n_act[level + 1], 1);
-          a.act[((level + 1) & 1) * a.B + pos] = b;
-        }
-        list_subtree(a, level + 1, b, child, k + 1, n);
-      }
     }
     __syncthreads();
-    const int next = s_next;
-    if (!fin || next < 0) break;
-    u = next;
+    if (s_next < 0) return;
+    u = s_next;
+    ++k;
+    at = a.place[tr + u] & 0xFFFF;
+    if (at >= span.y) break;
   }
+  __syncthreads();  // every wave has read the places that are rewritten now
+  if (wave > 0) return;
+  if (lane == 0) {
+    const int pos = atomicAdd(&a.n_act[pass + 1], 1);
+    a.act[((pass + 1) & 1) * a.B + pos] = b;
+  }
+  const int32_t* par = stage_parents(a, b, n, s_par);
+  list_subtree(a, b, u, k, n, par);
 }
 
 }  // namespace
@@ -541,10 +680,7 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   if (reinterpret_cast<uintptr_t>(scratch) & 255) return SRT_ERR_INVALID;
   const ScratchLayout L = scratch_layout(B, N, V);
   if (scratch_bytes < L.total) return SRT_ERR_CAPACITY;
-  const int64_t n_vt = (static_cast<int64_t>(V) + kTV - 1) / kTV;
-  const int64_t n_mb = (std::max<int64_t>(B, kFinishRows) + Narrow::TM - 1) / Narrow::TM;
-  const int64_t n_vt_pad = (n_vt + kXcds - 1) / kXcds * kXcds;
-  if (n_vt_pad * n_mb > 0x7FFFFFFF) return SRT_ERR_UNSUPPORTED;
+  const Split sp = split_for(V);
 
   char* base = static_cast<char*>(scratch);
   HeadArgs a;
@@ -559,38 +695,39 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.out_nodes = out_nodes;
   a.n_emitted = n_emitted;
   a.n_act = reinterpret_cast<int32_t*>(base);
-  a.fin_n = reinterpret_cast<int32_t*>(base + L.off_fin_n);
   a.act = reinterpret_cast<int32_t*>(base + L.off_act);
-  a.fin = reinterpret_cast<int32_t*>(base + L.off_fin);
   a.cur = reinterpret_cast<int32_t*>(base + L.off_cur);
-  a.rowtab = reinterpret_cast<int32_t*>(base + L.off_rowtab);
+  a.cnt = reinterpret_cast<int32_t*>(base + L.off_cnt);
+  a.span = reinterpret_cast<int2*>(base + L.off_span);
+  a.list = reinterpret_cast<int32_t*>(base + L.off_list);
+  a.place = reinterpret_cast<int32_t*>(base + L.off_place);
   a.cand = reinterpret_cast<unsigned long long*>(base + L.off_cand);
   a.B = B;
   a.N = N;
   a.dm = d_model;
   a.V = V;
   a.Dmax = Dmax;
-  a.n_vt = static_cast<int>(n_vt);
+  a.L = std::min(N, kLook);
+  a.n_cand = sp.grid * sp.tiles;
+  a.units = sp.units;
+  a.tiles = sp.tiles;
   a.invT = inv_temperature;
   a.vec_noise = gumbel && V % 4 == 0 && (reinterpret_cast<uintptr_t>(gumbel) & 15) == 0;
 
   hipStream_t s = as_stream(stream);
-  head_reset_kernel<<<1, 128, 0, s>>>(a);
+  head_init_kernel<<<B, SRT_WAVE, 0, s>>>(a);
   int st = launch_status();
-  if (st == SRT_OK) {
-    head_init_kernel<<<B, SRT_WAVE, 0, s>>>(a);
-    st = launch_status();
-  }
-  const unsigned grid = static_cast<unsigned>(n_vt_pad * n_mb);
-  const unsigned walk_grid = static_cast<unsigned>(B);
-  for (int level = 0; level <= Dmax && st == SRT_OK; ++level) {
-    if (gumbel)
-      head_level_kernel<true><<<grid, kThreads, 0, s>>>(a, level);
-    else
-      head_level_kernel<false><<<grid, kThreads, 0, s>>>(a, level);
+  // A walker's quota is at least kLook / B (see pass_rows), and a walk that
+  // leaves a pass has moved that many places on in its tree.
+  const int quota = std::max(1, kLook / B);
+  const int passes = std::min(Dmax + 1, (N - 1) / quota + 1);
+  const unsigned grid = static_cast<unsigned>(sp.grid);
+  for (int pass = 0; pass < passes && st == SRT_OK; ++pass) {
+    if (gumbel) head_pass_kernel<true><<<grid, kThreads, 0, s>>>(a, pass);
+    else head_pass_kernel<false><<<grid, kThreads, 0, s>>>(a, pass);
     st = launch_status();
     if (st != SRT_OK) break;
-    head_walk_kernel<<<walk_grid, kWalkThreads, 0, s>>>(a, level);
+    head_walk_kernel<<<static_cast<unsigned>(B), kWalkThreads, 0, s>>>(a, pass);
     st = launch_status();
   }
   return st;

@@ -120,3 +120,16 @@ def test_more_than_one_gpu_is_refused():
                        text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr
+
+
+def test_look_passes_fill_the_pass_and_end_with_the_walk():
+    # one 300-node chain walked 299 steps deep: 256 nodes a pass, then the rest;
+    # with a second sequence, a 10-node chain, the pass is shared 246 + 10
+    N, Dmax = 300, 299
+    tp = np.stack([np.arange(-1, N - 1), np.arange(-1, N - 1)]).astype(np.int32)
+    out_nodes = np.full((2, Dmax + 1), -1, np.int32)
+    out_nodes[0, :299] = np.arange(1, 300)
+    one = {"tree_parent": tp[:1], "n_nodes": np.array([N], np.int32)}
+    assert bench.look_passes(one, out_nodes[:1], np.array([300]), Dmax) == [256, 44]
+    two = {"tree_parent": tp, "n_nodes": np.array([N, 10], np.int32)}
+    assert bench.look_passes(two, out_nodes, np.array([300, 1]), Dmax) == [256, 54]

@@ -236,3 +236,54 @@ def test_qwen7b_head_sampled():
                          n, Dmax)
         assert_accept_equal(got, b, want, Dmax)
     assert got["n_accepted"].max() >= 4
+
+
+def planted_tree(rng, B, N, Dmax, V, deep):
+    """Random trees with a long chain first (`deep` nodes), the rest hanging on
+    random earlier nodes; tokens distinct among siblings as far as V allows."""
+    tt = np.full((B, N), -1, np.int32)
+    tp = np.full((B, N), -1, np.int32)
+    nn = rng.integers(1, N + 1, size=B).astype(np.int32)
+    nn[0] = N
+    for b in range(B):
+        n = int(nn[b])
+        chain = np.sort(rng.choice(np.arange(1, n), size=min(deep, n - 1), replace=False)) if n > 1 else []
+        last, on = 0, set(int(c) for c in chain)
+        for i in range(1, n):
+            tp[b, i] = last if i in on else rng.integers(0, i)
+            last = i if i in on else last
+        tt[b, :n] = rng.integers(0, V, size=n)
+    return {"tree_tokens": tt, "tree_parent": tp, "n_nodes": nn}
+
+
+@pytest.mark.parametrize("B,N,Dmax,V,d,deep,sampled", [
+    (1, 64, 20, 4096, 64, 20, True),      # one sequence: its whole tree in one pass
+    (2, 300, 40, 300, 128, 40, False),    # trees longer than a pass's list
+    (1, 1100, 63, 257, 64, 63, False),    # more nodes than the staged parents
+    (3, 200, 12, 17, 320, 12, True),      # units of 16 head rows: 2 of them, the last with one row
+    (31, 40, 10, 4113, 192, 10, False),   # uneven quotas, 258 units over 256 workgroups
+    (129, 24, 8, 65553, 64, 8, True),     # 129 walkers: 256-row layout; two tiles a workgroup
+    (256, 8, 6, 1000, 128, 6, False),     # exactly as many walkers as rows
+    (257, 16, 6, 1000, 448, 6, True),     # more walkers than rows: one node each
+])
+def test_passes_look_ahead(B, N, Dmax, V, d, deep, sampled):
+    rng = np.random.default_rng(B * 1000 + N)
+    say(f"lmhead passes: B={B} N={N} Dmax={Dmax} V={V} d={d}")
+    tree = planted_tree(rng, B, N, Dmax, V, deep)
+    hidden, w = W.make_head(B, N, d, V, device="cuda", seed=B + N, kind="int", tree_tokens=tree["tree_tokens"],
+                            tree_parent=tree["tree_parent"], n_nodes=tree["n_nodes"], plant_p=0.9)
+    # the chain's next token wins at most of its nodes (integers: sums stay exact)
+    for b in range(B):
+        for i in range(1, int(tree["n_nodes"][b])):
+            u = int(tree["tree_parent"][b, i])
+            if rng.random() < 0.3:
+                hidden[b, u] = w[int(tree["tree_tokens"][b, i])]
+    gumbel = torch.randint(-3, 4, (B, Dmax + 1, V), device="cuda").float() if sampled else None
+    got = run_fused(hidden, w, gumbel, 1.0, tree, Dmax)
+    if N <= 256:
+        assert_same(got, run_materialised(hidden, w, gumbel, 1.0, tree, Dmax), B)
+    else:  # beyond srt_accept's trees
+        want = oracle_rows(hidden, w, gumbel, 1.0, tree, range(B), Dmax)
+        for b in range(B):
+            assert_accept_equal(got, b, want[b], Dmax)
+    assert got["n_accepted"].max() >= 2
