@@ -36,17 +36,15 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// 16-byte loads of noise rows, which start at any multiple of 4 bytes (the
+// hardware's requirement) when V is not a multiple of 4.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kWaves = 8;
-constexpr int kThreads = kWaves * SRT_WAVE;
-constexpr int kTV = 256;                 // head rows of a tile
 constexpr int kUnit = 16;                // head rows are shared out in units of 16
 constexpr int kKC = 64;                  // d_model elements per step (one 128-byte line of a row)
 constexpr int kRowBytes = kKC * 2 + 16;  // padded LDS row (conflict-free operand reads)
-constexpr int kStageRows = kThreads / 8; // rows staged by one load of every thread
-constexpr int kMaxTM = 256;              // rows of a pass multiplied together
 // Rows that a pass is filled up to.  One pass over a 152064 x 3584 head takes
 // 221 us for 64 rows, 260 for 128 and 380 for 256 (sampled; reading the head
 // alone takes 190), and the walks of 256 sequences, 13 levels deep, take 6
@@ -54,10 +52,11 @@ constexpr int kMaxTM = 256;              // rows of a pass multiplied together
 // and 11 passes (2.70 ms) one level at a time with a last pass over what is left.
 constexpr int kLook = 256;
 constexpr int kMaxLevels = 64;           // Dmax + 1 <= 64
-constexpr int kGrid = 256;               // workgroups of a pass, at most: one per CU
+constexpr int kGrid = 256;               // workgroups of a pass over a large head: one per CU
+constexpr int kXcds = 8;
 constexpr int kWalkThreads = 256;
 constexpr int kParents = 1024;           // nodes of a tree whose parents are staged in LDS
-constexpr int kUncovered = 0xFFFF;       // place of a subtree node beyond every pass
+constexpr int kUncovered = 0x7FFFFFFF;   // place of a subtree node beyond every pass
 
 struct HeadArgs {
   const uint16_t* hidden;   // [B, N, dm]
@@ -71,57 +70,75 @@ struct HeadArgs {
   int32_t* out_nodes;
   int32_t* n_emitted;
   int32_t* n_act;           // [kMaxLevels + 1] walking sequences per pass
-  int32_t* act;             // [2, B] walking sequences, by pass parity
-  int32_t* cur;             // [B] current node of each sequence
-  int32_t* cnt;             // [B] nodes listed for it (its subtree's first kLook at most)
+  int2* act;                // [2, B] walking sequences and their listed nodes, by pass parity
   int2* span;               // [kLook] first row and row count of each walker of the pass
-  int32_t* list;            // [B, min(N, kLook)] those nodes
-  int32_t* place;           // [B, N] place of a node in its list | depth << 16
+  int2* list;               // [B, min(N, kLook)] (node, depth) of each sequence's next subtree
+  int32_t* place;           // [B, N] place of a node in its list
   unsigned long long* cand; // [max(B, kLook), n_cand] packed candidates of the pass
   int B, N, L, dm, V, Dmax, n_cand;
-  int units, tiles;         // 16-row units of the head; tiles per workgroup
-  int vec_noise;            // gumbel rows can be read as float4
+  int look;                 // rows that a pass is filled up to (<= kLook)
+  int units, tiles;         // see Split
   float invT;
 };
 
-// How a pass divides the head: 16-row units shared out evenly over at most
-// kGrid workgroups, each of which reads its share in tiles of up to kTV rows.
+// How a pass divides the head.  Large heads (wide): 16-row units shared out
+// evenly over at most kGrid workgroups, one per CU, each of which reads its
+// share in tiles of up to 256 rows.  Small ones: 128-row tiles, a workgroup
+// for each and 64 rows of the pass.
 struct Split {
-  int units, grid, tiles;
+  bool wide;
+  int units, grid, tiles;  // wide: units, workgroups, tiles per workgroup; else tiles in all
 };
 
-inline Split split_for(int64_t V) {
+// A head that the caches hold is not worth keeping every CU streaming for:
+// there more, smaller workgroups finish a pass sooner (56 sequences, 20-node
+// trees, V 7918, d 1472, greedy: 71 us on wide tiles, 63 on small ones; 27
+// sequences, 7 nodes, V 14227, d 1280, sampled: 38 and 33).
+constexpr int64_t kWideBytes = int64_t(128) << 20;
+
+inline Split split_for(int64_t V, int64_t d_model) {
   Split s;
+  s.wide = V >= 128 * kGrid && V * d_model * 2 >= kWideBytes;
+  if (!s.wide) {
+    s.units = s.grid = 0;
+    s.tiles = static_cast<int>((V + 127) / 128);
+    return s;
+  }
   s.units = static_cast<int>((V + kUnit - 1) / kUnit);
-  s.grid = std::min(kGrid, s.units);
-  const int per = s.grid * (kTV / kUnit);
+  s.grid = kGrid;
+  const int per = s.grid * (256 / kUnit);
   s.tiles = (s.units + per - 1) / per;
   return s;
 }
 
-// Scratch layout: counters, lists, current nodes, node places, candidates.
+// Rows that passes over a head of this width are filled up to: nearly free up
+// to kLook while a pass is bound by reading the head or by its own latency,
+// less for a narrow head, whose rows' noise (4 V bytes each, against 2 d_model
+// V for the head) soon costs as much.  Walks of at most three steps end about
+// as soon with 64 rows (21 sequences, 47-node trees, V 15805, d 2176, depth 2:
+// two passes either way, 68 us filled to 256 rows and 56 filled to 64).
+inline int look_for(int d_model, int Dmax) {
+  return Dmax <= 2 ? 64 : std::min(kLook, std::max(64, d_model / 4 / 64 * 64));
+}
+
+// Scratch layout: counters, lists, node places, candidates.
 struct ScratchLayout {
-  size_t off_act, off_cur, off_cnt, off_span, off_list, off_place, off_cand, total;
+  size_t off_act, off_span, off_list, off_place, off_cand, total;
 };
 
 inline ScratchLayout scratch_layout(int64_t B, int64_t N, int64_t V) {
   auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
   ScratchLayout s;
-  const Split sp = split_for(V);
   const size_t b = static_cast<size_t>(B), n = static_cast<size_t>(N);
   s.off_act = up(sizeof(int32_t) * (kMaxLevels + 1));
-  s.off_cur = s.off_act + up(sizeof(int32_t) * 2 * b);
-  s.off_cnt = s.off_cur + up(sizeof(int32_t) * b);
-  s.off_span = s.off_cnt + up(sizeof(int32_t) * b);
+  s.off_span = s.off_act + up(sizeof(int2) * 2 * b);
   s.off_list = s.off_span + up(sizeof(int2) * kLook);
-  s.off_place = s.off_list + up(sizeof(int32_t) * b * std::min<size_t>(n, kLook));
+  s.off_place = s.off_list + up(sizeof(int2) * b * std::min<size_t>(n, kLook));
   s.off_cand = s.off_place + up(sizeof(int32_t) * b * n);
+  // one candidate per row and 128 head rows (the wide division has no more:
+  // kGrid per 256 kGrid rows, from 128 kGrid rows on)
   s.total = s.off_cand +
-            up(sizeof(unsigned long long) * std::max<size_t>(b, kLook) * static_cast<size_t>(sp.grid) * sp.tiles);
-  // At least a 128-row table of candidates per 128 head rows, as callers may
-  // have sized their buffer by that.
-  const size_t by_tile = sizeof(unsigned long long) * std::max<size_t>(b, 128) * ((static_cast<size_t>(V) + 127) / 128);
-  s.total = std::max(s.total, up(sizeof(int32_t) * (3 * b + b * n + 1024)) + up(by_tile) + 1024);
+            up(sizeof(unsigned long long) * std::max<size_t>(b, kLook) * ((static_cast<size_t>(V) + 127) / 128));
   return s;
 }
 
@@ -146,11 +163,11 @@ __device__ inline void take(float& bv, int& bi, float v, int i) {
 
 // One wave lists the subtree of node u of sequence b (u at depth du, nodes of
 // depth <= Dmax, in tree order): the first a.L nodes go to the list, every
-// node learns its place and depth.  Descendants have larger indices; a
+// node learns its place; returns the number listed.  Descendants have larger indices; a
 // node's ancestry is followed up through parents with smaller indices only,
 // so malformed parent links end the search.  `par`: the tree's parents in
 // LDS (staged), or null.
-__device__ inline void list_subtree(const HeadArgs& a, int b, int u, int du, int n, const int32_t* par) {
+__device__ inline int list_subtree(const HeadArgs& a, int b, int u, int du, int n, const int32_t* par) {
   const int lane = threadIdx.x % SRT_WAVE;
   const int64_t tr = static_cast<int64_t>(b) * a.N;
   int base = 0;
@@ -170,24 +187,12 @@ __device__ inline void list_subtree(const HeadArgs& a, int b, int u, int du, int
     const unsigned long long m = __ballot(depth >= 0);
     if (depth >= 0) {
       const int j = base + __popcll(m & ((1ull << lane) - 1));
-      if (j < a.L) a.list[static_cast<int64_t>(b) * a.L + j] = c;
-      a.place[tr + c] = (j < a.L ? j : kUncovered) | (depth << 16);
+      if (j < a.L) a.list[static_cast<int64_t>(b) * a.L + j] = make_int2(c, depth);
+      a.place[tr + c] = j < a.L ? j : kUncovered;
     }
     base += __popcll(m);
   }
-  if (lane == 0) {
-    a.cur[b] = u;
-    a.cnt[b] = min(base, a.L);
-  }
-}
-
-// Stages a tree's parents in LDS if they fit (one wave); null if not.
-__device__ inline const int32_t* stage_parents(const HeadArgs& a, int b, int n, int32_t* s_par) {
-  if (n > kParents) return nullptr;
-  const int lane = threadIdx.x % SRT_WAVE;
-  for (int c = lane; c < n; c += SRT_WAVE) s_par[c] = a.tree_parent[static_cast<int64_t>(b) * a.N + c];
-  __builtin_amdgcn_wave_barrier();
-  return s_par;
+  return min(base, a.L);
 }
 
 // One wave per sequence: outputs to -1, walking from the root with its whole
@@ -203,61 +208,62 @@ __global__ __launch_bounds__(SRT_WAVE) void head_init_kernel(HeadArgs a) {
     a.out_tokens[row + k] = -1;
     a.out_nodes[row + k] = -1;
   }
-  if (lane == 0) a.act[b] = b;
   const int n = min(max(a.n_nodes[b], 1), a.N);
-  const int32_t* par = stage_parents(a, b, n, s_par);
+  if (n <= kParents)
+    for (int c = lane; c < n; c += SRT_WAVE) s_par[c] = a.tree_parent[static_cast<int64_t>(b) * a.N + c];
   __syncthreads();
-  list_subtree(a, b, 0, 0, n, par);
+  const int listed = list_subtree(a, b, 0, 0, n, n <= kParents ? s_par : nullptr);
+  if (lane == 0) a.act[b] = make_int2(b, listed);
 }
 
-// LDS of a product kernel (152 of the CU's 160 KB).
+// LDS of a product kernel: TV head rows and TM hidden rows a tile.
+template <int TV, int TM>
 struct PassShared {
   union {
     struct {
-      uint8_t w[2][kTV * kRowBytes];           // head rows of two steps
-      uint8_t h[2][kMaxTM * kRowBytes];        // hidden rows of two steps
+      uint8_t w[2][TV * kRowBytes];              // head rows of two steps
+      uint8_t h[2][TM * kRowBytes];              // hidden rows of two steps
     };
-    unsigned long long key[kWaves][kMaxTM];    // after the steps
+    unsigned long long key[8][TM];               // after the steps, by wave
   };
-  int64_t hoff[kMaxTM], goff[kMaxTM];          // a row's hidden and noise offsets
-  int base[kMaxTM];                            // first row of each walker
-  int cnt[kMaxTM];
+  int64_t hoff[TM], goff[TM];                    // a row's hidden and noise offsets
+  int base[kLook];                               // first row of each walker
+  alignas(16) int cnt[kLook];                    // its listed nodes
+  int seq[kLook];                                // its sequence
+  int rows;                                      // rows at the quota
 };
-
-__device__ inline int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, SRT_WAVE);
-  return v;
-}
 
 // Rows of the pass: fills s.base (W <= kLook walkers) and returns their
 // number.  Each walker takes the first min(q, listed) nodes of its list, q
-// the largest number for which the rows fit kLook, and the first walkers with
-// more listed one more each while rows are left.  Every workgroup works this
-// out for itself; the first records it for the walk kernel.
-__device__ inline int pass_rows(const HeadArgs& a, int pass, int W, PassShared& s) {
-  static_assert(kLook <= kMaxTM && kThreads >= kLook && kLook % SRT_WAVE == 0, "a thread per walker");
+// the largest number for which the rows fit, and the first walkers with more
+// listed one more each while rows are left.  Every workgroup works this out
+// for itself; the first records it for the walk kernel.
+template <typename Shared>
+__device__ inline int pass_rows(const HeadArgs& a, int pass, int W, Shared& s) {
+  static_assert(kLook == 256 && kLook % SRT_WAVE == 0, "a thread per walker (workgroups have 256 or more)");
   const int tid = threadIdx.x, lane = tid % SRT_WAVE;
+  const int look = max(a.look, W);
   if (tid < kLook) {
-    const int b = tid < W ? min(max(a.act[(pass & 1) * a.B + tid], 0), a.B - 1) : -1;
-    s.cnt[tid] = b >= 0 ? min(max(a.cnt[b], 1), a.L) : 0;
+    const int2 x = tid < W ? a.act[static_cast<int64_t>(pass & 1) * a.B + tid] : make_int2(0, 0);
+    s.seq[tid] = min(max(x.x, 0), a.B - 1);
+    s.cnt[tid] = tid < W ? min(max(x.y, 1), a.L) : 0;
   }
   __syncthreads();
+  // thread t tries the quota t + 1 (the rows grow with it; 1 always fits)
+  int v = 0;
+  if (tid < kLook)
+    for (int i = 0; i < W; i += 4) {  // (entries past W are 0)
+      const int4 c4 = *reinterpret_cast<const int4*>(&s.cnt[i]);
+      v += min(c4.x, tid + 1) + min(c4.y, tid + 1) + min(c4.z, tid + 1) + min(c4.w, tid + 1);
+    }
+  const int q = __syncthreads_count(tid < kLook && v <= look);
+  if (tid == q - 1) s.rows = v;
+  __syncthreads();
+  const int rows = s.rows;
   constexpr int kPer = kLook / SRT_WAVE;
   int c[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) c[k] = s.cnt[lane * kPer + k];
-  int q = 0, rows = 0;
-  for (int bit = kLook; bit >= 1; bit >>= 1) {
-    int v = 0;
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) v += min(c[k], q | bit);
-    v = wave_sum(v);
-    if (v <= kLook) {
-      q |= bit;
-      rows = v;
-    }
-  }
   // walkers ahead of this lane that have more than q listed, and their rows
   int more = 0, mine = 0;
 #pragma unroll
@@ -274,7 +280,7 @@ __device__ inline int pass_rows(const HeadArgs& a, int pass, int W, PassShared& 
       ir += y;
     }
   }
-  const int left = kLook - rows, all_more = __shfl(im, SRT_WAVE - 1, SRT_WAVE);
+  const int left = look - rows, all_more = __shfl(im, SRT_WAVE - 1, SRT_WAVE);
   const int total = rows + min(left, all_more);
   int ahead = im - more, first = ir - mine;
   if (tid < SRT_WAVE) {
@@ -292,15 +298,15 @@ __device__ inline int pass_rows(const HeadArgs& a, int pass, int W, PassShared& 
   return total;
 }
 
-// Offsets of rows m0 .. of the pass (a thread per row).  Beyond kLook walkers
-// every one brings its current node only.
-__device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_rows, int m0, PassShared& s) {
+// Offsets of rows m0 .. m0 + TM - 1 of the pass (a thread per row).  Beyond
+// kLook walkers every one brings its current node only.
+template <int TM, typename Shared>
+__device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_rows, int m0, Shared& s) {
   const int r = m0 + static_cast<int>(threadIdx.x);
-  static_assert(kThreads >= kMaxTM, "a thread per row");
-  if (threadIdx.x >= kMaxTM) return;
+  if (threadIdx.x >= TM) return;
   int64_t ho = 0, go = 0;
   if (r < n_rows) {
-    int i = r, j = 0;
+    int b, j = 0;
     if (W <= kLook) {  // the walker whose rows hold r
       int lo = 0, hi = W - 1;
       while (lo < hi) {
@@ -308,63 +314,59 @@ __device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_row
         if (s.base[mid] <= r) lo = mid;
         else hi = mid - 1;
       }
-      i = lo;
+      b = s.seq[lo];
       j = r - s.base[lo];
+    } else {
+      b = min(max(a.act[static_cast<int64_t>(pass & 1) * a.B + r].x, 0), a.B - 1);
     }
-    const int b = min(max(a.act[(pass & 1) * a.B + i], 0), a.B - 1);
-    const int u = min(max(a.list[static_cast<int64_t>(b) * a.L + j], 0), a.N - 1);
-    const int64_t node = static_cast<int64_t>(b) * a.N + u;
-    const int d = min(max(a.place[node] >> 16, 0), a.Dmax);
-    ho = node * a.dm;
-    go = (static_cast<int64_t>(b) * (a.Dmax + 1) + d) * a.V;
+    const int2 x = a.list[static_cast<int64_t>(b) * a.L + j];
+    ho = (static_cast<int64_t>(b) * a.N + min(max(x.x, 0), a.N - 1)) * a.dm;
+    go = (static_cast<int64_t>(b) * (a.Dmax + 1) + min(max(x.y, 0), a.Dmax)) * a.V;
   }
   s.hoff[threadIdx.x] = ho;
   s.goff[threadIdx.x] = go;
 }
 
-// acc += x y (32 x 32 x 16).  The accumulators stay in place; hazards that the
-// compiler would manage for its own form: products into one accumulator are
-// at least two products apart, operands come from loads (waited for as
-// register reads), and mfma_drain() stands before the accumulators are read.
-__device__ inline __attribute__((always_inline)) void mfma(f32x16& acc, bf16x8 x, bf16x8 y) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(x), "v"(y));
-}
-__device__ inline void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-
-// Wave layouts of a tile: the 8 waves split its 256 head rows into WV groups
-// of 32 VT rows and the TM = 32 WS ST hidden rows into WS groups of 32 ST; a
-// wave multiplies its head rows with its hidden rows (VT x ST products a
-// step of 16).  kRing, kRingH: steps of head and hidden loads in registers (up
-// to 128 rows four; 256 rows leave room for two and one, and the hidden rows
-// come from the L2).
+// Wave layouts of a tile: the WV x WS waves split its TV = 32 WV VT head rows
+// and its TM = 32 WS ST hidden rows; a wave multiplies its head rows with its
+// hidden rows (VT x ST products a step of 16).  kRing, kRingH: steps of head
+// and hidden loads in registers (256 rows leave room for two and one, and the
+// hidden rows come from the L2).
 struct Rows64 {
-  static constexpr int WV = 8, VT = 1, WS = 1, ST = 2, TM = 64, kRing = 4, kRingH = 4;
+  static constexpr int WV = 8, VT = 1, WS = 1, ST = 2, kRing = 4, kRingH = 4;
 };
 struct Rows128 {
-  static constexpr int WV = 4, VT = 2, WS = 2, ST = 2, TM = 128, kRing = 4, kRingH = 4;
+  static constexpr int WV = 4, VT = 2, WS = 2, ST = 2, kRing = 4, kRingH = 4;
 };
 struct Rows256 {
-  static constexpr int WV = 4, VT = 2, WS = 2, ST = 4, TM = 256, kRing = 2, kRingH = 1;
+  static constexpr int WV = 4, VT = 2, WS = 2, ST = 4, kRing = 2, kRingH = 1;
+};
+struct Small {
+  static constexpr int WV = 4, VT = 1, WS = 1, ST = 2, kRing = 4, kRingH = 4;
 };
 
-// One tile: head rows v0 .. v_end-1 (at most kTV) times the TM rows of the pass
-// from m0 on.  Both operands are staged in padded, double-buffered LDS.  Up
-// to 128 rows a pass is bound by streaming the head (4.2 TB/s at 128 rows, 5.1
-// at 64), above by the products (0.75 PFLOP/s at 256 rows; large matrix
-// products reach 1.2 on this card).  256 x 256 tiles read 0.75 KB of LDS a
-// product and stage each head row once for all rows (385 us -> 355 for 256
-// greedy rows against 128 x 128 tiles, two workgroups a CU).  Head operands
+// One tile: head rows v0 .. v_end-1 (at most TV) times the TM rows of the pass
+// from m0 on (m_end: the end of this workgroup's rows).  Both operands are staged in padded, double-buffered
+// LDS.  Up to 128 rows a pass is bound by streaming the head (4.2 TB/s at 128
+// rows, 5.1 at 64), above by the products (0.75 PFLOP/s at 256 rows; large
+// matrix products reach 1.2 on this card).  256 x 256 tiles read 0.75 KB of
+// LDS a product and stage each head row once for all rows (385 us -> 355 for
+// 256 greedy rows against 128 x 128 tiles, two workgroups a CU).  Head operands
 // loaded straight into registers (16 rows of 64 bytes an instruction) took
-// 510: 64 separate 16-byte accesses an instruction keep the L1 busy.
-template <bool kNoise, typename Lay>
-__device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v_end, int m0, int n_rows, int col) {
-  constexpr int TM = Lay::TM, VT = Lay::VT, ST = Lay::ST, R = Lay::kRing, RH = Lay::kRingH;
-  constexpr int WJ = kTV / kStageRows, HJ = TM / kStageRows;
-  static_assert(Lay::WV * Lay::WS == kWaves && 32 * Lay::WV * VT == kTV && 32 * Lay::WS * ST == TM, "layout");
+// 510: 64 separate 16-byte accesses an instruction keep the L1 busy.  Issuing a
+// tile's first loads before the epilogue of the one before it cost 14-23 us at
+// 128 rows (loads retire in order, so the noise waits for them).
+template <bool kNoise, typename Lay, typename Shared>
+__device__ inline void head_tile(const HeadArgs& a, Shared& s, int v0, int v_end, int m0, int m_end, int col) {
+  constexpr int VT = Lay::VT, ST = Lay::ST, R = Lay::kRing, RH = Lay::kRingH;
+  constexpr int TV = 32 * Lay::WV * VT, TM = 32 * Lay::WS * ST;
+  constexpr int kStageRows = Lay::WV * Lay::WS * SRT_WAVE / 8;  // rows staged by one load of every thread
+  constexpr int WJ = TV / kStageRows, HJ = TM / kStageRows;
   // (values of its own for each layout: addresses that the compiler would
   // otherwise work out once for all three take registers in every loop)
   int tid = threadIdx.x;
   v0 = __builtin_amdgcn_readfirstlane(v0);
+  v_end = __builtin_amdgcn_readfirstlane(v_end);
   asm volatile("" : "+v"(tid), "+s"(v0));
   const int lane = tid % SRT_WAVE;
   const int wave = __builtin_amdgcn_readfirstlane(tid / SRT_WAVE);
@@ -410,6 +412,9 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
         *reinterpret_cast<u32x4*>(&s.h[c % 2][(r0 + kStageRows * j) * kRowBytes + lc * 16]) = hr[c % RH][j];
   };
 
+  const int a_rd = (32 * VT * wv + l32) * kRowBytes + 16 * hf;
+  const int b_rd = (32 * ST * ws + l32) * kRowBytes + 16 * hf;
+  const bool active = __builtin_amdgcn_readfirstlane(v0 + 32 * VT * wv < v_end && m0 + 32 * ST * ws < m_end);
   f32x16 acc[VT][ST];
 #pragma unroll
   for (int x = 0; x < VT; ++x)
@@ -417,9 +422,6 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
     for (int y = 0; y < ST; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-  const int a_rd = (32 * VT * wv + l32) * kRowBytes + 16 * hf;
-  const int b_rd = (32 * ST * ws + l32) * kRowBytes + 16 * hf;
-  const bool active = __builtin_amdgcn_readfirstlane(v0 + 32 * VT * wv < v_end && m0 + 32 * ST * ws < n_rows);
 
   // Step c: loads of step c + R are issued (its slot was staged a step ago),
   // step c is multiplied, step c + 1 is staged.  Loads retire in order, so
@@ -429,25 +431,36 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
     if (!kLateH) hload(S % RH, c + RH);
     wload(S % R, c + R);
     if (active) {
-      bf16x8 af[2][VT], bf[2][ST];
-      auto read = [&](int ks) __attribute__((always_inline)) {
+      // Operands are read one group of products ahead: a group is the whole of
+      // a 16-wide step, or half its hidden rows where four of them would
+      // leave too few registers.
+      constexpr int YH = ST > 2 ? 2 : 1, SY = ST / YH;
+      bf16x8 af[2][VT], bf[2][SY];
+      auto read = [&](int i) __attribute__((always_inline)) {
+        const int ks = i / YH;
+        if (i % YH == 0) {
 #pragma unroll
-        for (int x = 0; x < VT; ++x)
-          af[ks % 2][x] = *reinterpret_cast<const bf16x8*>(&s.w[S % 2][a_rd + 32 * x * kRowBytes + ks * 32]);
+          for (int x = 0; x < VT; ++x)
+            af[ks % 2][x] = *reinterpret_cast<const bf16x8*>(&s.w[S % 2][a_rd + 32 * x * kRowBytes + ks * 32]);
+        }
 #pragma unroll
-        for (int y = 0; y < ST; ++y)
-          bf[ks % 2][y] = *reinterpret_cast<const bf16x8*>(&s.h[S % 2][b_rd + 32 * y * kRowBytes + ks * 32]);
+        for (int y = 0; y < SY; ++y)
+          bf[i % 2][y] =
+              *reinterpret_cast<const bf16x8*>(&s.h[S % 2][b_rd + 32 * (i % YH * SY + y) * kRowBytes + ks * 32]);
       };
       read(0);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        if (ks < 3) read(ks + 1);
+      for (int i = 0; i < 4 * YH; ++i) {
+        const int ks = i / YH;
+        if (i + 1 < 4 * YH) read(i + 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int y = 0; y < ST; ++y)
+        for (int y = 0; y < SY; ++y)
 #pragma unroll
-          for (int x = 0; x < VT; ++x) mfma(acc[x][y], af[ks % 2][x], bf[ks % 2][y]);
-        stage(S + 1, ks);
+          for (int x = 0; x < VT; ++x)
+            acc[x][i % YH * SY + y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks % 2][x], bf[i % 2][y],
+                                                                              acc[x][i % YH * SY + y], 0, 0, 0);
+        if (i % YH == YH - 1) stage(S + 1, ks);
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
@@ -481,7 +494,6 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
     if (c + 1 < n_steps) step(std::integral_constant<int, 1>(), c + 1);
     if (c + 2 < n_steps) step(std::integral_constant<int, 2>(), c + 2);
   }
-  mfma_drain();
 
   // Epilogue: lane column l32 of tile y is row m0 + 32 ST ws + 32 y + l32 of the
   // pass; element r of tile x is head row v0 + 32 VT wv + 32 x + 8 (r / 4) +
@@ -492,7 +504,7 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
     const int sl = 32 * ST * ws + 32 * y + l32;
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
-    if (active && m0 + sl < n_rows) {
+    if (active && m0 + sl < m_end) {
       const float* gr = kNoise ? a.gumbel + s.goff[sl] : nullptr;
 #pragma unroll
       for (int x = 0; x < VT; ++x)
@@ -501,8 +513,8 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
           const int vb = v0 + 32 * VT * wv + 32 * x + 8 * q + 4 * hf;
           float gv[4] = {0.f, 0.f, 0.f, 0.f};
           if (kNoise) {
-            if (a.vec_noise && vb < v_end) {
-              const f32x4 g = *reinterpret_cast<const f32x4*>(gr + vb);
+            if (vb + 4 <= v_end) {
+              const f32x4 g = *reinterpret_cast<const f32x4u*>(gr + vb);
               gv[0] = g.x; gv[1] = g.y; gv[2] = g.z; gv[3] = g.w;
             } else {
 #pragma unroll
@@ -525,7 +537,7 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
     if (hf == 0) s.key[wv][sl] = pack_key(bv, bi);
   }
   __syncthreads();
-  if (tid < TM && m0 + tid < n_rows) {
+  if (tid < TM && m0 + tid < m_end) {
     unsigned long long k = s.key[0][tid];
 #pragma unroll
     for (int w = 1; w < Lay::WV; ++w) k = s.key[w][tid] > k ? s.key[w][tid] : k;
@@ -534,42 +546,58 @@ __device__ inline void head_tile(const HeadArgs& a, PassShared& s, int v0, int v
   __syncthreads();  // the keys' memory is the next tile's staging buffers
 }
 
-// One pass's products and per-tile arg-max candidates.  Workgroup g owns an
-// even share of the head's units, so that no CU is left with a tile more than
-// the others.
+// One pass's products and per-tile arg-max candidates over a large head.  The
+// workgroups share the head's units out evenly (so that no CU is left with a
+// tile more than the others), the shares of one tile next to each other.
 template <bool kNoise>
-__global__ __launch_bounds__(kThreads, 1) void head_pass_kernel(HeadArgs a, int pass) {
-  __shared__ __attribute__((aligned(16))) PassShared s;
+__global__ __launch_bounds__(512, 1) void head_pass_kernel(HeadArgs a, int pass) {
+  using Shared = PassShared<256, 256>;  // 151 of the CU's 160 KB
+  __shared__ __attribute__((aligned(16))) Shared s;
   const int W = a.n_act[pass];
   if (W <= 0) return;
   const int n_rows = W <= kLook ? pass_rows(a, pass, W, s) : W;
-  const int g = blockIdx.x;
-  if (n_rows <= kMaxTM) {
-    row_offsets(a, pass, W, n_rows, 0, s);
+  const int g = blockIdx.x, shares = gridDim.x;
+  for (int m0 = 0; m0 < n_rows; m0 += 256) {
+    row_offsets<256>(a, pass, W, n_rows, m0, s);
     __syncthreads();
-  }
-  for (int t = 0; t < a.tiles; ++t) {
-    const int u0 = static_cast<int>(static_cast<int64_t>(t) * a.units / a.tiles);
-    const int nu = static_cast<int>(static_cast<int64_t>(t + 1) * a.units / a.tiles) - u0;
-    const int v0 = (u0 + static_cast<int>(static_cast<int64_t>(g) * nu / gridDim.x)) * kUnit;
-    const int v1 = min((u0 + static_cast<int>(static_cast<int64_t>(g + 1) * nu / gridDim.x)) * kUnit, a.V);
-    const int col = g * a.tiles + t;
-    for (int m0 = 0; m0 < n_rows; m0 += kMaxTM) {
-      if (v0 >= v1) {  // a share with a tile less: no candidate here
-        for (int r = m0 + threadIdx.x; r < min(n_rows, m0 + kMaxTM); r += kThreads)
-          a.cand[static_cast<int64_t>(r) * a.n_cand + col] = 0;
-        continue;
+    for (int t = 0; t < a.tiles; ++t) {
+      const int u0 = static_cast<int>(static_cast<int64_t>(t) * a.units / a.tiles);
+      const int nu = static_cast<int>(static_cast<int64_t>(t + 1) * a.units / a.tiles) - u0;
+      const int v0 = (u0 + static_cast<int>(static_cast<int64_t>(g) * nu / shares)) * kUnit;
+      const int v1 = min((u0 + static_cast<int>(static_cast<int64_t>(g + 1) * nu / shares)) * kUnit, a.V);
+      const int col = t * shares + g, m = n_rows - m0;
+      if (v0 >= v1) {  // no unit of this tile: no candidate
+        const int r = m0 + static_cast<int>(threadIdx.x);
+        if (threadIdx.x < 256 && r < n_rows) a.cand[static_cast<int64_t>(r) * a.n_cand + col] = 0;
+      } else if (m <= 64) {
+        head_tile<kNoise, Rows64>(a, s, v0, v1, m0, n_rows, col);
+      } else if (m <= 128) {
+        head_tile<kNoise, Rows128>(a, s, v0, v1, m0, n_rows, col);
+      } else {
+        head_tile<kNoise, Rows256>(a, s, v0, v1, m0, n_rows, col);
       }
-      if (n_rows > kMaxTM) {
-        row_offsets(a, pass, W, n_rows, m0, s);
-        __syncthreads();
-      }
-      const int m = n_rows - m0;
-      if (m <= 64) head_tile<kNoise, Rows64>(a, s, v0, v1, m0, n_rows, col);
-      else if (m <= 128) head_tile<kNoise, Rows128>(a, s, v0, v1, m0, n_rows, col);
-      else head_tile<kNoise, Rows256>(a, s, v0, v1, m0, n_rows, col);
     }
   }
+}
+
+// The same over a small head: a workgroup takes 128 head rows and 64 rows of
+// the pass, working ones first in dispatch order; those of one tile are on
+// one XCD, whose L2 serves the head rows they share.
+template <bool kNoise>
+__global__ __launch_bounds__(256, 2) void head_small_kernel(HeadArgs a, int pass) {
+  using Shared = PassShared<128, 64>;
+  __shared__ __attribute__((aligned(16))) Shared s;
+  const int W = a.n_act[pass];
+  if (W <= 0) return;
+  const int n_rows = W <= kLook ? pass_rows(a, pass, W, s) : W;
+  const int n_mb = (n_rows + 63) / 64;
+  const int i = blockIdx.x / kXcds;
+  const int vt = i / n_mb * kXcds + blockIdx.x % kXcds;
+  if (vt >= a.tiles) return;
+  const int m0 = i % n_mb * 64;
+  row_offsets<64>(a, pass, W, n_rows, m0, s);
+  __syncthreads();
+  head_tile<kNoise, Small>(a, s, vt * 128, min(vt * 128 + 128, a.V), m0, min(n_rows, m0 + 64), vt);
 }
 
 // Best candidate of one row over the tiles: every thread of the workgroup
@@ -592,13 +620,14 @@ __device__ inline unsigned long long row_best(const HeadArgs& a, int r, unsigned
   return best;
 }
 
-// Child of u carrying tok (wave-wide search), or -1.
-__device__ inline int find_child(const HeadArgs& a, int64_t tr, int u, int n, int tok) {
+// Child of u carrying tok (wave-wide search), or -1.  par, ptok: the tree's
+// parents and tokens, in LDS where they fit.
+__device__ inline int find_child(const int32_t* par, const int32_t* ptok, int u, int n, int tok) {
   const int lane = threadIdx.x % SRT_WAVE;
   int child = -1;
   for (int c0 = u + 1; c0 < n && child < 0; c0 += SRT_WAVE) {
     const int cc = c0 + lane;
-    const bool hit = cc < n && a.tree_parent[tr + cc] == u && a.tree_tokens[tr + cc] == tok;
+    const bool hit = cc < n && par[cc] == u && ptok[cc] == tok;
     const unsigned long long m = __ballot(hit);
     if (m) child = c0 + __ffsll(static_cast<long long>(m)) - 1;
   }
@@ -611,23 +640,33 @@ __device__ inline int find_child(const HeadArgs& a, int64_t tr, int u, int n, in
 __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int pass) {
   __shared__ unsigned long long s_best[kWalkThreads / SRT_WAVE];
   __shared__ int s_next;
-  __shared__ int32_t s_par[kParents];
+  __shared__ int32_t s_par[kParents], s_tok[kParents];
   const int slot = blockIdx.x;
   const int W = a.n_act[pass];
   if (slot >= W) return;
   const int tid = threadIdx.x, lane = tid % SRT_WAVE, wave = tid / SRT_WAVE;
-  const int b = min(max(a.act[(pass & 1) * a.B + slot], 0), a.B - 1);
+  const int b = min(max(a.act[static_cast<int64_t>(pass & 1) * a.B + slot].x, 0), a.B - 1);
   const int n = min(max(a.n_nodes[b], 1), a.N);
   const int64_t tr = static_cast<int64_t>(b) * a.N;
   const int64_t orow = static_cast<int64_t>(b) * (a.Dmax + 1);
+  const bool staged = n <= kParents;  // beside the first row's candidates
+  if (staged)
+    for (int c = tid; c < n; c += kWalkThreads) {
+      s_par[c] = a.tree_parent[tr + c];
+      s_tok[c] = a.tree_tokens[tr + c];
+    }
   const int2 span = W <= kLook ? a.span[slot] : make_int2(slot, 1);
-  int u = min(max(a.cur[b], 0), a.N - 1);
-  int at = 0;                                          // u's place in the list
-  int k = min(max(a.place[tr + u] >> 16, 0), a.Dmax);  // its depth = the walk's step
+  const int2 first = a.list[static_cast<int64_t>(b) * a.L];
+  int u = min(max(first.x, 0), a.N - 1);
+  int at = 0;                               // u's place in the list
+  int k = min(max(first.y, 0), a.Dmax);     // its depth = the walk's step
   for (;;) {
     const int tok = key_token(row_best(a, span.x + at, s_best));
     if (wave == 0) {
-      const int child = k < a.Dmax ? find_child(a, tr, u, n, tok) : -1;
+      int child = -1;
+      if (k < a.Dmax)
+        child = staged ? find_child(s_par, s_tok, u, n, tok)
+                       : find_child(a.tree_parent + tr, a.tree_tokens + tr, u, n, tok);
       if (lane == 0) {
         a.out_tokens[orow + k] = tok;
         if (child >= 0) {
@@ -643,17 +682,16 @@ __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int
     if (s_next < 0) return;
     u = s_next;
     ++k;
-    at = a.place[tr + u] & 0xFFFF;
+    at = a.place[tr + u];
     if (at >= span.y) break;
   }
   __syncthreads();  // every wave has read the places that are rewritten now
   if (wave > 0) return;
+  const int listed = list_subtree(a, b, u, k, n, staged ? s_par : nullptr);
   if (lane == 0) {
     const int pos = atomicAdd(&a.n_act[pass + 1], 1);
-    a.act[((pass + 1) & 1) * a.B + pos] = b;
+    a.act[static_cast<int64_t>((pass + 1) & 1) * a.B + pos] = make_int2(b, listed);
   }
-  const int32_t* par = stage_parents(a, b, n, s_par);
-  list_subtree(a, b, u, k, n, par);
 }
 
 }  // namespace
@@ -680,7 +718,10 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   if (reinterpret_cast<uintptr_t>(scratch) & 255) return SRT_ERR_INVALID;
   const ScratchLayout L = scratch_layout(B, N, V);
   if (scratch_bytes < L.total) return SRT_ERR_CAPACITY;
-  const Split sp = split_for(V);
+  const Split sp = split_for(V, d_model);
+  const int64_t small_grid = static_cast<int64_t>((sp.tiles + kXcds - 1) / kXcds * kXcds) *
+                             ((std::max<int64_t>(B, kLook) + 63) / 64);
+  if (small_grid > 0x7FFFFFFF) return SRT_ERR_UNSUPPORTED;
 
   char* base = static_cast<char*>(scratch);
   HeadArgs a;
@@ -695,11 +736,9 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.out_nodes = out_nodes;
   a.n_emitted = n_emitted;
   a.n_act = reinterpret_cast<int32_t*>(base);
-  a.act = reinterpret_cast<int32_t*>(base + L.off_act);
-  a.cur = reinterpret_cast<int32_t*>(base + L.off_cur);
-  a.cnt = reinterpret_cast<int32_t*>(base + L.off_cnt);
+  a.act = reinterpret_cast<int2*>(base + L.off_act);
   a.span = reinterpret_cast<int2*>(base + L.off_span);
-  a.list = reinterpret_cast<int32_t*>(base + L.off_list);
+  a.list = reinterpret_cast<int2*>(base + L.off_list);
   a.place = reinterpret_cast<int32_t*>(base + L.off_place);
   a.cand = reinterpret_cast<unsigned long long*>(base + L.off_cand);
   a.B = B;
@@ -708,23 +747,28 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.V = V;
   a.Dmax = Dmax;
   a.L = std::min(N, kLook);
-  a.n_cand = sp.grid * sp.tiles;
+  a.look = look_for(d_model, Dmax);
+  a.n_cand = sp.wide ? sp.grid * sp.tiles : sp.tiles;
   a.units = sp.units;
   a.tiles = sp.tiles;
   a.invT = inv_temperature;
-  a.vec_noise = gumbel && V % 4 == 0 && (reinterpret_cast<uintptr_t>(gumbel) & 15) == 0;
 
   hipStream_t s = as_stream(stream);
   head_init_kernel<<<B, SRT_WAVE, 0, s>>>(a);
   int st = launch_status();
-  // A walker's quota is at least kLook / B (see pass_rows), and a walk that
+  // A walker's quota is at least look / B (see pass_rows), and a walk that
   // leaves a pass has moved that many places on in its tree.
-  const int quota = std::max(1, kLook / B);
+  const int quota = std::max(1, a.look / B);
   const int passes = std::min(Dmax + 1, (N - 1) / quota + 1);
-  const unsigned grid = static_cast<unsigned>(sp.grid);
   for (int pass = 0; pass < passes && st == SRT_OK; ++pass) {
-    if (gumbel) head_pass_kernel<true><<<grid, kThreads, 0, s>>>(a, pass);
-    else head_pass_kernel<false><<<grid, kThreads, 0, s>>>(a, pass);
+    if (sp.wide) {
+      if (gumbel) head_pass_kernel<true><<<sp.grid, 512, 0, s>>>(a, pass);
+      else head_pass_kernel<false><<<sp.grid, 512, 0, s>>>(a, pass);
+    } else {
+      const unsigned grid = static_cast<unsigned>(small_grid);
+      if (gumbel) head_small_kernel<true><<<grid, 256, 0, s>>>(a, pass);
+      else head_small_kernel<false><<<grid, 256, 0, s>>>(a, pass);
+    }
     st = launch_status();
     if (st != SRT_OK) break;
     head_walk_kernel<<<static_cast<unsigned>(B), kWalkThreads, 0, s>>>(a, pass);
