@@ -83,7 +83,6 @@ struct AttnArgs {
   float* part_ml;
   int32_t* plan;  // work lists built by the plan kernel
   int64_t combine_at;  // offset (int32 elements) of the combine list in plan
-  int32_t max_units;   // capacity of the combine list
   int32_t B, N, Hq, Hkv, G, page, page_shift, max_pages;
   int64_t num_pages;
   float scale_log2;
@@ -95,10 +94,11 @@ struct AttnArgs {
 // then item i at plan[kPlanHeader + 2 i] = sequence, [.. + 1] = KV head |
 // split << 8 | row block << 20.  Items are ordered by decreasing cost
 // (tiles, then active waves) so that the longest ones start first.
-// plan[2] = number of combine units; unit u (8 rows of one sequence and KV
-// head whose context spans several splits) at plan[a.combine_at + u] =
-// sequence | KV head << 16 (the host rejects B > 65535) and the 8-row group
-// at plan[a.combine_at + a.max_units + u].
+// plan[2] = number of sequences whose context spans several splits; entry e of
+// them at plan[a.combine_at + 2 e] = sequence | splits << 16 (the host rejects
+// B > 65535 and more than 4095 splits) and [.. + 1] = its query rows per KV
+// head.  (Listing every 8-row group of them here took one thread per sequence
+// 20 to 40 us of stores; the combine kernel works the group out instead.)
 constexpr int kPlanHeader = 64;
 constexpr int kPlanKeys = (kChunk / kTile) * kWaves;  // (tiles, waves) classes
 
@@ -570,28 +570,32 @@ __global__ __launch_bounds__(kThreads, 1) void tree_attn_kernel(AttnArgs a) {
 // the same time and the second stream of the same K/V tiles is served by
 // the caches.  One workgroup; also resets the hand-out counter.
 __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
-  __shared__ int32_t cnt[kPlanKeys], off[kPlanKeys], fill[kPlanKeys];
+  __shared__ int32_t cnt[kPlanKeys], off[kPlanKeys];
   __shared__ int32_t wsum[1024 / SRT_WAVE];
+  __shared__ int32_t s_total[1024], s_rows[1024], s_pos[2][1024];
+  __shared__ int32_t ncomb;
   const int tid = threadIdx.x;
-  for (int k = tid; k < kPlanKeys; k += 1024) {
-    cnt[k] = 0;
-    fill[k] = 0;
-  }
-  __syncthreads();
-  // Visits the item classes of sequence b: f(key, first split, splits,
-  // row blocks).
-  auto classes = [&](int b, auto&& f) {
-    const SeqInfo si = seq_info(a, b);
-    const int rows = si.n * a.G;
-    const int rbs = (rows + kRowsPerBlock - 1) / kRowsPerBlock;
-    const int full = si.total / a.chunk;
-    const int tail = si.total - full * a.chunk;
+  for (int k = tid; k < kPlanKeys; k += 1024) cnt[k] = 0;
+  if (tid == 0) ncomb = 0;
+  const int cshift = 31 - __clz(a.chunk);  // chunk is a power of two
+  // Visits the item classes of a sequence: f(key, splits).
+  auto classes = [&](int total, int rows, auto&& f) {
+    const int full = total >> cshift;
+    const int tail = total - (full << cshift);
     const int waves = min(kWaves, (rows + kRowsPerWave - 1) / kRowsPerWave);
-    if (full > 0) f(plan_key(a.chunk / kTile, waves), 0, full, rbs);
-    if (tail > 0) f(plan_key((tail + kTile - 1) / kTile, waves), full, 1, rbs);
+    if (full > 0) f(0, plan_key(a.chunk / kTile, waves), full);
+    if (tail > 0) f(1, plan_key((tail + kTile - 1) / kTile, waves), 1);
   };
-  for (int b = tid; b < a.B; b += 1024)
-    classes(b, [&](int key, int, int ns, int rbs) { atomicAdd(&cnt[key], ns * a.Hkv * rbs); });
+  auto row_blocks = [&](int rows) { return (rows + kRowsPerBlock - 1) / kRowsPerBlock; };
+  SeqInfo si = {0, 0, 0};  // of this thread's sequence of the current 1024
+  if (tid < a.B) si = seq_info(a, tid);
+  __syncthreads();
+  for (int b0 = 0; b0 < a.B; b0 += 1024) {
+    if (b0 > 0 && b0 + tid < a.B) si = seq_info(a, b0 + tid);
+    if (b0 + tid < a.B)
+      classes(si.total, si.n * a.G,
+              [&](int, int key, int ns) { atomicAdd(&cnt[key], ns * a.Hkv * row_blocks(si.n * a.G)); });
+  }
   __syncthreads();
   // Exclusive prefix sum of the class counts (one class per thread).
   static_assert(kPlanKeys <= 1024, "one class per thread");
@@ -607,86 +611,95 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
   __syncthreads();
   int before = 0;
   for (int j = 0; j < wv; ++j) before += wsum[j];
-  if (tid < kPlanKeys) off[tid] = before + incl - mine;
-  __shared__ int32_t ncomb;
+  if (tid < kPlanKeys) off[tid] = before + incl - mine;  // next free place of the class
   if (tid == 1023) {
     a.plan[0] = before + incl;  // all classes
     a.plan[1] = 0;
-    ncomb = 0;
   }
   __syncthreads();
-  // combine units: 8-row groups of every (sequence, KV head) with several splits
-  for (int b = tid; b < a.B; b += 1024) {
-    const SeqInfo si = seq_info(a, b);
-    if (si.total <= a.chunk) continue;
-    const int groups = (si.n * a.G + 7) / 8;
-    int u = atomicAdd(&ncomb, groups * a.Hkv);
-    for (int g = 0; g < a.Hkv; ++g)
-      for (int r8 = 0; r8 < groups; ++r8, ++u) {
-        a.plan[a.combine_at + u] = b | (g << 16);
-        a.plan[a.combine_at + a.max_units + u] = r8;
+  // 1024 sequences at a time: a thread per sequence takes its places in the
+  // class lists (and in the list of split sequences), then all threads, the
+  // same number for each sequence, write the items.  (One thread per sequence
+  // wrote them in up to 280 stores one after the other: 20 us for 256
+  // sequences of up to 32k, 46 for 8 with 256-node trees; now 6 and 5.)
+  const int group = min(a.B, 1024);
+  const int per_seq_log2 = group > 1 ? __clz(group - 1) - 22 : 10;  // 1024 / (group rounded up to a power of two)
+  for (int b0 = 0; b0 < a.B; b0 += 1024) {
+    if (a.B > 1024 && b0 + tid < a.B) si = seq_info(a, b0 + tid);
+    if (b0 + tid < a.B) {
+      const int rows = si.n * a.G;
+      s_total[tid] = si.total;
+      s_rows[tid] = rows;
+      classes(si.total, rows, [&](int c, int key, int ns) {
+        s_pos[c][tid] = atomicAdd(&off[key], ns * a.Hkv * row_blocks(rows));
+      });
+      if (si.total > a.chunk)
+        *reinterpret_cast<int2*>(a.plan + a.combine_at + 2 * atomicAdd(&ncomb, 1)) =
+            make_int2((b0 + tid) | ((si.total + a.chunk - 1) >> cshift) << 16, rows);
+    }
+    __syncthreads();
+    const int i = tid >> per_seq_log2;
+    if (b0 + i < a.B && i < group) {
+      const int total = s_total[i], rbs = row_blocks(s_rows[i]), per = a.Hkv * rbs;
+      const int full = total >> cshift, splits = (total + a.chunk - 1) >> cshift;
+      for (int x = tid & ((1 << per_seq_log2) - 1); x < splits * per; x += 1 << per_seq_log2) {
+        const int s = x / per, r = x - s * per, g = r / rbs;
+        const int at = s < full ? s_pos[0][i] + x : s_pos[1][i] + x - full * per;
+        *reinterpret_cast<int2*>(a.plan + kPlanHeader + 2 * at) = make_int2(b0 + i, g | (s << 8) | ((r - g * rbs) << 20));
       }
+    }
+    if (b0 + 1024 < a.B) __syncthreads();
   }
-  __syncthreads();
   if (tid == 0) a.plan[2] = ncomb;
-  for (int b = tid; b < a.B; b += 1024)
-    classes(b, [&](int key, int s0, int ns, int rbs) {
-      int pos = off[key] + atomicAdd(&fill[key], ns * a.Hkv * rbs);
-      for (int s = s0; s < s0 + ns; ++s)
-        for (int g = 0; g < a.Hkv; ++g)
-          for (int rb = 0; rb < rbs; ++rb, ++pos) {
-            a.plan[kPlanHeader + 2 * pos] = b;
-            a.plan[kPlanHeader + 2 * pos + 1] = g | (s << 8) | (rb << 20);
-          }
-    });
 }
 
 // Merges the split partials of sequences that needed more than one split:
 // out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s with M = max_s m_s (m
-// in log2 units).  Persistent workgroups stride over the combine units of
-// the plan; a unit is 8 rows, one thread per row and four head dims, so
-// partial reads are 16-byte coalesced.  The splits are folded with a
-// running maximum, so the loads of different splits are independent.
+// in log2 units).  Persistent workgroups stride over the 8-row groups of the
+// plan's split sequences, one thread per row and four head dims, so partial
+// reads are 16-byte coalesced.  The splits are folded with a running maximum,
+// so the loads of different splits are independent.  A group is a chain of
+// two round trips (entry, partials), so 16 workgroups per CU keep enough of
+// them in flight: 26 -> 20 us for 256 sequences of up to 32k with trees of 1
+// to 64 nodes, 44 -> 27 with full ones, 26 -> 20 for 8 of 16k-32k with
+// 64-256 nodes (four workgroups per CU, and a list entry for every group).
+constexpr int kCombineRows = 8;
 template <int D>
-__global__ __launch_bounds__(256) void tree_attn_combine_kernel(AttnArgs a) {
+__global__ __launch_bounds__(kCombineRows * D / 4) void tree_attn_combine_kernel(AttnArgs a) {
   constexpr int Q = D / 4;
-  constexpr int kRowsPerUnit = 256 / Q;
-  static_assert(kRowsPerUnit * Q == 256 && kRowsPerUnit >= 8, "unit shape");
-  const int n_units = a.plan[2];
+  const int per_head = (a.N * a.G + kCombineRows - 1) / kCombineRows;  // groups of the widest tree
+  const int n_units = a.plan[2] * a.Hkv * per_head;
   const int RBR = a.RB * kRowsPerBlock;
+  const int q = threadIdx.x % Q;
   for (int u = blockIdx.x; u < n_units; u += gridDim.x) {
-    const int bg = a.plan[a.combine_at + u];
-    const int b = bg & 0xffff, g = bg >> 16;
-    const SeqInfo si = seq_info(a, b);
-    const int nsplit = (si.total + a.chunk - 1) / a.chunk;
-    const int rows = si.n * a.G;
-    for (int sub = threadIdx.x; sub < 8 * Q; sub += 256) {
-      const int r = a.plan[a.combine_at + a.max_units + u] * 8 + sub / Q, q = sub % Q;
-      if (r >= rows) continue;
-      const int64_t base = (static_cast<int64_t>(b) * a.Hkv + g) * a.S * RBR + r;
-      float M = -INFINITY, den = 0.f;
-      f32x4 num = {0.f, 0.f, 0.f, 0.f};
+    const int e = u / (a.Hkv * per_head), rest = u - e * a.Hkv * per_head;
+    const int g = rest / per_head;
+    const int r = (rest - g * per_head) * kCombineRows + threadIdx.x / Q;
+    const int2 entry = *reinterpret_cast<const int2*>(a.plan + a.combine_at + 2 * e);
+    const int b = entry.x & 0xffff, nsplit = static_cast<int>(static_cast<uint32_t>(entry.x) >> 16);
+    if (r >= entry.y) continue;
+    const int64_t base = (static_cast<int64_t>(b) * a.Hkv + g) * a.S * RBR + r;
+    float M = -INFINITY, den = 0.f;
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-      for (int s = 0; s < nsplit; ++s) {
-        const int64_t prow = base + static_cast<int64_t>(s) * RBR;
-        const float ms = a.part_ml[2 * prow];
-        const float ls = a.part_ml[2 * prow + 1];
-        const f32x4 os = *reinterpret_cast<const f32x4*>(a.part_o + prow * D + 4 * q);
-        if (ms == -INFINITY) continue;
-        const float mn = fmaxf(M, ms);
-        const float c_old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
-        const float c_new = __builtin_amdgcn_exp2f(ms - mn);
-        den = den * c_old + ls * c_new;
-        num = num * c_old + os * c_new;
-        M = mn;
-      }
-      const float inv = den > 0.f ? 1.f / den : 0.f;
-      const int node = r / a.G, h = g * a.G + r % a.G;
-      uint16_t* op = a.out + ((static_cast<int64_t>(b) * a.N + node) * a.Hq + h) * D + 4 * q;
-      const uint32_t x0 = to_bf16_bits(num[0] * inv) | (uint32_t(to_bf16_bits(num[1] * inv)) << 16);
-      const uint32_t x1 = to_bf16_bits(num[2] * inv) | (uint32_t(to_bf16_bits(num[3] * inv)) << 16);
-      *reinterpret_cast<uint2*>(op) = make_uint2(x0, x1);
+    for (int s = 0; s < nsplit; ++s) {
+      const int64_t prow = base + static_cast<int64_t>(s) * RBR;
+      const float2 ml = *reinterpret_cast<const float2*>(a.part_ml + 2 * prow);
+      const f32x4 os = *reinterpret_cast<const f32x4*>(a.part_o + prow * D + 4 * q);
+      if (ml.x == -INFINITY) continue;
+      const float mn = fmaxf(M, ml.x);
+      const float c_old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
+      const float c_new = __builtin_amdgcn_exp2f(ml.x - mn);
+      den = den * c_old + ml.y * c_new;
+      num = num * c_old + os * c_new;
+      M = mn;
     }
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    const int node = r / a.G, h = g * a.G + r % a.G;
+    uint16_t* op = a.out + ((static_cast<int64_t>(b) * a.N + node) * a.Hq + h) * D + 4 * q;
+    const uint32_t x0 = to_bf16_bits(num[0] * inv) | (uint32_t(to_bf16_bits(num[1] * inv)) << 16);
+    const uint32_t x1 = to_bf16_bits(num[2] * inv) | (uint32_t(to_bf16_bits(num[3] * inv)) << 16);
+    *reinterpret_cast<uint2*>(op) = make_uint2(x0, x1);
   }
 }
 
@@ -707,7 +720,8 @@ int splits_for(int32_t page, int32_t max_pages, int chunk) {
   return static_cast<int>((cap + chunk - 1) / chunk);
 }
 
-// Combine units (8-row groups) needed at most.
+// 8-row groups of all sequences and KV heads, each word pair of which the
+// scratch holds room for (the list of split sequences needs less).
 int64_t max_combine_units(int32_t B, int32_t N, int32_t G, int32_t Hkv) {
   return static_cast<int64_t>(B) * Hkv * ((static_cast<int64_t>(N) * G + 7) / 8);
 }
@@ -795,7 +809,6 @@ extern "C" int srt_tree_attn(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int3
   const size_t pbytes = plan_bytes(total, units);
   a.plan = static_cast<int32_t*>(scratch);
   a.combine_at = kPlanHeader + 2 * total;
-  a.max_units = static_cast<int32_t>(units);
   a.part_o = a.S > 1 ? reinterpret_cast<float*>(static_cast<uint8_t*>(scratch) + pbytes) : nullptr;
   a.part_ml = a.S > 1 ? a.part_o + static_cast<int64_t>(B) * Hkv * a.S * RBR * d : nullptr;
 
@@ -810,11 +823,11 @@ extern "C" int srt_tree_attn(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int3
     tree_attn_kernel<64><<<grid, kThreads, 0, s>>>(a);
   }
   if (a.S > 1) {
-    const unsigned cgrid = static_cast<unsigned>(std::min<int64_t>(units, 4 * cus));
+    const unsigned cgrid = static_cast<unsigned>(std::min<int64_t>(units, 16 * cus));
     if (d == 128) {
-      tree_attn_combine_kernel<128><<<cgrid, 256, 0, s>>>(a);
+      tree_attn_combine_kernel<128><<<cgrid, kCombineRows * 32, 0, s>>>(a);
     } else {
-      tree_attn_combine_kernel<64><<<cgrid, 256, 0, s>>>(a);
+      tree_attn_combine_kernel<64><<<cgrid, kCombineRows * 16, 0, s>>>(a);
     }
   }
   return launch_status();

@@ -209,3 +209,44 @@ def test_dominant_keys_late_in_a_split(factor):
         if L > 9000:
             c.plant(b, 8192 + 700, 0, factor * 1.5)
     c.check(c.run(), f"dominant keys x{factor}")
+
+
+@pytest.mark.parametrize("B,N,hkv,G,lo,hi", [
+    (1, 5, 1, 3, 900, 1100),      # one sequence, at the edge of one split
+    (3, 256, 2, 5, 1000, 3000),   # 1024 threads shared by 3 sequences; 5 row blocks each
+    (65, 3, 2, 1, 1, 2300),       # 128 places for 65 sequences, one to three splits
+    (1030, 2, 1, 2, 1, 200),      # more sequences than the plan takes at a time
+])
+def test_work_list_covers_every_sequence(B, N, hkv, G, lo, hi):
+    """Every (sequence, KV head, split, row block) is worked on exactly once:
+    ragged contexts around the split size, batches around the plan's group
+    sizes; fp64 reference of every row, bf16 tolerance."""
+    d, page = 64, 16
+    g = torch.Generator(device="cuda").manual_seed(B * 100 + N)
+    rng = np.random.default_rng(B * 100 + N)
+    L = rng.integers(lo, hi, size=B)
+    n = rng.integers(1, N + 1, size=B)
+    n[0] = N
+    per = (L + N + page - 1) // page
+    bt = np.full((B, per.max()), -1, np.int32)
+    order, at = rng.permutation(int(per.sum())).astype(np.int32), 0
+    for b in range(B):
+        bt[b, :per[b]] = order[at:at + per[b]]
+        at += per[b]
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+    q, k, v = rnd(B, N, hkv * G, d), rnd(at, hkv, page, d), rnd(at, hkv, page, d)
+    par = np.tile(np.arange(-1, N - 1, dtype=np.int32), (B, 1))  # chains
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.int32, device="cuda")
+    out = srt.srt_tree_attn(q, k, v, dev(bt), dev(L), dev(par), dev(n), d ** -0.5, out=torch.full_like(q, 7.0))
+    for b in (range(B) if B <= 65 else rng.choice(B, 60, replace=False)):
+        T, m = int(L[b] + n[b]), int(n[b])
+        pages = torch.as_tensor(bt[b, :per[b]], device="cuda").long()
+        kk, vv = (x[pages].transpose(0, 1).reshape(hkv, -1, d)[:, :T].double() for x in (k, v))
+        qq = q[b, :m].double().reshape(m, hkv, G, d).permute(1, 2, 0, 3)  # [hkv, G, m, d]
+        x = torch.matmul(qq, kk[:, None].transpose(2, 3).contiguous()) * d ** -0.5
+        late = torch.arange(T, device="cuda")[None, :] > int(L[b]) + torch.arange(m, device="cuda")[:, None]
+        ref = torch.matmul(torch.softmax(x.masked_fill(late, -float("inf")), -1), vv[:, None])
+        ref = ref.permute(2, 0, 1, 3).reshape(m, hkv * G, d)
+        err = (out[b, :m].double() - ref).abs()
+        assert bool((err <= 1e-2 + 2e-2 * ref.abs()).all()), (b, float(err.max()))
+        assert bool((out[b, m:] == 7.0).all()), b  # rows past the tree are not written
