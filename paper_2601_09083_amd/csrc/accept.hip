@@ -32,6 +32,7 @@
 //     resets the walk's state (no separate launch).  Candidates and current
 //     nodes alternate between two buffers by level parity, so no launch
 //     reads a buffer it writes.
+//   * Short rows are walked by one workgroup per sequence in one launch.
 // x = fl(fl(l * inv_T) + g) is evaluated with explicitly rounded multiply
 // and add (no FMA), matching the fp32 reference bit for bit.
 #include <algorithm>
@@ -46,6 +47,9 @@ using namespace srt;
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Rows start at any multiple of 4 bytes (the hardware's requirement for its
+// 16-byte loads too) when V is not a multiple of 4.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kThreads = 256;
 constexpr int kMaxN = 256;
@@ -53,6 +57,13 @@ constexpr int kMaxLevels = 64;   // Dmax + 1 <= 64
 constexpr int kMaxChunks = 32;   // chunks per visited row, at most
 constexpr int kMinChunk = 4096;  // vocabulary entries per chunk, at least
 constexpr int kWalkWaves = 4;
+// Entries (logits and noise) of a row that one workgroup walks faster than a
+// launch per step: 64 sequences, 8-deep walks, sampled, V 1024 / 4096 / 16384 /
+// 32768: 13 / 19 / 40 / 66 us against 47 / 58 / 59 / 59 with the level kernels
+// (greedy 16384 / 32768 / 65536: 30 / 43 / 71 against 57 / 56 / 59; 512
+// sequences alike).
+constexpr int64_t kShortRow = 40960;
+constexpr int kNarrowRow = 2048;  // rows up to this take 256 threads, longer ones 1024 (V 1024: 13 us against 15)
 
 struct AcceptArgs {
   const float* logits;
@@ -69,7 +80,6 @@ struct AcceptArgs {
   int32_t* cur;              // [2, B] node each sequence stands on, by level parity
   unsigned long long* cand;  // [2, B, kMaxChunks] packed candidates of a level, by parity
   int B, N, V, Dmax, chunk, n_chunks;
-  int vec;                   // rows can be read as float4
   float invT;
 };
 
@@ -115,58 +125,55 @@ __device__ inline float score(float l, float g, float invT, bool noisy) {
   return noisy ? __fadd_rn(__fmul_rn(l, invT), g) : l;
 }
 
+// This thread's share of the arg-max of x_j over j in [lo, hi) of one row (lo a
+// multiple of 4), `threads` of them together.  16-byte loads, eight in flight;
+// the row's last one to three entries go to the first threads.
+template <bool kNoise>
+__device__ inline Best part_argmax(const float* __restrict__ row, const float* __restrict__ noise, float invT, int lo,
+                                   int hi, int threads) {
+  Best b{-INFINITY, 0x7FFFFFFF};
+  const int tid = threadIdx.x;
+  const f32x4u* r4 = reinterpret_cast<const f32x4u*>(row);
+  const f32x4u* g4 = reinterpret_cast<const f32x4u*>(noise);
+  const int e4 = hi / 4;
+  int i = lo / 4 + tid;
+  for (; i + 3 * threads < e4; i += 4 * threads) {
+    f32x4 x[4], g[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = __builtin_nontemporal_load(&r4[i + u * threads]);
+    if (kNoise) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) g[u] = __builtin_nontemporal_load(&g4[i + u * threads]);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = 4 * (i + u * threads);
+      take(b, score(x[u].x, kNoise ? g[u].x : 0.f, invT, kNoise), j);
+      take(b, score(x[u].y, kNoise ? g[u].y : 0.f, invT, kNoise), j + 1);
+      take(b, score(x[u].z, kNoise ? g[u].z : 0.f, invT, kNoise), j + 2);
+      take(b, score(x[u].w, kNoise ? g[u].w : 0.f, invT, kNoise), j + 3);
+    }
+  }
+  for (; i < e4; i += threads) {
+    const f32x4 x = r4[i];
+    f32x4 g = {0.f, 0.f, 0.f, 0.f};
+    if (kNoise) g = g4[i];
+    take(b, score(x.x, g.x, invT, kNoise), 4 * i);
+    take(b, score(x.y, g.y, invT, kNoise), 4 * i + 1);
+    take(b, score(x.z, g.z, invT, kNoise), 4 * i + 2);
+    take(b, score(x.w, g.w, invT, kNoise), 4 * i + 3);
+  }
+  const int j = 4 * e4 + tid;
+  if (j < hi) take(b, score(row[j], kNoise ? noise[j] : 0.f, invT, kNoise), j);
+  return b;
+}
+
 // Arg-max of x_j over j in [lo, hi) of one row, in every thread.
 template <bool kNoise>
 __device__ inline Best chunk_argmax(const AcceptArgs& a, const float* __restrict__ row,
                                     const float* __restrict__ noise, int lo, int hi) {
-  Best b{-INFINITY, 0x7FFFFFFF};
+  Best b = part_argmax<kNoise>(row, noise, a.invT, lo, hi, kThreads);
   const int tid = threadIdx.x;
-  if (a.vec) {  // lo, hi multiples of 4 and rows 16-byte aligned
-    const f32x4* r4 = reinterpret_cast<const f32x4*>(row);
-    const f32x4* g4 = reinterpret_cast<const f32x4*>(noise);
-    const int e4 = hi / 4;
-    int i = lo / 4 + tid;
-    for (; i + 3 * kThreads < e4; i += 4 * kThreads) {
-      f32x4 x[4], g[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = __builtin_nontemporal_load(&r4[i + u * kThreads]);
-      if (kNoise) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) g[u] = __builtin_nontemporal_load(&g4[i + u * kThreads]);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = 4 * (i + u * kThreads);
-        take(b, score(x[u].x, kNoise ? g[u].x : 0.f, a.invT, kNoise), j);
-        take(b, score(x[u].y, kNoise ? g[u].y : 0.f, a.invT, kNoise), j + 1);
-        take(b, score(x[u].z, kNoise ? g[u].z : 0.f, a.invT, kNoise), j + 2);
-        take(b, score(x[u].w, kNoise ? g[u].w : 0.f, a.invT, kNoise), j + 3);
-      }
-    }
-    for (; i < e4; i += kThreads) {
-      const f32x4 x = r4[i];
-      f32x4 g = {0.f, 0.f, 0.f, 0.f};
-      if (kNoise) g = g4[i];
-      take(b, score(x.x, g.x, a.invT, kNoise), 4 * i);
-      take(b, score(x.y, g.y, a.invT, kNoise), 4 * i + 1);
-      take(b, score(x.z, g.z, a.invT, kNoise), 4 * i + 2);
-      take(b, score(x.w, g.w, a.invT, kNoise), 4 * i + 3);
-    }
-  } else {
-    int j = lo + tid;
-    for (; j + 7 * kThreads < hi; j += 8 * kThreads) {
-      float x[8], g[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = __builtin_nontemporal_load(&row[j + u * kThreads]);
-      if (kNoise) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) g[u] = __builtin_nontemporal_load(&noise[j + u * kThreads]);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) take(b, score(x[u], kNoise ? g[u] : 0.f, a.invT, kNoise), j + u * kThreads);
-    }
-    for (; j < hi; j += kThreads) take(b, score(row[j], kNoise ? noise[j] : 0.f, a.invT, kNoise), j);
-  }
   // lanes, then waves through LDS
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
@@ -297,6 +304,70 @@ __global__ __launch_bounds__(kWalkWaves * SRT_WAVE) void accept_walk_kernel(Acce
   if (lane == 0) record(a, b, level, st);
 }
 
+// Short rows: one workgroup walks one sequence from the root to its end, no
+// launches between the steps and nothing exchanged between workgroups.  A step
+// is bound by its own chain (row loads, the reduction, one barrier, the child
+// search in LDS), about 2 us, where a step of the level kernels is a launch
+// and their longer chain, 4 to 7 us; what a single CU streams (about 100 GB/s)
+// sets the rule below.  Every wave merges the waves' candidates and looks for
+// the child by itself, so a step needs one barrier.
+template <bool kNoise>
+__global__ __launch_bounds__(1024) void accept_short_kernel(AcceptArgs a) {
+  __shared__ int32_t s_par[kMaxN], s_tok[kMaxN];
+  __shared__ unsigned long long s_key[2][1024 / SRT_WAVE];
+  const int b = blockIdx.x, tid = threadIdx.x, threads = blockDim.x;
+  const int lane = tid % SRT_WAVE, wave = tid / SRT_WAVE;
+  const int64_t tr = static_cast<int64_t>(b) * a.N, orow = static_cast<int64_t>(b) * (a.Dmax + 1);
+  const int n = min(max(a.n_nodes[b], 1), a.N);
+  for (int c = tid; c < n; c += threads) {
+    s_par[c] = a.tree_parent[tr + c];
+    s_tok[c] = a.tree_tokens[tr + c];
+  }
+  int u = 0, k = 0;
+  for (;; ++k) {
+    const float* row = a.logits + (tr + u) * a.V;
+    const float* noise = kNoise ? a.gumbel + (orow + k) * a.V : nullptr;
+    const Best m = part_argmax<kNoise>(row, noise, a.invT, 0, a.V, threads);
+    unsigned long long key = pack_key(m.v, m.i);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const unsigned long long o = shfl_xor_u64(key, off);
+      key = o > key ? o : key;
+    }
+    if (lane == 0) s_key[k & 1][wave] = key;
+    __syncthreads();  // (also the staged tree, before its first use)
+    key = lane < threads / SRT_WAVE ? s_key[k & 1][lane] : 0ull;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+      const unsigned long long o = shfl_xor_u64(key, off);
+      key = o > key ? o : key;
+    }
+    const int tok = key_token(shfl_u64(key, 0));
+    int child = -1;
+    if (k < a.Dmax) {  // children of u have larger indices
+      for (int c0 = u + 1; c0 < n && child < 0; c0 += SRT_WAVE) {
+        const int c = c0 + lane;
+        const unsigned long long hit = __ballot(c < n && s_par[c] == u && s_tok[c] == tok);
+        if (hit) child = c0 + __ffsll(static_cast<long long>(hit)) - 1;
+      }
+    }
+    if (tid == 0) {
+      a.out_tokens[orow + k] = tok;
+      a.out_nodes[orow + k] = child;  // -1 at the last step
+    }
+    if (child < 0) break;
+    u = child;
+  }
+  if (tid == 0) {
+    a.n_accepted[b] = k;
+    if (a.n_emitted) a.n_emitted[b] = k + 1;
+  }
+  for (int j = k + 1 + tid; j <= a.Dmax; j += threads) {
+    a.out_tokens[orow + j] = -1;
+    a.out_nodes[orow + j] = -1;
+  }
+}
+
 // Host checks shared by both entry points (before any scratch is touched).
 int check_args(int32_t B, int32_t N, int32_t V, int32_t Dmax, const float* logits, float inv_temperature,
                const int32_t* tree_tokens, const int32_t* tree_parent, const int32_t* n_nodes,
@@ -339,13 +410,19 @@ int launch_accept(int32_t B, int32_t N, int32_t V, int32_t Dmax, const float* lo
   const int64_t per = (static_cast<int64_t>(V) + kMaxChunks - 1) / kMaxChunks;
   a.chunk = static_cast<int>(std::max<int64_t>(kMinChunk, (per + 3) / 4 * 4));
   a.n_chunks = static_cast<int>((static_cast<int64_t>(V) + a.chunk - 1) / a.chunk);
-  a.vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0 &&
-          (!gumbel || (reinterpret_cast<uintptr_t>(gumbel) & 15) == 0);
   a.invT = inv_temperature;
   const int64_t grid = static_cast<int64_t>(B) * a.n_chunks;
   if (grid > 0x7FFFFFFF) return SRT_ERR_UNSUPPORTED;
 
   hipStream_t s = as_stream(stream);
+  if (static_cast<int64_t>(V) * (gumbel ? 2 : 1) <= kShortRow) {
+    const unsigned threads = V <= kNarrowRow ? 256 : 1024;
+    if (gumbel)
+      accept_short_kernel<true><<<static_cast<unsigned>(B), threads, 0, s>>>(a);
+    else
+      accept_short_kernel<false><<<static_cast<unsigned>(B), threads, 0, s>>>(a);
+    return launch_status();
+  }
   int st = SRT_OK;
   const unsigned walk_grid = static_cast<unsigned>((B + kWalkWaves - 1) / kWalkWaves);
   for (int level = 0; level <= Dmax && st == SRT_OK; ++level) {

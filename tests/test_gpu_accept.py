@@ -227,3 +227,32 @@ def test_deepest_walk(Dmax, sampled):
     for b in range(B):
         assert_accept_equal(got, b, want[b], Dmax)
     assert (got["n_accepted"] == min(Dmax, N - 1)).all()
+
+
+@pytest.mark.parametrize("V,sampled,N,Dmax", [
+    (1, False, 3, 2), (3, True, 40, 6), (2048, True, 33, 8), (2049, False, 65, 8), (4099, True, 256, 20),
+    (20480, True, 32, 8), (20481, True, 32, 8), (40960, False, 32, 8), (40963, False, 32, 8)])
+def test_walk_exact_at_the_edges_of_short_rows(V, sampled, N, Dmax):
+    """Rows that one workgroup walks (256 threads up to 2048 entries, 1024
+    above) and the first that the level kernels take, with V mod 4 of every
+    kind; integer logits (ties), most of some rows at the lowest finite value."""
+    rng = random.Random(V + N)
+    B = 20
+    say(f"accept short rows: V={V} sampled={sampled} N={N}")
+    tree = random_trees(rng, B, N, Dmax, V) if V > 3 else {
+        "tree_tokens": np.zeros((B, N), np.int32), "n_nodes": np.full(B, min(N, Dmax + 3), np.int32),
+        "tree_parent": np.tile(np.arange(-1, N - 1, dtype=np.int32), (B, 1))}
+    g = torch.Generator(device="cuda").manual_seed(V)
+    logits = torch.round(torch.randn((B, N, V), generator=g, device="cuda") * 2)
+    tt = torch.as_tensor(tree["tree_tokens"], device="cuda").long()
+    for b in range(B):  # most nodes' first child carries the arg-max
+        for c in range(int(tree["n_nodes"][b]) - 1, 0, -1):
+            if rng.random() < 0.8:
+                logits[b, int(tree["tree_parent"][b, c]), tt[b, c]] = 12.0 + rng.randrange(2)
+    logits[3:9, ::2, V // 3:] = torch.finfo(torch.float32).min
+    gumbel = torch.round(torch.randn((B, Dmax + 1, V), generator=g, device="cuda")) if sampled else None
+    got = run(tree, logits, gumbel, 1.0, Dmax)
+    want = oracle_accept_rows(logits, gumbel, 1.0, tree, range(B), Dmax)
+    for b in range(B):
+        assert_accept_equal(got, b, want[b], Dmax)
+    assert got["n_accepted"].max() >= 2
