@@ -74,7 +74,7 @@ def counter_traffic(config_name):
         return None
 
 
-ATTN_KERNELS = ("tree_attn_plan_kernel", "tree_attn_kernel<128>", "tree_attn_combine_kernel<128>")
+ATTN_KERNELS = ("tree_attn_plan_kernel", "tree_attn_kernel<128, false>", "tree_attn_combine_kernel<128, false>")
 
 
 def _short_name(name):

@@ -182,8 +182,10 @@ int srt_draft(const void* ws, int32_t B, const int32_t* prompt_ids, const int32_
  * srt_tree_attn_scratch_bytes(...) bytes (always > 0): the work list the
  * call builds for its own kernels, plus split-context partial results when
  * a context can exceed one split.  A split is 8192 keys, or a smaller power
- * of two (down to 1024) when B * Hkv is small, chosen from B, Hkv, page and
- * max_pages alone (the results do not depend on it beyond fp32 rounding).
+ * of two (down to 1024) when B * Hkv is small and down to 256 when the whole
+ * call leaves CUs idle otherwise, chosen from B, N, Hq / Hkv, Hkv, page and
+ * max_pages alone (the results do not depend on it beyond fp32 rounding).  A
+ * scratch with room for the 1024-key splits only is taken too and makes them.
  * Owned by the caller; contents are overwritten; calls that share a
  * scratch buffer must not overlap.
  * Unsupported (SRT_ERR_UNSUPPORTED): B > 65535, Hkv > 255, max_pages *

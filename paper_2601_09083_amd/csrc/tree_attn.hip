@@ -69,6 +69,9 @@ constexpr int kSubRows = kTile / kWaves;   // keys of each tile one wave stages
 constexpr int kMaxN = 256;                 // tree rows
 constexpr int kChunk = 8192;               // keys per split, at most (the split size is chosen per call)
 constexpr int kMinChunk = 1024;            // keys per split, at least
+constexpr int kSmallChunk = 256;           // the same where every split has a CU of its own
+constexpr int kSmallItems = 256;           // work items up to which that is so (one per CU)
+constexpr int kSmallSplits = 32;           // splits of a context then, at most
 
 struct AttnArgs {
   const uint16_t* q;
@@ -87,7 +90,7 @@ struct AttnArgs {
   int64_t num_pages;
   float scale_log2;
   int32_t S, RB, total;
-  int32_t chunk;  // keys per split: a power of two in [kMinChunk, kChunk]
+  int32_t chunk;  // keys per split: a power of two in [kSmallChunk, kChunk]
 };
 
 // Work list: plan[0] = number of items, plan[1] = next item to hand out,
@@ -175,7 +178,7 @@ __device__ inline float sum_halves(float x) {
   return u + v;
 }
 
-template <int D>
+template <int D, bool kDirect>
 __global__ __launch_bounds__(kThreads, 1) void tree_attn_kernel(AttnArgs a) {
   using Sh = Shape<D>;
   constexpr int CPR = Sh::CPR;
@@ -184,16 +187,12 @@ __global__ __launch_bounds__(kThreads, 1) void tree_attn_kernel(AttnArgs a) {
   __shared__ uint64_t anc[kMaxN][4];
   __shared__ int32_t spar[kMaxN];
 
-  __shared__ int32_t s_item;
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid / SRT_WAVE);  // wave-uniform, in an SGPR
   const int lane = tid % SRT_WAVE;
   const int l32 = lane % 32;  // query row of this lane inside the wave's 32
   const int h = lane / 32;    // lane half
-  const int n_items = a.plan[0];
 
-  // Persistent workgroups: each takes the next item of the work list until
-  // the list is exhausted.
   auto run_item = [&](const int b, const int g, const int s, const int rb) {
   const SeqInfo si = seq_info(a, b);
   const int rows = si.n * a.G;
@@ -551,6 +550,15 @@ __global__ __launch_bounds__(kThreads, 1) void tree_attn_kernel(AttnArgs a) {
   }
   };
 
+  if constexpr (kDirect) {  // a workgroup for every item there can be
+    const int x = blockIdx.x / a.RB, y = x / a.S;
+    run_item(y / a.Hkv, y % a.Hkv, x - y * a.S, blockIdx.x - x * a.RB);
+    return;
+  }
+  // Persistent workgroups: each takes the next item of the work list until
+  // the list is exhausted.
+  __shared__ int32_t s_item;
+  const int n_items = a.plan[0];
   for (;;) {
     if (tid == 0) s_item = atomicAdd(a.plan + 1, 1);
     __syncthreads();
@@ -664,20 +672,29 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
 // to 64 nodes, 44 -> 27 with full ones, 26 -> 20 for 8 of 16k-32k with
 // 64-256 nodes (four workgroups per CU, and a list entry for every group).
 constexpr int kCombineRows = 8;
-template <int D>
+template <int D, bool kDirect>
 __global__ __launch_bounds__(kCombineRows * D / 4) void tree_attn_combine_kernel(AttnArgs a) {
   constexpr int Q = D / 4;
   const int per_head = (a.N * a.G + kCombineRows - 1) / kCombineRows;  // groups of the widest tree
-  const int n_units = a.plan[2] * a.Hkv * per_head;
+  const int n_units = (kDirect ? a.B : a.plan[2]) * a.Hkv * per_head;
   const int RBR = a.RB * kRowsPerBlock;
   const int q = threadIdx.x % Q;
   for (int u = blockIdx.x; u < n_units; u += gridDim.x) {
     const int e = u / (a.Hkv * per_head), rest = u - e * a.Hkv * per_head;
     const int g = rest / per_head;
     const int r = (rest - g * per_head) * kCombineRows + threadIdx.x / Q;
-    const int2 entry = *reinterpret_cast<const int2*>(a.plan + a.combine_at + 2 * e);
-    const int b = entry.x & 0xffff, nsplit = static_cast<int>(static_cast<uint32_t>(entry.x) >> 16);
-    if (r >= entry.y) continue;
+    int b = e, nsplit, rows;
+    if constexpr (kDirect) {  // every sequence, whatever its splits
+      const SeqInfo si = seq_info(a, b);
+      nsplit = (si.total + a.chunk - 1) / a.chunk;
+      rows = si.n * a.G;
+    } else {
+      const int2 entry = *reinterpret_cast<const int2*>(a.plan + a.combine_at + 2 * e);
+      b = entry.x & 0xffff;
+      nsplit = static_cast<int>(static_cast<uint32_t>(entry.x) >> 16);
+      rows = entry.y;
+    }
+    if (nsplit < 2 || r >= rows) continue;
     const int64_t base = (static_cast<int64_t>(b) * a.Hkv + g) * a.S * RBR + r;
     float M = -INFINITY, den = 0.f;
     f32x4 num = {0.f, 0.f, 0.f, 0.f};
@@ -707,11 +724,25 @@ __global__ __launch_bounds__(kCombineRows * D / 4) void tree_attn_combine_kernel
 // gives B * Hkv * RB * (capacity / chunk) >= 512 work items (two per CU of
 // the 256; RB row blocks per sequence and KV head), so that small batches
 // of long contexts are split over enough workgroups; large batches and wide
-// trees keep 8192-key splits (fewer partial results).
-int chunk_for(int32_t B, int32_t Hkv, int64_t RB, int32_t page, int32_t max_pages) {
+// trees keep 8192-key splits (fewer partial results).  A batch that leaves CUs
+// idle even so is a serial chain of up to 16 tiles (about 1.3 us each); as
+// long as all of its items run at once it takes 256- or 512-key splits.  28
+// heads, 4 KV heads, d 128, one sequence, 8-node trees, capacity 1024 / 2048 /
+// 4096: 14 / 15 / 18 us against 20 / 25 / 27 with 1024-key splits; 16
+// sequences, 64-node trees, 2048: 45.7 against 45.4 (no CU left).  Contexts of
+// up to 768 keys (1024 with 512-key splits) gain little over the combine's cost
+// (16 sequences of 32 heads, 8 KV heads, 64 nodes, capacity 768: 34 us with
+// 512-key splits, 30 with one; 4 of 4 heads, d 64, 8 nodes: 13.7 and 13.1), and past 32 splits the combine's own chain is the longer one
+// (one sequence, 16k keys: 39 us with 63 splits, 25 with 32 or 16).  small =
+// false: without these, for a scratch that has no room for their partials.
+int chunk_for(int32_t B, int32_t Hkv, int64_t RB, int32_t page, int32_t max_pages, bool small) {
   const int64_t cap = static_cast<int64_t>(page) * max_pages;
   int chunk = kChunk;
-  while (chunk > kMinChunk && static_cast<int64_t>(B) * Hkv * RB * ((cap + chunk - 1) / chunk) < 512) chunk /= 2;
+  auto items = [&](int c) { return static_cast<int64_t>(B) * Hkv * RB * ((cap + c - 1) / c); };
+  while (chunk > kMinChunk && items(chunk) < 512) chunk /= 2;
+  if (small && chunk == kMinChunk)
+    for (int c = kSmallChunk; c < kMinChunk; c *= 2)
+      if (cap > c + 512 && cap <= kSmallSplits * c && items(c) <= kSmallItems) return c;
   return chunk;
 }
 
@@ -732,6 +763,16 @@ size_t plan_bytes(int64_t items, int64_t units) {
   return ((kPlanHeader + 2 * items + 2 * units) * sizeof(int32_t) + 255) / 256 * 256;
 }
 
+size_t scratch_for(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int32_t d, int32_t page, int32_t max_pages,
+                   int chunk) {
+  const int G = Hq / Hkv;
+  const int64_t RB = (N * G + kRowsPerBlock - 1) / kRowsPerBlock;
+  const int S = splits_for(page, max_pages, chunk);
+  const size_t plan = plan_bytes(static_cast<int64_t>(B) * Hkv * S * RB, max_combine_units(B, N, G, Hkv));
+  if (S <= 1) return plan;
+  return plan + static_cast<size_t>(B) * Hkv * S * RB * kRowsPerBlock * (d + 2) * sizeof(float);
+}
+
 int cu_count() {
   static int cached[64] = {0};
   int dev = 0;
@@ -743,17 +784,33 @@ int cu_count() {
   return n;
 }
 
+void launch_main(const AttnArgs& a, int d, bool direct, unsigned grid, hipStream_t s) {
+  if (d == 128) {
+    if (direct) tree_attn_kernel<128, true><<<grid, kThreads, 0, s>>>(a);
+    else tree_attn_kernel<128, false><<<grid, kThreads, 0, s>>>(a);
+  } else {
+    if (direct) tree_attn_kernel<64, true><<<grid, kThreads, 0, s>>>(a);
+    else tree_attn_kernel<64, false><<<grid, kThreads, 0, s>>>(a);
+  }
+}
+
+void launch_combine(const AttnArgs& a, int d, bool direct, unsigned grid, hipStream_t s) {
+  if (d == 128) {
+    if (direct) tree_attn_combine_kernel<128, true><<<grid, kCombineRows * 32, 0, s>>>(a);
+    else tree_attn_combine_kernel<128, false><<<grid, kCombineRows * 32, 0, s>>>(a);
+  } else {
+    if (direct) tree_attn_combine_kernel<64, true><<<grid, kCombineRows * 16, 0, s>>>(a);
+    else tree_attn_combine_kernel<64, false><<<grid, kCombineRows * 16, 0, s>>>(a);
+  }
+}
+
 }  // namespace
 
 extern "C" size_t srt_tree_attn_scratch_bytes(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int32_t d, int32_t page,
                                               int32_t max_pages) {
   if (B < 0 || N < 1 || N > kMaxN || Hq < 1 || Hkv < 1 || Hq % Hkv || page < 1 || max_pages < 1) return 0;
-  const int G = Hq / Hkv;
-  const int64_t RB = (N * G + kRowsPerBlock - 1) / kRowsPerBlock;
-  const int S = splits_for(page, max_pages, chunk_for(B, Hkv, RB, page, max_pages));
-  const size_t plan = plan_bytes(static_cast<int64_t>(B) * Hkv * S * RB, max_combine_units(B, N, G, Hkv));
-  if (S <= 1) return plan;
-  return plan + static_cast<size_t>(B) * Hkv * S * RB * kRowsPerBlock * (d + 2) * sizeof(float);
+  const int64_t RB = (N * (Hq / Hkv) + kRowsPerBlock - 1) / kRowsPerBlock;
+  return scratch_for(B, N, Hq, Hkv, d, page, max_pages, chunk_for(B, Hkv, RB, page, max_pages, true));
 }
 
 extern "C" int srt_tree_attn(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int32_t d, int32_t page,
@@ -768,15 +825,17 @@ extern "C" int srt_tree_attn(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int3
   if (page < 16 || (page & (page - 1))) return SRT_ERR_UNSUPPORTED;
   // work-list packing: sequence < 65536, KV head < 256, split < 4096,
   // row block < 2048, combine units < 2^31
-  const int chunk = chunk_for(B, Hkv, (N * (Hq / Hkv) + kRowsPerBlock - 1) / kRowsPerBlock, page, max_pages);
+  const int64_t RB = (N * (Hq / Hkv) + kRowsPerBlock - 1) / kRowsPerBlock;
+  int chunk = chunk_for(B, Hkv, RB, page, max_pages, true);
   if (B > 65535 || Hkv > 255 || splits_for(page, max_pages, chunk) > 4095 || (N * (Hq / Hkv)) / kRowsPerBlock > 2046 ||
       max_combine_units(B, N, Hq / Hkv, Hkv) > (int64_t(1) << 30))
     return SRT_ERR_UNSUPPORTED;
   if (B == 0) return SRT_OK;
   if (!q || !k_cache || !v_cache || !block_table || !ctx_len || !tree_parent || !n_nodes || !out)
     return SRT_ERR_INVALID;
-  const size_t need = srt_tree_attn_scratch_bytes(B, N, Hq, Hkv, d, page, max_pages);
-  if (!scratch || scratch_bytes < need) return SRT_ERR_CAPACITY;
+  if (scratch_bytes < scratch_for(B, N, Hq, Hkv, d, page, max_pages, chunk))
+    chunk = chunk_for(B, Hkv, RB, page, max_pages, false);
+  if (!scratch || scratch_bytes < scratch_for(B, N, Hq, Hkv, d, page, max_pages, chunk)) return SRT_ERR_CAPACITY;
   if (reinterpret_cast<uintptr_t>(scratch) % 256) return SRT_ERR_INVALID;
 
   AttnArgs a;
@@ -800,7 +859,7 @@ extern "C" int srt_tree_attn(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int3
   a.scale_log2 = static_cast<float>(static_cast<double>(scale) * 1.4426950408889634);
   a.chunk = chunk;
   a.S = splits_for(page, max_pages, chunk);
-  a.RB = (N * a.G + kRowsPerBlock - 1) / kRowsPerBlock;
+  a.RB = static_cast<int32_t>(RB);
   const int64_t total = static_cast<int64_t>(B) * Hkv * a.S * a.RB;
   if (total > (int64_t(1) << 30)) return SRT_ERR_INVALID;
   a.total = static_cast<int32_t>(total);
@@ -816,19 +875,14 @@ extern "C" int srt_tree_attn(int32_t B, int32_t N, int32_t Hq, int32_t Hkv, int3
   if (cus <= 0) return SRT_ERR_HIP;
   const unsigned grid = static_cast<unsigned>(std::min<int64_t>(total, cus));
   hipStream_t s = as_stream(stream);
-  tree_attn_plan_kernel<<<1, 1024, 0, s>>>(a);
-  if (d == 128) {
-    tree_attn_kernel<128><<<grid, kThreads, 0, s>>>(a);
-  } else {
-    tree_attn_kernel<64><<<grid, kThreads, 0, s>>>(a);
-  }
+  // Where every item that the batch can have gets a CU of its own there is
+  // nothing to order or hand out: no plan kernel, one launch less (16
+  // sequences of up to 400 keys, 8-node trees, 28 heads: 17.3 -> 13.2 us).
+  const bool direct = total <= cus;
+  if (!direct) tree_attn_plan_kernel<<<1, 1024, 0, s>>>(a);
+  launch_main(a, d, direct, grid, s);
   if (a.S > 1) {
-    const unsigned cgrid = static_cast<unsigned>(std::min<int64_t>(units, 16 * cus));
-    if (d == 128) {
-      tree_attn_combine_kernel<128><<<cgrid, kCombineRows * 32, 0, s>>>(a);
-    } else {
-      tree_attn_combine_kernel<64><<<cgrid, kCombineRows * 16, 0, s>>>(a);
-    }
+    launch_combine(a, d, direct, static_cast<unsigned>(std::min<int64_t>(units, 16 * cus)), s);
   }
   return launch_status();
 }

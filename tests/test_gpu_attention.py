@@ -216,6 +216,12 @@ def test_dominant_keys_late_in_a_split(factor):
     (3, 256, 2, 5, 1000, 3000),   # 1024 threads shared by 3 sequences; 5 row blocks each
     (65, 3, 2, 1, 1, 2300),       # 128 places for 65 sequences, one to three splits
     (1030, 2, 1, 2, 1, 200),      # more sequences than the plan takes at a time
+    (32, 3, 2, 1, 900, 1000),     # a CU for each of 256 items, 256-key splits
+    (33, 3, 2, 1, 900, 1000),     # one sequence more: one split each
+    (129, 1, 2, 1, 300, 500),     # 258 items: handed out from the list
+    (1, 7, 1, 4, 8100, 8150),     # 32 splits of 256 keys
+    (1, 7, 1, 4, 8200, 8300),     # 17 splits of 512 keys
+    (2, 256, 1, 5, 1, 1100),      # five row blocks, splits without keys
 ])
 def test_work_list_covers_every_sequence(B, N, hkv, G, lo, hi):
     """Every (sequence, KV head, split, row block) is worked on exactly once:
@@ -250,3 +256,26 @@ def test_work_list_covers_every_sequence(B, N, hkv, G, lo, hi):
         err = (out[b, :m].double() - ref).abs()
         assert bool((err <= 1e-2 + 2e-2 * ref.abs()).all()), (b, float(err.max()))
         assert bool((out[b, m:] == 7.0).all()), b  # rows past the tree are not written
+
+
+def test_scratch_for_large_splits_only():
+    """One sequence of 1900 keys is worked on in 256-key splits; a scratch with
+    room for two 1024-key splits' partials is taken as well, less is refused."""
+    c = Case(5, 1, 8, 4, 1, 64, [1900])
+    pages = int(c.block_table.shape[1])
+    plan = -(-((64 + 2 * 2 + 2 * 4) * 4) // 256) * 256
+    small = plan + 2 * 256 * (64 + 2) * 4
+    assert 1024 < pages * 16 <= 2048 and small < srt.srt_tree_attn_scratch_bytes(1, 8, 4, 1, 64, 16, pages)
+    t = lambda a: torch.as_tensor(a, device="cuda")
+    ins = [c.q, c.k_cache, c.v_cache, c.block_table, t(c.ctx), t(c.parent), t(c.n_nodes)]
+    out, scratch = torch.zeros_like(c.q), torch.empty(small, dtype=torch.uint8, device="cuda")
+
+    def call(nbytes):
+        return srt.lib().srt_tree_attn(1, 8, 4, 1, 64, 16, pages, c.k_cache.shape[0], *[x.data_ptr() for x in ins],
+                                       c.scale, out.data_ptr(), scratch.data_ptr(), nbytes,
+                                       torch.cuda.current_stream().cuda_stream)
+
+    assert call(small - 256) == srt.SRT_ERR_CAPACITY
+    assert call(small) == srt.SRT_OK
+    c.check(out, "1024-key splits")
+    c.check(c.run(), "256-key splits")
