@@ -92,7 +92,10 @@ int srt_trie_init(void* ws, size_t ws_bytes, const srt_trie_config* cfg, void* s
  * occurrence.  Arrays: prompt_ids, stream_ids, lengths [n] int32; tokens
  * [n, stride] int32 (tokens >= 0).  Stream ids must be distinct within one
  * call.  n == 0 is a no-op.  Entries with an out-of-range prompt or stream,
- * or a stream bound to another prompt, are skipped and flagged. */
+ * or a stream bound to another prompt, are skipped and flagged.  An entry that
+ * takes the cache past node_capacity sets SRT_FLAG_CAPACITY and is counted
+ * whole as far as the table has free slots (at least a quarter more than
+ * node_capacity); entries that come to a flagged cache are dropped whole. */
 int srt_trie_insert(void* ws, int32_t n, const int32_t* prompt_ids, const int32_t* stream_ids,
                     const int32_t* tokens, const int32_t* lengths, int32_t stride, void* stream);
 

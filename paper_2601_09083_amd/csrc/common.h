@@ -44,6 +44,10 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kRootParent = 0xFFFFFFFFu;
 constexpr uint32_t kCountBias = 2u;  // count = stored count + 2 (mod 2^32)
 constexpr uint32_t kMaxSlotsLog2 = 31;  // node ids stay below kRootParent
+// Slots a key may lie past its first one.  Up to the capacity (a load of at
+// most 0.8) a run of 1000 taken slots is not to be expected in the largest
+// table; the bound ends probes of a table that a call fills past its capacity.
+constexpr uint64_t kMaxProbes = 4096;
 
 struct alignas(256) WsHeader {
   uint32_t magic;
@@ -81,6 +85,7 @@ struct TrieView {
   int32_t* streams;
   char* table;
   uint64_t mask;
+  uint64_t probes;  // slots a key may lie in: min(slots, kMaxProbes)
   int32_t depth;
 
   __device__ Slot* slot(uint64_t id) const {
@@ -100,6 +105,7 @@ __host__ __device__ inline TrieView trie_view(void* ws, const WsHeader& h) {
   v.streams = reinterpret_cast<int32_t*>(base + h.off_streams);
   v.table = base + h.off_table;
   v.mask = h.slots - 1;
+  v.probes = h.slots < kMaxProbes ? h.slots : kMaxProbes;
   v.depth = h.max_depth;
   return v;
 }
@@ -131,7 +137,7 @@ __device__ inline void set_flag(const TrieView& t, uint32_t f) { atomicOr(&t.hdr
 __device__ inline uint32_t trie_lookup(const TrieView& t, uint32_t parent, uint32_t token, uint32_t& first) {
   const uint64_t key = node_key(parent, token);
   uint64_t h = mix64(key) & t.mask;
-  for (uint64_t probe = 0; probe <= t.mask; probe += 2) {
+  for (uint64_t probe = 0; probe < t.probes; probe += 2) {
     const uint64_t h1 = (h + 1) & t.mask;
     const Slot s0 = *t.slot(h), s1 = *t.slot(h1);
     if (s0.key == key) {
@@ -150,7 +156,7 @@ __device__ inline uint32_t trie_lookup(const TrieView& t, uint32_t parent, uint3
 }
 
 // Slot of `key`, created by this thread (created = true) if absent; kNone
-// and the capacity flag if every slot is taken.  The probe is the CAS itself
+// and the capacity flag if every slot it may lie in is taken.  The probe is the CAS itself
 // (a failed one returns the slot's key), one round trip for a new key in a
 // free slot.  `beside()` runs once, before the first probe returns.
 // Reading first costs more than the failed CASes it spares, also in bulk
@@ -163,7 +169,7 @@ __device__ inline uint32_t trie_find_or_create(const TrieView& t, uint64_t key, 
   beside();
   unsigned long long old = atomicCAS(&t.slot(h)->key, kEmptyKey, (unsigned long long)key);
   for (uint64_t probes = 1; old != kEmptyKey && old != key; ++probes) {
-    if (probes > t.mask) {
+    if (probes >= t.probes) {
       created = false;
       set_flag(t, SRT_FLAG_CAPACITY);
       return kNone;

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(kHeadThreads) void insert_head_kernel(void* ws, con
     s_m = m;
     s_rec = rec;
     s_created = 0;
-    // What the second kernel cannot see by itself (a full table) is recorded
+    // What the second kernel does not look at again (a full table) is recorded
     // too; an entry with an id out of range touches no record.
     if (!s_ok && rec_of(t, p, stream_ids[entry], rec)) rec[kStreamHead + t.depth - 1] = 0;
   }
@@ -308,9 +308,8 @@ __global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, con
   const int len = lengths[entry];
   if (part * kBodyThreads >= len) return;
   const TrieView t = trie_view_dev(ws);
-  // A cache that filled up in the meantime takes no more (its streams take no
-  // later insert either, so slices left out here are never built upon).
-  if (t.hdr->flags & SRT_FLAG_CAPACITY) return;
+  // The first kernel's verdict holds for the whole entry: a cache that fills
+  // up in the meantime takes all of it (as far as the table has slots).
   const int p = prompt_ids[entry];
   int32_t* rec = nullptr;
   if (len > stride || !rec_of(t, p, stream_ids[entry], rec) || rec[kStreamHead + t.depth - 1] != 1) return;

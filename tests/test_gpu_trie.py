@@ -185,6 +185,41 @@ def test_long_segments_beside_short_and_rejected_ones(D, width):
             check_prompt(c, p, [np.array(h) for h, q in zip(have, prompts) if q == p], D)
 
 
+@pytest.mark.parametrize("D,lens,capacity", [(8, [3000], 15000), (20, [1500, 2500, 5, 1800], 60000), (64, [1000], 52500)])
+def test_long_segments_that_overflow_the_capacity_are_counted_whole(D, lens, capacity):
+    # the capacity is passed in the middle of the call, the table has slots for
+    # all of it: every string is counted, and every node is charged
+    rng = np.random.default_rng(D)
+    segs = [rng.integers(0, 50000, size=n) for n in lens]
+    c = Caches.create(1, len(lens), D, capacity)
+    say(f"cache: long segments past the capacity, D={D} lens={lens}")
+    c.insert([0] * len(lens), np.arange(len(lens), dtype=np.int32), segs)
+    st = c.status()
+    want = TR.substring_counts(segs, D)
+    assert capacity < len(want) < st["slots"] and st["flags"] == srt.SRT_FLAG_CAPACITY
+    parent, token, count = srt.srt_trie_export(c.ws, 0, len(want) + 10)
+    assert len(count) == len(want) and st["nodes"] == len(want) + 1
+    check_prompt(c, 0, segs, D)
+
+
+@pytest.mark.parametrize("capacity,n,width", [(100, 3, 2000), (8000, 8, 3000)])
+def test_a_table_without_slots_ends_the_call(capacity, n, width):
+    # far more strings than slots: what found a slot is charged and linked
+    D = 8
+    rng = np.random.default_rng(capacity)
+    c = Caches.create(2, n, D, capacity)
+    say(f"cache: table of {c.status()['slots']} slots filled up")
+    c.insert([0] * n, np.arange(n, dtype=np.int32), [rng.integers(0, 50000, size=width) for _ in range(n)])
+    st = c.status()
+    assert st["flags"] == srt.SRT_FLAG_CAPACITY and capacity < st["nodes"] <= st["slots"]
+    parent, token, count = srt.srt_trie_export(c.ws, 0, st["slots"])
+    assert len(count) == st["nodes"] - 2  # the roots are no strings
+    tail = torch.full((1, 8), 3, dtype=torch.int32, device="cuda")
+    one = torch.ones(1, dtype=torch.int32, device="cuda")
+    srt.srt_draft(c.ws, one, tail, 8 * one, 8, 16, 4)  # lookups end too
+    torch.cuda.synchronize()
+
+
 def test_long_segment_after_overflow_is_dropped():
     D = 8
     c = Caches.create(1, 4, D, 200)
