@@ -9,7 +9,8 @@
 //
 // GPU design: threads walk independent chains, one per start position k of a
 // substring that ends in the new segment; a workgroup takes a short segment,
-// or a slice of a long one.  A stream remembers its active nodes -- the nodes of its
+// or a slice of a long one.
+// A stream remembers its active nodes -- the nodes of its
 // suffixes of length 1 .. D-1 -- so a chain that starts j tokens before the
 // segment starts at the active node of length j instead of walking from the
 // root; a chain that starts inside the segment starts at the prompt's root.
@@ -167,7 +168,18 @@ __device__ inline uint32_t walk_chain(const TrieView& t, const int32_t* __restri
   return made;
 }
 
-// Short segments (the step's emitted tokens): one workgroup per entry.
+// One workgroup per entry checks it, binds its stream and walks its chains, a
+// thread each (a segment of up to 960 tokens in one round).
+// kLong: calls whose segments can be longer; an entry of more than kLongChains
+// chains is left to insert_body_kernel, its verdict in the record's spare word.
+// 64 continued segments of 300 tokens take 49 us there and 46 in a workgroup
+// each, 64 of 600 tokens and depth 64 252 and 249, 8 of 1000 tokens 35 and 74;
+// left to it above 512 or 1024 chains, builds from rollouts of 500 to 3000
+// tokens take 1.45 or 1.65 ms (1.36 above 256).
+constexpr int kLongChains = 256;
+constexpr int kLongThreads = 512;
+
+template <bool kLong>
 __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* __restrict__ prompt_ids,
                                                      const int32_t* __restrict__ stream_ids,
                                                      const int32_t* __restrict__ tokens,
@@ -191,22 +203,29 @@ __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* _
     s_m = m;
     s_rec = rec;
     s_created = 0;
+    // (an entry with an id out of range touches no record)
+    if (kLong && rec_of(t, p, sid, rec)) rec[kStreamHead + t.depth - 1] = 0;
   }
   __syncthreads();
   if (!s_ok) return;
 
   // Reject the entry whole if any token is negative.
   int bad = 0;
+#pragma unroll 8
   for (int j = threadIdx.x; j < len; j += blockDim.x) bad |= tok[j] < 0;
   if (__syncthreads_or(bad)) {
     if (threadIdx.x == 0) set_flag(t, SRT_FLAG_STREAM);
     return;
   }
+  const int m = s_m;
+  int32_t* rec = s_rec;
+  if (kLong && len > kLongChains - m) {
+    if (threadIdx.x == 0) rec[kStreamHead + t.depth - 1] = 1;
+    return;
+  }
 
   // Active nodes before the segment: s_act[j-1] = node of the suffix of
   // length j (j = 1..m).
-  const int m = s_m;
-  int32_t* rec = s_rec;
   if (static_cast<int>(threadIdx.x) < m) s_act[threadIdx.x] = static_cast<uint32_t>(rec[kStreamHead + threadIdx.x]);
   __syncthreads();
 
@@ -224,12 +243,12 @@ __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* _
   }
 }
 
-// Long segments (rollouts), two kernels.  The first checks and binds each
-// entry (one workgroup), walks the chains that start before the segment --
-// the only readers of the stream's old active nodes -- and leaves its verdict
-// in the record's spare word; the second spreads the chains that start inside
-// the segments over the whole GPU, a slice of a segment per workgroup, and
-// its last chains write the new active nodes.
+// The long entries of a call (rollouts), spread over the whole GPU: the first
+// workgroup of an entry walks the chains that start before the segment -- the
+// only readers of the stream's old active nodes -- and the last D - 1 of it,
+// which write the new ones; the others take a slice of the rest each.  The
+// first kernel's verdict holds for the whole entry: a cache that fills up in
+// the meantime takes all of it (as far as the table has slots).
 // What bounds it: atomics on random slots, which run at memory (every one of
 // the 2.4 a step takes leaves the L2): a step of one CAS and one exchange
 // alone runs at 11.7 G/s on a 671 MB table, this kernel at about 9 G/s.  The
@@ -240,64 +259,15 @@ __global__ __launch_bounds__(1024) void insert_kernel(void* ws, const int32_t* _
 // one prompt meet at the same nodes, and 256-thread workgroups took 4.0 ms
 // for the same build against 3.4 (64-thread ones 3.3, but 10-20% more where
 // every stream has a prompt of its own).
-// kShortStride: up to there one 1024-thread workgroup walks an entry's chains
-// in one round, in one launch.  At 512 tokens and 8 to 64 entries it takes
-// 132-136 us for new streams and 173-209 us for continued ones, the two
-// kernels 101-118 and 213-242; at 1024 tokens, two rounds, 137-221 and
-// 253-366 against 85-187 and 238-327.
-constexpr int kShortStride = 960;
-constexpr int64_t kBodyGrid = 32768;  // workgroups aimed at; more tokens loop
-constexpr int kHeadThreads = 512;
+// A call with wide rows and short segments only pays for the empty launch: 64
+// segments of 5 tokens in rows of 16384 take 13 us, 10 without it.
+constexpr int kShortStride = 960;     // one launch up to here
+// Workgroups aimed at; more tokens loop.  With 16384 or 8192 the build above
+// takes 3.45 or 3.70 ms instead of 3.34, 8 segments of 8 tokens in rows of 2^20
+// 16 or 14 us instead of 19.
+constexpr int64_t kBodyGrid = 32768;
 constexpr int kBodyThreads = 128;
-
-__global__ __launch_bounds__(kHeadThreads) void insert_head_kernel(void* ws, const int32_t* __restrict__ prompt_ids,
-                                                                   const int32_t* __restrict__ stream_ids,
-                                                                   const int32_t* __restrict__ tokens,
-                                                                   const int32_t* __restrict__ lengths,
-                                                                   int32_t stride) {
-  const TrieView t = trie_view_dev(ws);
-  const int entry = blockIdx.x;
-  __shared__ int s_ok, s_m;
-  __shared__ int32_t* s_rec;
-  __shared__ uint32_t s_created;
-  const int p = prompt_ids[entry];
-  const int len = lengths[entry];
-  const int32_t* tok = tokens + static_cast<int64_t>(entry) * stride;
-  if (threadIdx.x == 0) {
-    int m = 0;
-    int32_t* rec = nullptr;
-    s_ok = bind_entry(t, p, stream_ids[entry], len, stride, rec, m);
-    s_m = m;
-    s_rec = rec;
-    s_created = 0;
-    // What the second kernel does not look at again (a full table) is recorded
-    // too; an entry with an id out of range touches no record.
-    if (!s_ok && rec_of(t, p, stream_ids[entry], rec)) rec[kStreamHead + t.depth - 1] = 0;
-  }
-  __syncthreads();
-  if (!s_ok) return;
-  int bad = 0;
-#pragma unroll 8
-  for (int j = threadIdx.x; j < len; j += kHeadThreads) bad |= tok[j] < 0;
-  bad = __syncthreads_or(bad);
-  int32_t* rec = s_rec;
-  const int m = s_m;
-  uint32_t act = kNone;
-  if (!bad && static_cast<int>(threadIdx.x) < m) act = static_cast<uint32_t>(rec[kStreamHead + threadIdx.x]);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (bad) set_flag(t, SRT_FLAG_STREAM);
-    rec[kStreamHead + t.depth - 1] = bad ? 0 : 1;
-    if (!bad) rec[1] = rec[1] + len;
-  }
-  if (bad) return;
-  if (static_cast<int>(threadIdx.x) < m) {
-    const uint32_t made = walk_chain(t, tok, len, 0, act, threadIdx.x + 1, rec);
-    if (made) atomicAdd(&s_created, made);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) charge(t, s_created);
-}
+static_assert(kBodyThreads >= 2 * 63, "the first workgroup's chains: at most 63 before the segment, 63 last ones");
 
 __global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, const int32_t* __restrict__ prompt_ids,
                                                                    const int32_t* __restrict__ stream_ids,
@@ -306,24 +276,34 @@ __global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, con
                                                                    int32_t stride, int32_t parts) {
   const int entry = blockIdx.x / parts, part = blockIdx.x - entry * parts;
   const int len = lengths[entry];
-  if (part * kBodyThreads >= len) return;
+  const int64_t slice = parts > 1 ? part - 1 : 0;  // (-1: the first workgroup, no slice)
+  if (len <= 0 || slice * kBodyThreads >= len) return;
   const TrieView t = trie_view_dev(ws);
-  // The first kernel's verdict holds for the whole entry: a cache that fills
-  // up in the meantime takes all of it (as far as the table has slots).
   const int p = prompt_ids[entry];
   int32_t* rec = nullptr;
   if (len > stride || !rec_of(t, p, stream_ids[entry], rec) || rec[kStreamHead + t.depth - 1] != 1) return;
   const int32_t* tok = tokens + static_cast<int64_t>(entry) * stride;
+  const int tid = threadIdx.x;
   const uint32_t root = t.roots[p];
-  uint32_t made = 0;
-  for (int k = part * kBodyThreads + threadIdx.x; k < len; k += parts * kBodyThreads)
-    made += walk_chain(t, tok, len, k, root, 0, rec);
+  const int last = min(len, t.depth - 1);  // chains that reach the segment's end
   __shared__ uint32_t s_created;
-  if (threadIdx.x == 0) s_created = 0;
+  if (tid == 0) s_created = 0;
+  uint32_t made = 0;
+  if (part == 0) {
+    const int m = min(rec[1], t.depth - 1);
+    const uint32_t act = tid < m ? static_cast<uint32_t>(rec[kStreamHead + tid]) : kNone;
+    __syncthreads();  // the old active nodes are read
+    if (tid < m) made = walk_chain(t, tok, len, 0, act, tid + 1, rec);
+    else if (kBodyThreads - 1 - tid < last) made = walk_chain(t, tok, len, len - kBodyThreads + tid, root, 0, rec);
+    if (tid == 0) rec[1] = rec[1] + len;
+  }
+  if (slice >= 0)
+    for (int64_t k = slice * kBodyThreads + tid; k < len - last; k += static_cast<int64_t>(max(parts - 1, 1)) * kBodyThreads)
+      made += walk_chain(t, tok, len, static_cast<int>(k), root, 0, rec);
   __syncthreads();
   if (made) atomicAdd(&s_created, made);
   __syncthreads();
-  if (threadIdx.x == 0) charge(t, s_created);
+  if (tid == 0) charge(t, s_created);
 }
 
 __global__ void reset_streams_kernel(void* ws, int32_t n, const int32_t* __restrict__ ids) {
@@ -459,8 +439,8 @@ int srt_trie_insert(void* ws, int32_t n, const int32_t* prompt_ids, const int32_
   hipStream_t s = as_stream(stream);
   if (stride > kShortStride) {
     const int64_t slices = (static_cast<int64_t>(stride) + kBodyThreads - 1) / kBodyThreads;
-    const int32_t parts = static_cast<int32_t>(std::min<int64_t>(slices, std::max<int64_t>(1, kBodyGrid / n)));
-    insert_head_kernel<<<n, kHeadThreads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
+    const int32_t parts = static_cast<int32_t>(std::min<int64_t>(slices + 1, std::max<int64_t>(1, kBodyGrid / n)));
+    insert_kernel<true><<<n, kLongThreads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
     insert_body_kernel<<<static_cast<unsigned>(static_cast<int64_t>(n) * parts), kBodyThreads, 0, s>>>(
         ws, prompt_ids, stream_ids, tokens, lengths, stride, parts);
     return launch_status();
@@ -469,7 +449,7 @@ int srt_trie_insert(void* ws, int32_t n, const int32_t* prompt_ids, const int32_
   // one per token)
   const int64_t starts = static_cast<int64_t>(stride) + 63;
   const unsigned threads = static_cast<unsigned>(std::min<int64_t>(1024, (starts + 63) / 64 * 64));
-  insert_kernel<<<n, threads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
+  insert_kernel<false><<<n, threads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
   return launch_status();
 }
 

@@ -229,3 +229,28 @@ def test_long_segment_after_overflow_is_dropped():
     assert before["flags"] & srt.SRT_FLAG_CAPACITY
     c.insert([0, 0], np.array([0, 1], np.int32), [np.arange(1200), np.arange(1200)])
     assert c.status()["nodes"] == before["nodes"]
+
+
+@pytest.mark.parametrize("D", [1, 20, 64])
+def test_segments_at_the_edge_of_one_workgroup(D):
+    # rows wide enough for long segments: the chains of a stream's segment
+    # (tokens and active nodes) number 255, 256 and 257, empty ones between, then
+    # one more token for every stream
+    rng = np.random.default_rng(D)
+    have = [list(rng.integers(0, 30, size=n)) for n in (0, 0, 0, 100, 100, 100, 3, 0)]
+    c = Caches.create(2, 8, D, 20000 * D)
+    ids, prompts = np.arange(8, dtype=np.int32), [0, 1] * 4
+    say(f"cache: segments around one workgroup's chains, D={D}")
+    c.insert(prompts, ids, [np.array(h, dtype=np.int64) for h in have])
+    for step in range(2):
+        segs = []
+        for i, h in enumerate(have):
+            m = min(len(h), D - 1)
+            n = (255, 256, 257, 255 - m, 256 - m, 257 - m, 0, 1200)[i] if step == 0 else 1
+            segs.append(rng.integers(0, 30, size=n))
+        c.insert(prompts, ids, segs)
+        for h, s in zip(have, segs):
+            h.extend(s)
+        assert c.status()["flags"] == 0
+        for p in range(2):
+            check_prompt(c, p, [np.array(h) for h, q in zip(have, prompts) if q == p], D)
