@@ -82,7 +82,10 @@ typedef struct {
 size_t srt_trie_workspace_bytes(const srt_trie_config* cfg);
 
 /* Formats `ws` (device, ws_bytes >= srt_trie_workspace_bytes(cfg), 256-byte
- * aligned) as empty caches for every prompt and unbound streams. */
+ * aligned) as empty caches for every prompt and unbound streams.  The layout
+ * is this library version's own: a workspace that another one formatted (saved
+ * and restored by the caller, say) takes no insertion, drafts one-node trees,
+ * and srt_trie_status and srt_trie_export return SRT_ERR_INVALID. */
 int srt_trie_init(void* ws, size_t ws_bytes, const srt_trie_config* cfg, void* stream);
 
 /* Appends tokens to streams and updates the counts (online insertion).

@@ -806,7 +806,7 @@ __global__ __launch_bounds__(64) void draft_kernel(const void* ws, const int32_t
   const int32_t* tail = ctx_tail + static_cast<int64_t>(b) * Q;
   const int tlen = max(ctx_len[b], 0);
   const int p = prompt_ids[b];
-  const bool pvalid = p >= 0 && p < t.hdr->n_prompts;
+  const bool pvalid = t.hdr->magic == kMagic && p >= 0 && p < t.hdr->n_prompts;
   // Longest suffix with a continuation: lane q-1 tries length q.  The tail is
   // staged in LDS first, so that a step of the walk is one memory round trip
   // (a lookup, which also returns the node's list head).

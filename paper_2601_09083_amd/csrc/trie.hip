@@ -101,10 +101,11 @@ __global__ void create_roots_kernel(void* ws, int32_t n_prompts) {
 }
 
 // Checks entry `entry` of an insertion and binds its stream; false (with the
-// sticky flag set) if the entry is to be skipped.  m = active nodes of the
+// sticky flag set, unless the workspace is not of this layout) if the entry is
+// to be skipped.  m = active nodes of the
 // stream (lengths 1 .. m).
 __device__ inline bool bind_entry(const TrieView& t, int p, int sid, int len, int32_t stride, int32_t*& rec, int& m) {
-  if (t.hdr->flags & SRT_FLAG_CAPACITY) return false;
+  if (t.hdr->magic != kMagic || (t.hdr->flags & SRT_FLAG_CAPACITY)) return false;
   if (p < 0 || p >= t.hdr->n_prompts) {
     set_flag(t, SRT_FLAG_PROMPT);
     return false;
@@ -127,6 +128,7 @@ __device__ inline bool bind_entry(const TrieView& t, int p, int sid, int len, in
 
 // The record of stream sid if both ids are in range and it is bound to p.
 __device__ inline bool rec_of(const TrieView& t, int p, int sid, int32_t*& rec) {
+  if (t.hdr->magic != kMagic) return false;
   if (p < 0 || p >= t.hdr->n_prompts || sid < 0 || sid >= t.hdr->max_streams) return false;
   rec = t.streams + static_cast<int64_t>(sid) * t.hdr->stream_stride;
   return rec[0] == p;
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, con
 __global__ void reset_streams_kernel(void* ws, int32_t n, const int32_t* __restrict__ ids) {
   const TrieView t = trie_view_dev(ws);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i >= n || t.hdr->magic != kMagic) return;
   const int sid = ids[i];
   if (sid < 0 || sid >= t.hdr->max_streams) {
     set_flag(t, SRT_FLAG_STREAM);

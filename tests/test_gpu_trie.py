@@ -231,6 +231,32 @@ def test_long_segment_after_overflow_is_dropped():
     assert c.status()["nodes"] == before["nodes"]
 
 
+def test_a_workspace_of_another_layout_is_left_alone():
+    # the layout's mark in the header (its first word) of an older library
+    D = 6
+    c = Caches.create(1, 2, D, 20000)
+    say("cache: workspace of another layout")
+    seg = np.arange(40) % 7
+    c.insert([0], np.array([0], np.int32), [seg])
+    words = c.ws.view(torch.int32)
+    mark = int(words[0])
+    words[0] = 0x53525431
+    before = c.ws.clone()
+    for width in (10, 1000):
+        c.insert([0], np.array([1], np.int32), [np.arange(width)])
+    srt.srt_trie_reset_streams(c.ws, torch.tensor([0], dtype=torch.int32, device="cuda"))
+    one = torch.ones(1, dtype=torch.int32, device="cuda")
+    tail = torch.tensor([[3, 4, 5, 6]], dtype=torch.int32, device="cuda")
+    args = (c.ws, 0 * one, tail, 40 * one, 4, 8, 2)
+    assert srt.srt_draft(*args)["n_nodes"].item() == 1
+    with pytest.raises(srt.SrtError):
+        c.status()
+    assert torch.equal(c.ws, before)
+    words[0] = mark
+    assert srt.srt_draft(*args)["n_nodes"].item() > 1
+    check_prompt(c, 0, [seg], D)
+
+
 @pytest.mark.parametrize("D", [1, 20, 64])
 def test_segments_at_the_edge_of_one_workgroup(D):
     # rows wide enough for long segments: the chains of a stream's segment
