@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, con
                                                                    int32_t stride, int32_t parts) {
   const int entry = blockIdx.x / parts, part = blockIdx.x - entry * parts;
   const int len = lengths[entry];
-  const int64_t slice = parts > 1 ? part - 1 : 0;  // (-1: the first workgroup, no slice)
+  const int64_t slice = part - 1;  // (-1: the first workgroup, no slice)
   if (len <= 0 || slice * kBodyThreads >= len) return;
   const TrieView t = trie_view_dev(ws);
   const int p = prompt_ids[entry];
@@ -298,10 +298,10 @@ __global__ __launch_bounds__(kBodyThreads) void insert_body_kernel(void* ws, con
     if (tid < m) made = walk_chain(t, tok, len, 0, act, tid + 1, rec);
     else if (kBodyThreads - 1 - tid < last) made = walk_chain(t, tok, len, len - kBodyThreads + tid, root, 0, rec);
     if (tid == 0) rec[1] = rec[1] + len;
-  }
-  if (slice >= 0)
-    for (int64_t k = slice * kBodyThreads + tid; k < len - last; k += static_cast<int64_t>(max(parts - 1, 1)) * kBodyThreads)
+  } else {
+    for (int64_t k = slice * kBodyThreads + tid; k < len - last; k += static_cast<int64_t>(parts - 1) * kBodyThreads)
       made += walk_chain(t, tok, len, static_cast<int>(k), root, 0, rec);
+  }
   __syncthreads();
   if (made) atomicAdd(&s_created, made);
   __syncthreads();
@@ -441,7 +441,7 @@ int srt_trie_insert(void* ws, int32_t n, const int32_t* prompt_ids, const int32_
   hipStream_t s = as_stream(stream);
   if (stride > kShortStride) {
     const int64_t slices = (static_cast<int64_t>(stride) + kBodyThreads - 1) / kBodyThreads;
-    const int32_t parts = static_cast<int32_t>(std::min<int64_t>(slices + 1, std::max<int64_t>(1, kBodyGrid / n)));
+    const int32_t parts = static_cast<int32_t>(std::max<int64_t>(2, std::min<int64_t>(slices + 1, kBodyGrid / n)));
     insert_kernel<true><<<n, kLongThreads, 0, s>>>(ws, prompt_ids, stream_ids, tokens, lengths, stride);
     insert_body_kernel<<<static_cast<unsigned>(static_cast<int64_t>(n) * parts), kBodyThreads, 0, s>>>(
         ws, prompt_ids, stream_ids, tokens, lengths, stride, parts);
