@@ -285,11 +285,13 @@ int srt_accept_noalloc(int32_t B, int32_t N, int32_t V, int32_t Dmax, const floa
  * materialised logits bit for bit).  No [B, N, V] logits tensor is formed.
  * The walk advances in passes, each of which reads the head once.  A pass
  * computes the arg-max at the current node of every walking sequence and, as
- * long as it has room (256 rows), at the next nodes of those nodes' subtrees
- * in tree order, and the walks go on through the computed nodes (same
- * results: a node's dot product does not depend on the pass).  At most
- * min(Dmax + 1, ceil(N / max(1, 256 / B))) passes are enqueued; one with no
- * walking sequence exits at once.
+ * long as it has room, at the next nodes of those nodes' subtrees in tree
+ * order, and the walks go on through the computed nodes (same results: a
+ * node's dot product does not depend on the pass).  R, the rows that a pass
+ * has room for, is 64 or 256, chosen from B, V and Dmax alone; nodes that are
+ * all the walks can still reach are taken in one pass up to 256 (128 if
+ * Dmax <= 2 and d_model < 1024).  min(Dmax + 1, ceil(N / max(1, R / B)))
+ * passes are enqueued; one with no walking sequence exits at once.
  * Layouts: hidden [B, N, d_model] bf16 bits (the final hidden state of each
  * tree node), w_head [V, d_model] bf16 bits, both 16-byte aligned; gumbel
  * [B, Dmax+1, V] fp32 or NULL (greedy; inv_temperature then unused, else it

@@ -12,11 +12,10 @@
 //
 // GPU design.  The batch advances in passes; a pass reads the head once.
 //   * Rows of a pass: every sequence still walking brings its current node
-//     and, as long as the pass has room (kLook rows), the next nodes of that
+//     and, as long as the pass has room (see Fill), the next nodes of that
 //     node's subtree in tree order, the same number for everybody (draft
-//     rank order: likely descendants first).  A pass is bound by reading the
-//     head up to about 256 rows, so these rows are nearly free and each
-//     spares the walk a pass of its own.
+//     rank order: likely descendants first).  Each of these rows may spare
+//     the walk a pass of its own.
 //   * A product kernel multiplies the rows with the whole head and reduces
 //     each to one (score, token) candidate per tile of the vocabulary.
 //   * A walk kernel (one workgroup per walking sequence) follows the walk
@@ -45,7 +44,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kUnit = 16;                // head rows are shared out in units of 16
 constexpr int kKC = 64;                  // d_model elements per step (one 128-byte line of a row)
 constexpr int kRowBytes = kKC * 2 + 16;  // padded LDS row (conflict-free operand reads)
-// Rows that a pass is filled up to.  One pass over a 152064 x 3584 head takes
+// Rows that a pass is filled up to, at most.  One pass over a 152064 x 3584 head takes
 // 221 us for 64 rows, 260 for 128 and 380 for 256 (sampled; reading the head
 // alone takes 190), and the walks of 256 sequences, 13 levels deep, take 6
 // passes when filled to 256 rows, 9 when filled to 128 (2.36 against 2.59 ms)
@@ -76,7 +75,7 @@ struct HeadArgs {
   int32_t* place;           // [B, N] place of a node in its list
   unsigned long long* cand; // [max(B, kLook), n_cand] packed candidates of the pass
   int B, N, L, dm, V, Dmax, n_cand;
-  int look;                 // rows that a pass is filled up to (<= kLook)
+  int look, finish;         // see Fill
   int units, tiles;         // see Split
   float invT;
 };
@@ -111,14 +110,30 @@ inline Split split_for(int64_t V, int64_t d_model) {
   return s;
 }
 
-// Rows that passes over a head of this width are filled up to: nearly free up
-// to kLook while a pass is bound by reading the head or by its own latency,
-// less for a narrow head, whose rows' noise (4 V bytes each, against 2 d_model
-// V for the head) soon costs as much.  Walks of at most three steps end about
-// as soon with 64 rows (21 sequences, 47-node trees, V 15805, d 2176, depth 2:
-// two passes either way, 68 us filled to 256 rows and 56 filled to 64).
-inline int look_for(int d_model, int Dmax) {
-  return Dmax <= 2 ? 64 : std::min(kLook, std::max(64, d_model / 4 / 64 * 64));
+// Rows that passes are filled up to (look), and nodes up to which a pass takes
+// every one the walks can still reach, so that it is the last (finish; at most
+// kLook).
+// finish: kLook, as such a pass costs less than two smaller ones (us; V 151936,
+// d 1536, 32 sequences of 64 nodes, Dmax 6, greedy: 434 without, 300 with it; 8 of
+// 32, Dmax 2: 209 and 134); 128 where two passes end most walks and the rows'
+// noise (4 V bytes each, against 2 d_model V for the head) weighs most (d 896,
+// 16 sequences of 32, Dmax 2, sampled: 138 with 128, 150 with kLook; d 2048:
+// 272 and 196).
+// look: kLook, as up to there rows cost less than the passes that they spare
+// (256 sequences, Dmax 8, d 1536: 948 us with 64, 853 with 256; 16 sequences of
+// 32, Dmax 8, d 3584: 380 and 360).  64 where they do not: for walks that two or
+// three passes end anyhow (32 sequences, Dmax 2, sampled, d 2048: 334 with 64, 357
+// with 128), and for 25 to 96 sequences, which have a row or two each then, most of
+// them of walks that end at the root (64 sequences of 32, Dmax 8, sampled: d 896
+// 322 and 396, d 1536 452 and 542, d 3584 820 and 967); heads under 24000 rows are
+// too small for the rows to weigh (V 4096, d 1024: 89 and 86).
+struct Fill {
+  int look, finish;
+};
+
+inline Fill fill_for(int B, int V, int d_model, int Dmax) {
+  const bool brief = Dmax <= 2;
+  return {brief || (B > 24 && B <= 96 && V >= 24000) ? 64 : kLook, brief && d_model < 1024 ? 128 : kLook};
 }
 
 // Scratch layout: counters, lists, node places, candidates.
@@ -234,15 +249,15 @@ struct PassShared {
 };
 
 // Rows of the pass: fills s.base (W <= kLook walkers) and returns their
-// number.  Each walker takes the first min(q, listed) nodes of its list, q
-// the largest number for which the rows fit, and the first walkers with more
-// listed one more each while rows are left.  Every workgroup works this out
+// number.  Where all listed nodes are few they are the pass.  Else each walker
+// takes the first min(q, listed) nodes of its list, q the largest number for
+// which the rows fit, and the first walkers with more listed one more each
+// while rows are left.  Every workgroup works this out
 // for itself; the first records it for the walk kernel.
 template <typename Shared>
 __device__ inline int pass_rows(const HeadArgs& a, int pass, int W, Shared& s) {
   static_assert(kLook == 256 && kLook % SRT_WAVE == 0, "a thread per walker (workgroups have 256 or more)");
   const int tid = threadIdx.x, lane = tid % SRT_WAVE;
-  const int look = max(a.look, W);
   if (tid < kLook) {
     const int2 x = tid < W ? a.act[static_cast<int64_t>(pass & 1) * a.B + tid] : make_int2(0, 0);
     s.seq[tid] = min(max(x.x, 0), a.B - 1);
@@ -250,12 +265,13 @@ __device__ inline int pass_rows(const HeadArgs& a, int pass, int W, Shared& s) {
   }
   __syncthreads();
   // thread t tries the quota t + 1 (the rows grow with it; 1 always fits)
-  int v = 0;
-  if (tid < kLook)
-    for (int i = 0; i < W; i += 4) {  // (entries past W are 0)
-      const int4 c4 = *reinterpret_cast<const int4*>(&s.cnt[i]);
-      v += min(c4.x, tid + 1) + min(c4.y, tid + 1) + min(c4.z, tid + 1) + min(c4.w, tid + 1);
-    }
+  int v = 0, all = 0;
+  for (int i = 0; i < W; i += 4) {  // (entries past W are 0)
+    const int4 c4 = *reinterpret_cast<const int4*>(&s.cnt[i]);
+    v += min(c4.x, tid + 1) + min(c4.y, tid + 1) + min(c4.z, tid + 1) + min(c4.w, tid + 1);
+    all += c4.x + c4.y + c4.z + c4.w;
+  }
+  const int look = all <= a.finish ? kLook : max(a.look, W);
   const int q = __syncthreads_count(tid < kLook && v <= look);
   if (tid == q - 1) s.rows = v;
   __syncthreads();
@@ -747,7 +763,9 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.V = V;
   a.Dmax = Dmax;
   a.L = std::min(N, kLook);
-  a.look = look_for(d_model, Dmax);
+  const Fill fill = fill_for(B, V, d_model, Dmax);
+  a.look = fill.look;
+  a.finish = fill.finish;
   a.n_cand = sp.wide ? sp.grid * sp.tiles : sp.tiles;
   a.units = sp.units;
   a.tiles = sp.tiles;

@@ -256,6 +256,40 @@ def planted_tree(rng, B, N, Dmax, V, deep):
     return {"tree_tokens": tt, "tree_parent": tp, "n_nodes": nn}
 
 
+@pytest.mark.parametrize("B,N,Dmax,V,d,sampled", [
+    (40, 20, 19, 24000, 64, False),  # 64 rows: 24 of 40 walkers bring a second node
+    (40, 20, 19, 23999, 64, True),   # 256 rows
+    (24, 16, 9, 24000, 64, False),   # 24 and 97 sequences: 256 rows
+    (25, 16, 9, 24000, 64, True),
+    (97, 8, 7, 24000, 64, False),
+    (16, 16, 15, 500, 64, True),     # 256 nodes in all: one pass
+    (17, 16, 15, 500, 64, False),    # 272: 256 of them, then what is left
+    (8, 16, 2, 500, 64, True),       # short walks: 128 nodes, one pass
+    (9, 16, 2, 500, 64, False),      # 144: 64 rows
+    (16, 16, 2, 500, 1024, True),    # 256 nodes and a wider head: one pass
+    (70, 5, 1, 500, 128, False),     # 70 walkers in passes of 64 rows: their own nodes
+])
+def test_rows_of_a_pass(B, N, Dmax, V, d, sampled):
+    """Full trees on both sides of every rule that gives a pass its rows."""
+    rng = np.random.default_rng(B * 100 + N)
+    say(f"lmhead rows of a pass: B={B} N={N} Dmax={Dmax} V={V} d={d}")
+    tree = planted_tree(rng, B, N, Dmax, V, N // 2)
+    tree["n_nodes"][:] = N
+    for b in range(B):
+        for i in range(1, N):
+            if tree["tree_parent"][b, i] < 0:
+                tree["tree_parent"][b, i] = rng.integers(0, i)
+                tree["tree_tokens"][b, i] = rng.integers(0, V)
+    hidden, w = W.make_head(B, N, d, V, device="cuda", seed=B + N, kind="int", tree_tokens=tree["tree_tokens"],
+                            tree_parent=tree["tree_parent"], n_nodes=tree["n_nodes"], plant_p=0.9)
+    gumbel = torch.randint(-3, 4, (B, Dmax + 1, V), device="cuda").float() if sampled else None
+    got = run_fused(hidden, w, gumbel, 1.0, tree, Dmax)
+    want = oracle_rows(hidden, w, gumbel, 1.0, tree, range(B), Dmax)
+    for b in range(B):
+        assert_accept_equal(got, b, want[b], Dmax)
+    assert got["n_accepted"].max() >= 1
+
+
 @pytest.mark.parametrize("B,N,Dmax,V,d,deep,sampled", [
     (1, 64, 20, 4096, 64, 20, True),      # one sequence: its whole tree in one pass
     (2, 300, 40, 300, 128, 40, False),    # trees longer than a pass's list
