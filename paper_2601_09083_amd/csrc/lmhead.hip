@@ -81,28 +81,35 @@ struct HeadArgs {
 };
 
 // How a pass divides the head.  Large heads (wide): 16-row units shared out
-// evenly over at most kGrid workgroups, one per CU, each of which reads its
-// share in tiles of up to 256 rows.  Small ones: 128-row tiles, a workgroup
-// for each and 64 rows of the pass.
+// evenly over kGrid workgroups, one per CU, each of which reads its share (at
+// least 128 rows) in tiles of up to 256 rows.  Small ones: 128-row tiles, a
+// workgroup for each and 64 or 128 rows of the pass.
 struct Split {
-  bool wide;
+  bool wide, tall;
   int units, grid, tiles;  // wide: units, workgroups, tiles per workgroup; else tiles in all
 };
 
-// A head that the caches hold is not worth keeping every CU streaming for:
-// there more, smaller workgroups finish a pass sooner (56 sequences, 20-node
-// trees, V 7918, d 1472, greedy: 71 us on wide tiles, 63 on small ones; 27
-// sequences, 7 nodes, V 14227, d 1280, sampled: 38 and 33).
-constexpr int64_t kWideBytes = int64_t(128) << 20;
+// The line lies where the small tiles need more than one round of the CUs.
+// Small and wide tiles, us: V 32768, d 1024, 256 sequences of 32 nodes, Dmax 8
+// 210 and 224, 8 of 32, Dmax 2 31 and 36 (d 2048, 256 of 64, Dmax 1 104 and 120);
+// V 36000, the same 264 and 235, 39 and 37 (d 2560 433 and 392, 64 and 58);
+// V 65536, d 512 (64 MB) 264 and 200.  The head's bytes make no difference: what
+// decides is how many CUs have a tile, and how full theirs are.
+constexpr int kSmallTiles = kGrid;
+// Passes of more than 64 rows over small heads: workgroups of 128 rows read the
+// head half as often, but up to here those of 64 finish 256 rows in one round of
+// two a CU (us with 64 and with 128 rows, d 4096, 256 sequences of 64 nodes, Dmax
+// 1: V 8192 83 and 108, 16384 105 and 113, 18432 145 and 134, 32768 194 and 167; d
+// 512: 16384 46 and 53, 18432 62 and 59).
+constexpr int kFlatTiles = kGrid / 2;
 
-inline Split split_for(int64_t V, int64_t d_model) {
+inline Split split_for(int64_t V) {
   Split s;
-  s.wide = V >= 128 * kGrid && V * d_model * 2 >= kWideBytes;
-  if (!s.wide) {
-    s.units = s.grid = 0;
-    s.tiles = static_cast<int>((V + 127) / 128);
-    return s;
-  }
+  s.units = s.grid = 0;
+  s.tiles = static_cast<int>((V + 127) / 128);
+  s.wide = s.tiles > kSmallTiles;
+  s.tall = !s.wide && s.tiles > kFlatTiles;
+  if (!s.wide) return s;
   s.units = static_cast<int>((V + kUnit - 1) / kUnit);
   s.grid = kGrid;
   const int per = s.grid * (256 / kUnit);
@@ -151,7 +158,7 @@ inline ScratchLayout scratch_layout(int64_t B, int64_t N, int64_t V) {
   s.off_place = s.off_list + up(sizeof(int2) * b * std::min<size_t>(n, kLook));
   s.off_cand = s.off_place + up(sizeof(int32_t) * b * n);
   // one candidate per row and 128 head rows (the wide division has no more:
-  // kGrid per 256 kGrid rows, from 128 kGrid rows on)
+  // kGrid per 256 kGrid rows or part of them, from 128 kGrid rows on)
   s.total = s.off_cand +
             up(sizeof(unsigned long long) * std::max<size_t>(b, kLook) * ((static_cast<size_t>(V) + 127) / 128));
   return s;
@@ -357,8 +364,11 @@ struct Rows128 {
 struct Rows256 {
   static constexpr int WV = 4, VT = 2, WS = 2, ST = 4, kRing = 2, kRingH = 1;
 };
-struct Small {
+struct Small64 {
   static constexpr int WV = 4, VT = 1, WS = 1, ST = 2, kRing = 4, kRingH = 4;
+};
+struct Small128 {
+  static constexpr int WV = 2, VT = 2, WS = 2, ST = 2, kRing = 4, kRingH = 4;
 };
 
 // One tile: head rows v0 .. v_end-1 (at most TV) times the TM rows of the pass
@@ -597,23 +607,33 @@ __global__ __launch_bounds__(512, 1) void head_pass_kernel(HeadArgs a, int pass)
 }
 
 // The same over a small head: a workgroup takes 128 head rows and 64 rows of
-// the pass, working ones first in dispatch order; those of one tile are on
-// one XCD, whose L2 serves the head rows they share.
-template <bool kNoise>
+// the pass (kTall: 128 of a pass of more than 64), working ones first in
+// dispatch order; those of one tile are on one XCD, whose L2 serves the head
+// rows they share.
+template <bool kNoise, bool kTall>
 __global__ __launch_bounds__(256, 2) void head_small_kernel(HeadArgs a, int pass) {
-  using Shared = PassShared<128, 64>;
+  constexpr int TM = kTall ? 128 : 64;
+  using Shared = PassShared<128, TM>;  // 79 KB or less, two workgroups a CU
   __shared__ __attribute__((aligned(16))) Shared s;
   const int W = a.n_act[pass];
   if (W <= 0) return;
   const int n_rows = W <= kLook ? pass_rows(a, pass, W, s) : W;
-  const int n_mb = (n_rows + 63) / 64;
+  const int tm = n_rows > 64 ? TM : 64;
+  const int n_mb = (n_rows + tm - 1) / tm;
   const int i = blockIdx.x / kXcds;
   const int vt = i / n_mb * kXcds + blockIdx.x % kXcds;
   if (vt >= a.tiles) return;
-  const int m0 = i % n_mb * 64;
-  row_offsets<64>(a, pass, W, n_rows, m0, s);
+  const int m0 = i % n_mb * tm;
+  row_offsets<TM>(a, pass, W, n_rows, m0, s);
   __syncthreads();
-  head_tile<kNoise, Small>(a, s, vt * 128, min(vt * 128 + 128, a.V), m0, min(n_rows, m0 + 64), vt);
+  const int v0 = vt * 128, v1 = min(v0 + 128, a.V), m1 = min(n_rows, m0 + tm);
+  if constexpr (kTall) {
+    if (tm == TM) {
+      head_tile<kNoise, Small128>(a, s, v0, v1, m0, m1, vt);
+      return;
+    }
+  }
+  head_tile<kNoise, Small64>(a, s, v0, v1, m0, m1, vt);
 }
 
 // Best candidate of one row over the tiles: every thread of the workgroup
@@ -734,7 +754,7 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   if (reinterpret_cast<uintptr_t>(scratch) & 255) return SRT_ERR_INVALID;
   const ScratchLayout L = scratch_layout(B, N, V);
   if (scratch_bytes < L.total) return SRT_ERR_CAPACITY;
-  const Split sp = split_for(V, d_model);
+  const Split sp = split_for(V);
   const int64_t small_grid = static_cast<int64_t>((sp.tiles + kXcds - 1) / kXcds * kXcds) *
                              ((std::max<int64_t>(B, kLook) + 63) / 64);
   if (small_grid > 0x7FFFFFFF) return SRT_ERR_UNSUPPORTED;
@@ -784,8 +804,13 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
       else head_pass_kernel<false><<<sp.grid, 512, 0, s>>>(a, pass);
     } else {
       const unsigned grid = static_cast<unsigned>(small_grid);
-      if (gumbel) head_small_kernel<true><<<grid, 256, 0, s>>>(a, pass);
-      else head_small_kernel<false><<<grid, 256, 0, s>>>(a, pass);
+      if (sp.tall) {
+        if (gumbel) head_small_kernel<true, true><<<grid, 256, 0, s>>>(a, pass);
+        else head_small_kernel<false, true><<<grid, 256, 0, s>>>(a, pass);
+      } else {
+        if (gumbel) head_small_kernel<true, false><<<grid, 256, 0, s>>>(a, pass);
+        else head_small_kernel<false, false><<<grid, 256, 0, s>>>(a, pass);
+      }
     }
     st = launch_status();
     if (st != SRT_OK) break;

@@ -256,6 +256,34 @@ def planted_tree(rng, B, N, Dmax, V, deep):
     return {"tree_tokens": tt, "tree_parent": tp, "n_nodes": nn}
 
 
+@pytest.mark.parametrize("V,d,split", [
+    (16384, 64, "small, 64 rows"), (16385, 192, "small, 64 or 128 rows"), (32768, 320, "small, 64 or 128 rows"),
+    (32769, 320, "wide"), (40001, 2112, "wide"), (65537, 1088, "wide, two tiles a workgroup")])
+@pytest.mark.parametrize("B,N,Dmax,sampled", [(30, 6, 5, False), (110, 4, 3, True), (300, 3, 2, True), (290, 5, 4, False)])
+def test_both_divisions_of_the_head(V, d, split, B, N, Dmax, sampled):
+    """The head on both sides of every line between its divisions, with
+    vocabularies that are no multiple of a tile, a unit or 4 (noise rows then
+    start at any float) and odd numbers of 64-wide steps (1, 3, 5, 17, 33),
+    in passes of up to 64, up to 128, up to 256 and more rows (the sequences'
+    own nodes and those looked ahead at)."""
+    tiles = -(-V // 128)
+    assert split == ("small, 64 rows" if tiles <= 128 else "small, 64 or 128 rows" if tiles <= 256 else
+                     "wide" if V <= 65536 else "wide, two tiles a workgroup")
+    rng = random.Random(V + B)
+    say(f"lmhead divisions: V={V} d={d} ({split}) B={B} N={N} Dmax={Dmax} sampled={sampled}")
+    tree = random_trees(rng, B, N, Dmax, V)
+    hidden, w = W.make_head(B, N, d, V, device="cuda", seed=V + B, kind="int", tree_tokens=tree["tree_tokens"],
+                            tree_parent=tree["tree_parent"], n_nodes=tree["n_nodes"], plant_p=0.9)
+    gumbel = torch.randint(-3, 4, (B, Dmax + 1, V), device="cuda").float() if sampled else None
+    got = run_fused(hidden, w, gumbel, 1.0, tree, Dmax)
+    assert_same(got, run_materialised(hidden, w, gumbel, 1.0, tree, Dmax), B)
+    seqs = sorted(rng.sample(range(B), 6)) + [int(np.argmax(got["n_accepted"]))]
+    want = oracle_rows(hidden, w, gumbel, 1.0, tree, seqs, Dmax)
+    for b in seqs:
+        assert_accept_equal(got, b, want[b], Dmax)
+    assert got["n_accepted"].max() >= 1
+
+
 @pytest.mark.parametrize("B,N,Dmax,V,d,sampled", [
     (40, 20, 19, 24000, 64, False),  # 64 rows: 24 of 40 walkers bring a second node
     (40, 20, 19, 23999, 64, True),   # 256 rows
