@@ -110,6 +110,7 @@ inline Split split_for(int64_t V) {
   s.wide = s.tiles > kSmallTiles;
   s.tall = !s.wide && s.tiles > kFlatTiles;
   if (!s.wide) return s;
+  static_assert(kSmallTiles * 128 / kUnit >= 8 * kGrid, "units for every workgroup");
   s.units = static_cast<int>((V + kUnit - 1) / kUnit);
   s.grid = kGrid;
   const int per = s.grid * (256 / kUnit);
@@ -592,10 +593,8 @@ __global__ __launch_bounds__(512, 1) void head_pass_kernel(HeadArgs a, int pass)
       const int v0 = (u0 + static_cast<int>(static_cast<int64_t>(g) * nu / shares)) * kUnit;
       const int v1 = min((u0 + static_cast<int>(static_cast<int64_t>(g + 1) * nu / shares)) * kUnit, a.V);
       const int col = t * shares + g, m = n_rows - m0;
-      if (v0 >= v1) {  // no unit of this tile: no candidate
-        const int r = m0 + static_cast<int>(threadIdx.x);
-        if (threadIdx.x < 256 && r < n_rows) a.cand[static_cast<int64_t>(r) * a.n_cand + col] = 0;
-      } else if (m <= 64) {
+      // (a tile has 2048 units or more, so every share has at least 8: v0 < v1)
+      if (m <= 64) {
         head_tile<kNoise, Rows64>(a, s, v0, v1, m0, n_rows, col);
       } else if (m <= 128) {
         head_tile<kNoise, Rows128>(a, s, v0, v1, m0, n_rows, col);
