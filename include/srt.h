@@ -298,12 +298,14 @@ int srt_accept_noalloc(int32_t B, int32_t N, int32_t V, int32_t Dmax, const floa
  * must be finite); tree arrays and outputs as srt_accept (unused entries
  * of out_tokens / out_nodes are -1).  d_model must be a multiple of 64
  * (else SRT_ERR_UNSUPPORTED); 0 <= Dmax <= 63.
- * scratch: device buffer, 256-byte aligned, of at least
- * srt_accept_lmhead_scratch_bytes(B, N, V) bytes (else SRT_ERR_CAPACITY):
- * per-pass lists of walking sequences and of their subtrees' nodes, a table
- * of the nodes' places in them (4 bytes per tree node) and per-tile arg-max
- * candidates (8 bytes per row and tile, for max(B, 256) rows).  Owned by
- * the caller; contents are overwritten; calls sharing a scratch buffer must
+ * scratch: device buffer, 256-byte aligned, of
+ * srt_accept_lmhead_scratch_bytes(B, N, V) bytes: per-pass lists of walking
+ * sequences and of their subtrees' nodes, a table of the nodes' places in
+ * them (4 bytes per tree node) and per-tile arg-max candidates (8 bytes per
+ * row and tile, for max(B, 256) rows).  A scratch of the size that passes
+ * without looking ahead need (max(B, 128) rows, no lists; what earlier
+ * versions asked for) or of more whole 256 bytes is taken too, with fewer
+ * rows a pass; else SRT_ERR_CAPACITY.  Owned by the caller; contents are overwritten; calls sharing a scratch buffer must
  * not overlap.
  * ---------------------------------------------------------------------- */
 size_t srt_accept_lmhead_scratch_bytes(int32_t B, int32_t N, int32_t V);

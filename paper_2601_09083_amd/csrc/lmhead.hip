@@ -69,10 +69,11 @@ struct HeadArgs {
   int32_t* out_nodes;
   int32_t* n_emitted;
   int32_t* n_act;           // [kMaxLevels + 1] walking sequences per pass
-  int2* act;                // [2, B] walking sequences and their listed nodes, by pass parity
+  int32_t* act;             // [2, B] walking sequences, by pass parity
+  int32_t* listed;          // [2, B] their listed nodes, or null (one each)
   int2* span;               // [kLook] first row and row count of each walker of the pass
-  int2* list;               // [B, min(N, kLook)] (node, depth) of each sequence's next subtree
-  int32_t* place;           // [B, N] place of a node in its list
+  int2* list;               // [B, L] (node, depth) of each sequence's next subtree
+  int32_t* place;           // [B, N] place of a node in its list, or null (L = 1)
   unsigned long long* cand; // [max(B, kLook), n_cand] packed candidates of the pass
   int B, N, L, dm, V, Dmax, n_cand;
   int look, finish;         // see Fill
@@ -144,25 +145,58 @@ inline Fill fill_for(int B, int V, int d_model, int Dmax) {
   return {brief || (B > 24 && B <= 96 && V >= 24000) ? 64 : kLook, brief && d_model < 1024 ? 128 : kLook};
 }
 
-// Scratch layout: counters, lists, node places, candidates.
+// Scratch layout: counters, lists, node places, candidates of passes of up to
+// `rows` rows (or a row for each sequence).  rows = 1: the walking sequences'
+// own nodes only.
 struct ScratchLayout {
-  size_t off_act, off_span, off_list, off_place, off_cand, total;
+  int rows, L;
+  size_t off_act, off_listed, off_span, off_list, off_place, off_cand, total;
 };
 
-inline ScratchLayout scratch_layout(int64_t B, int64_t N, int64_t V) {
-  auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
+inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
+
+inline ScratchLayout scratch_layout(int64_t B, int64_t N, int rows, int64_t n_cand) {
   ScratchLayout s;
   const size_t b = static_cast<size_t>(B), n = static_cast<size_t>(N);
-  s.off_act = up(sizeof(int32_t) * (kMaxLevels + 1));
-  s.off_span = s.off_act + up(sizeof(int2) * 2 * b);
-  s.off_list = s.off_span + up(sizeof(int2) * kLook);
-  s.off_place = s.off_list + up(sizeof(int2) * b * std::min<size_t>(n, kLook));
-  s.off_cand = s.off_place + up(sizeof(int32_t) * b * n);
-  // one candidate per row and 128 head rows (the wide division has no more:
-  // kGrid per 256 kGrid rows or part of them, from 128 kGrid rows on)
+  s.rows = rows;
+  s.L = static_cast<int>(std::min<int64_t>(N, rows));
+  s.off_act = up256(sizeof(int32_t) * (kMaxLevels + 1));
+  s.off_listed = s.off_act + up256(sizeof(int32_t) * 2 * b);
+  s.off_span = s.off_listed + (rows > 1 ? up256(sizeof(int32_t) * 2 * b) : 0);
+  s.off_list = s.off_span + up256(sizeof(int2) * kLook);
+  s.off_place = s.off_list + up256(sizeof(int2) * b * s.L);
+  s.off_cand = s.off_place + (rows > 1 ? up256(sizeof(int32_t) * b * n) : 0);
   s.total = s.off_cand +
-            up(sizeof(unsigned long long) * std::max<size_t>(b, kLook) * ((static_cast<size_t>(V) + 127) / 128));
+            up256(sizeof(unsigned long long) * std::max<size_t>(b, rows) * static_cast<size_t>(n_cand));
   return s;
+}
+
+// The scratch that callers are asked for: room for full passes, and one
+// candidate per row and 128 head rows (the wide division has no more: kGrid per
+// 256 kGrid rows or part of them, from 128 kGrid rows on).
+inline size_t full_scratch(int64_t B, int64_t N, int64_t V) {
+  return scratch_layout(B, N, kLook, (V + 127) / 128).total;
+}
+
+// What callers were asked for while a pass took the sequences' own nodes, or
+// the last 128 in all.  Sizes from there on are accepted still, if they are
+// whole 256 bytes as every size is that callers were ever told: anything else
+// below the full size is a mistake.
+inline size_t least_scratch(int64_t B, int64_t N, int64_t V) {
+  const size_t b = static_cast<size_t>(B), n = static_cast<size_t>(N);
+  return 1024 + up256(8 * b) + 3072 + up256(4 * b) + up256(4 * b * n) +
+         up256(8 * std::max<size_t>(b, 128) * ((static_cast<size_t>(V) + 127) / 128));
+}
+
+// The layout of the fullest passes that a scratch of `bytes` has room for.
+// (rows = 1 fits the least one: 512 + 2048 + 2 up256(8 B) is no more than 4096 +
+// up256(8 B) + up256(4 B) + up256(4 B N), and a pass has B rows.)
+inline ScratchLayout layout_for(int64_t B, int64_t N, int64_t n_cand, size_t bytes) {
+  for (int rows = kLook; rows >= 64; rows -= 64) {
+    const ScratchLayout s = scratch_layout(B, N, rows, n_cand);
+    if (s.total <= bytes) return s;
+  }
+  return scratch_layout(B, N, 1, n_cand);
 }
 
 // Total order key of a (score, token) candidate: larger score first, then
@@ -211,7 +245,7 @@ __device__ inline int list_subtree(const HeadArgs& a, int b, int u, int du, int 
     if (depth >= 0) {
       const int j = base + __popcll(m & ((1ull << lane) - 1));
       if (j < a.L) a.list[static_cast<int64_t>(b) * a.L + j] = make_int2(c, depth);
-      a.place[tr + c] = j < a.L ? j : kUncovered;
+      if (a.place) a.place[tr + c] = j < a.L ? j : kUncovered;
     }
     base += __popcll(m);
   }
@@ -236,7 +270,10 @@ __global__ __launch_bounds__(SRT_WAVE) void head_init_kernel(HeadArgs a) {
     for (int c = lane; c < n; c += SRT_WAVE) s_par[c] = a.tree_parent[static_cast<int64_t>(b) * a.N + c];
   __syncthreads();
   const int listed = list_subtree(a, b, 0, 0, n, n <= kParents ? s_par : nullptr);
-  if (lane == 0) a.act[b] = make_int2(b, listed);
+  if (lane == 0) {
+    a.act[b] = b;
+    if (a.listed) a.listed[b] = listed;
+  }
 }
 
 // LDS of a product kernel: TV head rows and TM hidden rows a tile.
@@ -267,9 +304,9 @@ __device__ inline int pass_rows(const HeadArgs& a, int pass, int W, Shared& s) {
   static_assert(kLook == 256 && kLook % SRT_WAVE == 0, "a thread per walker (workgroups have 256 or more)");
   const int tid = threadIdx.x, lane = tid % SRT_WAVE;
   if (tid < kLook) {
-    const int2 x = tid < W ? a.act[static_cast<int64_t>(pass & 1) * a.B + tid] : make_int2(0, 0);
-    s.seq[tid] = min(max(x.x, 0), a.B - 1);
-    s.cnt[tid] = tid < W ? min(max(x.y, 1), a.L) : 0;
+    const int64_t at = static_cast<int64_t>(pass & 1) * a.B + tid;
+    s.seq[tid] = tid < W ? min(max(a.act[at], 0), a.B - 1) : 0;
+    s.cnt[tid] = tid >= W ? 0 : a.listed ? min(max(a.listed[at], 1), a.L) : 1;
   }
   __syncthreads();
   // thread t tries the quota t + 1 (the rows grow with it; 1 always fits)
@@ -341,7 +378,7 @@ __device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_row
       b = s.seq[lo];
       j = r - s.base[lo];
     } else {
-      b = min(max(a.act[static_cast<int64_t>(pass & 1) * a.B + r].x, 0), a.B - 1);
+      b = min(max(a.act[static_cast<int64_t>(pass & 1) * a.B + r], 0), a.B - 1);
     }
     const int2 x = a.list[static_cast<int64_t>(b) * a.L + j];
     ho = (static_cast<int64_t>(b) * a.N + min(max(x.x, 0), a.N - 1)) * a.dm;
@@ -680,7 +717,7 @@ __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int
   const int W = a.n_act[pass];
   if (slot >= W) return;
   const int tid = threadIdx.x, lane = tid % SRT_WAVE, wave = tid / SRT_WAVE;
-  const int b = min(max(a.act[static_cast<int64_t>(pass & 1) * a.B + slot].x, 0), a.B - 1);
+  const int b = min(max(a.act[static_cast<int64_t>(pass & 1) * a.B + slot], 0), a.B - 1);
   const int n = min(max(a.n_nodes[b], 1), a.N);
   const int64_t tr = static_cast<int64_t>(b) * a.N;
   const int64_t orow = static_cast<int64_t>(b) * (a.Dmax + 1);
@@ -717,7 +754,7 @@ __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int
     if (s_next < 0) return;
     u = s_next;
     ++k;
-    at = a.place[tr + u];
+    at = a.place ? a.place[tr + u] : kUncovered;
     if (at >= span.y) break;
   }
   __syncthreads();  // every wave has read the places that are rewritten now
@@ -725,7 +762,9 @@ __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int
   const int listed = list_subtree(a, b, u, k, n, staged ? s_par : nullptr);
   if (lane == 0) {
     const int pos = atomicAdd(&a.n_act[pass + 1], 1);
-    a.act[static_cast<int64_t>((pass + 1) & 1) * a.B + pos] = make_int2(b, listed);
+    const int64_t to = static_cast<int64_t>((pass + 1) & 1) * a.B + pos;
+    a.act[to] = b;
+    if (a.listed) a.listed[to] = listed;
   }
 }
 
@@ -733,7 +772,7 @@ __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int
 
 extern "C" size_t srt_accept_lmhead_scratch_bytes(int32_t B, int32_t N, int32_t V) {
   if (B < 0 || N < 1 || V < 1) return 0;
-  return scratch_layout(std::max(B, 1), N, V).total;
+  return full_scratch(std::max(B, 1), N, V);
 }
 
 extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t V, int32_t Dmax,
@@ -751,9 +790,11 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
     return SRT_ERR_INVALID;
   if ((reinterpret_cast<uintptr_t>(hidden) | reinterpret_cast<uintptr_t>(w_head)) & 15) return SRT_ERR_INVALID;
   if (reinterpret_cast<uintptr_t>(scratch) & 255) return SRT_ERR_INVALID;
-  const ScratchLayout L = scratch_layout(B, N, V);
-  if (scratch_bytes < L.total) return SRT_ERR_CAPACITY;
+  if (scratch_bytes < full_scratch(B, N, V) && (scratch_bytes < least_scratch(B, N, V) || scratch_bytes % 256 != 0))
+    return SRT_ERR_CAPACITY;
   const Split sp = split_for(V);
+  const int n_cand = sp.wide ? sp.grid * sp.tiles : sp.tiles;
+  const ScratchLayout L = layout_for(B, N, n_cand, scratch_bytes);
   const int64_t small_grid = static_cast<int64_t>((sp.tiles + kXcds - 1) / kXcds * kXcds) *
                              ((std::max<int64_t>(B, kLook) + 63) / 64);
   if (small_grid > 0x7FFFFFFF) return SRT_ERR_UNSUPPORTED;
@@ -771,21 +812,22 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.out_nodes = out_nodes;
   a.n_emitted = n_emitted;
   a.n_act = reinterpret_cast<int32_t*>(base);
-  a.act = reinterpret_cast<int2*>(base + L.off_act);
+  a.act = reinterpret_cast<int32_t*>(base + L.off_act);
+  a.listed = L.rows > 1 ? reinterpret_cast<int32_t*>(base + L.off_listed) : nullptr;
   a.span = reinterpret_cast<int2*>(base + L.off_span);
   a.list = reinterpret_cast<int2*>(base + L.off_list);
-  a.place = reinterpret_cast<int32_t*>(base + L.off_place);
+  a.place = L.rows > 1 ? reinterpret_cast<int32_t*>(base + L.off_place) : nullptr;
   a.cand = reinterpret_cast<unsigned long long*>(base + L.off_cand);
   a.B = B;
   a.N = N;
   a.dm = d_model;
   a.V = V;
   a.Dmax = Dmax;
-  a.L = std::min(N, kLook);
+  a.L = L.L;
   const Fill fill = fill_for(B, V, d_model, Dmax);
-  a.look = fill.look;
-  a.finish = fill.finish;
-  a.n_cand = sp.wide ? sp.grid * sp.tiles : sp.tiles;
+  a.look = std::min(fill.look, L.rows);
+  a.finish = std::min(fill.finish, L.rows);
+  a.n_cand = n_cand;
   a.units = sp.units;
   a.tiles = sp.tiles;
   a.invT = inv_temperature;
@@ -795,7 +837,7 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   int st = launch_status();
   // A walker's quota is at least look / B (see pass_rows), and a walk that
   // leaves a pass has moved that many places on in its tree.
-  const int quota = std::max(1, a.look / B);
+  const int quota = std::max(1, std::min(a.L, a.look / B));
   const int passes = std::min(Dmax + 1, (N - 1) / quota + 1);
   for (int pass = 0; pass < passes && st == SRT_OK; ++pass) {
     if (sp.wide) {

@@ -256,6 +256,46 @@ def planted_tree(rng, B, N, Dmax, V, deep):
     return {"tree_tokens": tt, "tree_parent": tp, "n_nodes": nn}
 
 
+def least_scratch(B, N, V):
+    """Bytes that passes over the walking sequences' own nodes need."""
+    up = lambda x: -(-x // 256) * 256
+    return 4096 + up(8 * B) + up(4 * B) + up(4 * B * N) + up(8 * max(B, 128) * -(-V // 128))
+
+
+@pytest.mark.parametrize("B,N,Dmax,V,d,sampled", [
+    (1, 1, 3, 1, 64, False), (300, 1, 4, 300, 64, True), (300, 2, 4, 300, 64, False), (5000, 2, 2, 40, 64, False),
+    (16, 32, 8, 3000, 128, True), (257, 16, 8, 1000, 64, True), (2, 300, 20, 5000, 64, False), (40, 20, 9, 33000, 64, True)])
+def test_smaller_scratch_makes_smaller_passes(B, N, Dmax, V, d, sampled):
+    """From the full scratch down to the least one, that of passes without
+    looking ahead: the same walks, nothing written past the buffer's end."""
+    rng = random.Random(B + N)
+    say(f"lmhead scratch sizes: B={B} N={N} Dmax={Dmax} V={V}")
+    tree = random_trees(rng, B, N, Dmax, V) if V > 1 else chain_trees(B, N, Dmax)
+    hidden, w = W.make_head(B, N, d, V, device="cuda", seed=B, kind="int", tree_tokens=tree["tree_tokens"],
+                            tree_parent=tree["tree_parent"], n_nodes=tree["n_nodes"], plant_p=0.9)
+    gumbel = torch.randint(-3, 4, (B, Dmax + 1, V), device="cuda").float() if sampled else None
+    tt, tp, nn = tree_tensors(tree)
+    full, least = srt.srt_accept_lmhead_scratch_bytes(B, N, V), least_scratch(B, N, V)
+    want = run_fused(hidden, w, gumbel, 1.0, tree, Dmax)
+    buf = torch.empty(max(full, least) + 4096, dtype=torch.uint8, device="cuda")
+    out = srt._walk_outputs(B, Dmax, "cuda")
+    p = lambda x: None if x is None else x.data_ptr()
+
+    def call(nbytes):
+        buf.fill_(0x5A)
+        return srt.lib().srt_accept_lmhead(
+            B, N, d, V, Dmax, p(hidden), p(w), p(gumbel), 1.0, p(tt), p(tp), p(nn), p(out["n_accepted"]),
+            p(out["out_tokens"]), p(out["out_nodes"]), p(out["n_emitted"]), p(buf), nbytes,
+            torch.cuda.current_stream().cuda_stream)
+
+    for nbytes in sorted({full, least, *(least + (full - least) * i // 4 // 256 * 256 for i in (1, 2, 3) if full > least)}):
+        assert call(nbytes) == srt.SRT_OK, nbytes
+        assert_same({k: v.cpu().numpy() for k, v in out.items()}, want, B)
+        assert bool((buf[nbytes:] == 0x5A).all()), nbytes
+    assert call(min(full, least) - 256) == srt.SRT_ERR_CAPACITY
+    assert call(full - 1) == srt.SRT_ERR_CAPACITY
+
+
 @pytest.mark.parametrize("V,d,split", [
     (16384, 64, "small, 64 rows"), (16385, 192, "small, 64 or 128 rows"), (32768, 320, "small, 64 or 128 rows"),
     (32769, 320, "wide"), (40001, 2112, "wide"), (65537, 1088, "wide, two tiles a workgroup")])
