@@ -102,6 +102,18 @@ def _on(stream):
     return torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext()
 
 
+def _scratch_call(fn: str, call, scratch, need: int, device, stream):
+    """call(scratch) with the caller's buffer if there is one and the library
+    takes it (it says so before anything is enqueued), else with one of
+    ``need`` bytes."""
+    st = SRT_ERR_CAPACITY if scratch is None else call(scratch)
+    if st == SRT_ERR_CAPACITY and (scratch is None or scratch.numel() < need):
+        with _on(stream):
+            scratch = torch.empty(max(need, 1), dtype=torch.uint8, device=device)
+        st = call(scratch)
+    _check(fn, st)
+
+
 def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor"):
     if t is None:
         return None
@@ -206,17 +218,16 @@ def srt_tree_attn(q, k_cache, v_cache, block_table, ctx_len, tree_parent, n_node
         raise ValueError("cache shape mismatch")
     max_pages = int(block_table.shape[1])
     need = srt_tree_attn_scratch_bytes(B, N, Hq, Hkv, d, page, max_pages)
-    with _on(stream):
-        if out is None:
+    if out is None:
+        with _on(stream):
             out = torch.empty_like(q)
-        if need and (scratch is None or scratch.numel() < need):
-            scratch = torch.empty(need, dtype=torch.uint8, device=q.device)
-    _check("srt_tree_attn", lib().srt_tree_attn(
-        B, N, Hq, Hkv, d, page, max_pages, P, _ptr(q, torch.bfloat16, "q"), _ptr(k_cache, torch.bfloat16, "k_cache"),
-        _ptr(v_cache, torch.bfloat16, "v_cache"), _ptr(block_table, torch.int32, "block_table"),
-        _ptr(ctx_len, torch.int32, "ctx_len"), _ptr(tree_parent, torch.int32, "tree_parent"),
-        _ptr(n_nodes, torch.int32, "n_nodes"), float(scale), _ptr(out, torch.bfloat16, "out"),
-        _ptr(scratch) if need else None, need, _stream(stream)))
+    args = (B, N, Hq, Hkv, d, page, max_pages, P, _ptr(q, torch.bfloat16, "q"),
+            _ptr(k_cache, torch.bfloat16, "k_cache"), _ptr(v_cache, torch.bfloat16, "v_cache"),
+            _ptr(block_table, torch.int32, "block_table"), _ptr(ctx_len, torch.int32, "ctx_len"),
+            _ptr(tree_parent, torch.int32, "tree_parent"), _ptr(n_nodes, torch.int32, "n_nodes"), float(scale),
+            _ptr(out, torch.bfloat16, "out"))
+    _scratch_call("srt_tree_attn", lambda x: lib().srt_tree_attn(*args, _ptr(x, name="scratch"), x.numel(), _stream(stream)),
+                  scratch, need, q.device, stream)
     return out
 
 
@@ -291,19 +302,18 @@ def srt_accept_lmhead(hidden, w_head, gumbel, inv_temperature: float, tree_token
         raise ValueError("tree arrays must be [B, N]")
     dev = hidden.device
     need = srt_accept_lmhead_scratch_bytes(B, N, V)
-    with _on(stream):
-        if out is None:
+    if out is None:
+        with _on(stream):
             out = _walk_outputs(B, max_depth, dev)
-        if scratch is None or scratch.numel() < need:
-            scratch = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
-    _check("srt_accept_lmhead", lib().srt_accept_lmhead(
-        B, N, dm, V, max_depth, _ptr(hidden, torch.bfloat16, "hidden"), _ptr(w_head, torch.bfloat16, "w_head"),
-        _ptr(gumbel, torch.float32, "gumbel"), float(inv_temperature),
-        _ptr(tree_tokens, torch.int32, "tree_tokens"), _ptr(tree_parent, torch.int32, "tree_parent"),
-        _ptr(n_nodes, torch.int32, "n_nodes"), _ptr(out["n_accepted"], torch.int32),
-        _ptr(out["out_tokens"], torch.int32), _ptr(out["out_nodes"], torch.int32),
-        _ptr(out.get("n_emitted"), torch.int32), _ptr(scratch, name="scratch"), scratch.numel(),
-        _stream(stream)))
+    args = (B, N, dm, V, max_depth, _ptr(hidden, torch.bfloat16, "hidden"), _ptr(w_head, torch.bfloat16, "w_head"),
+            _ptr(gumbel, torch.float32, "gumbel"), float(inv_temperature),
+            _ptr(tree_tokens, torch.int32, "tree_tokens"), _ptr(tree_parent, torch.int32, "tree_parent"),
+            _ptr(n_nodes, torch.int32, "n_nodes"), _ptr(out["n_accepted"], torch.int32),
+            _ptr(out["out_tokens"], torch.int32), _ptr(out["out_nodes"], torch.int32),
+            _ptr(out.get("n_emitted"), torch.int32))
+    _scratch_call("srt_accept_lmhead",
+                  lambda x: lib().srt_accept_lmhead(*args, _ptr(x, name="scratch"), x.numel(), _stream(stream)),
+                  scratch, need, dev, stream)
     return out
 
 

@@ -52,6 +52,27 @@ def test_workspace_bytes_host_only():
     assert b > a
 
 
+def test_binding_keeps_a_scratch_that_the_library_takes():
+    torch = pytest.importorskip("torch")
+    seen = []
+
+    def call(least):
+        def f(x):
+            seen.append(x.numel())
+            return S.SRT_OK if x.numel() >= least else S.SRT_ERR_CAPACITY
+        return f
+
+    buf = lambda n: torch.empty(n, dtype=torch.uint8)
+    for scratch, least, want in ((buf(40), 30, [40]), (buf(20), 30, [20, 50]), (None, 30, [50]), (buf(60), 30, [60])):
+        seen.clear()
+        S._scratch_call("f", call(least), scratch, 50, "cpu", None)
+        assert seen == want
+    with pytest.raises(S.SrtError):
+        S._scratch_call("f", call(99), buf(60), 50, "cpu", None)
+    with pytest.raises(S.SrtError):
+        S._scratch_call("f", lambda x: S.SRT_ERR_INVALID, buf(20), 50, "cpu", None)
+
+
 def test_scratch_bytes():
     # one split: only the work list (header + 2 int32 per item), 256-byte rounded
     one = S.srt_tree_attn_scratch_bytes(4, 8, 4, 1, 64, 16, 40)

@@ -278,4 +278,12 @@ def test_scratch_for_large_splits_only():
     assert call(small - 256) == srt.SRT_ERR_CAPACITY
     assert call(small) == srt.SRT_OK
     c.check(out, "1024-key splits")
+    # the binding hands the caller's scratch over instead of allocating another
+    out.zero_(), scratch.fill_(0x5A)
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    q, k, v, bt, ctx, par, nn = ins
+    srt.srt_tree_attn(q, k, v, bt, ctx, par, nn, c.scale, out=out, scratch=scratch)
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    assert bool((scratch != 0x5A).any())
+    c.check(out, "1024-key splits, binding")
     c.check(c.run(), "256-key splits")

@@ -292,6 +292,13 @@ def test_smaller_scratch_makes_smaller_passes(B, N, Dmax, V, d, sampled):
         assert call(nbytes) == srt.SRT_OK, nbytes
         assert_same({k: v.cpu().numpy() for k, v in out.items()}, want, B)
         assert bool((buf[nbytes:] == 0x5A).all()), nbytes
+    # the binding hands the caller's scratch over instead of allocating another
+    buf.fill_(0x5A)
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    srt.srt_accept_lmhead(hidden, w, gumbel, 1.0, tt, tp, nn, Dmax, out=out, scratch=buf[:least])
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    assert bool((buf[:least] != 0x5A).any()) and bool((buf[least:] == 0x5A).all())
+    assert_same({k: v.cpu().numpy() for k, v in out.items()}, want, B)
     assert call(min(full, least) - 256) == srt.SRT_ERR_CAPACITY
     assert call(full - 1) == srt.SRT_ERR_CAPACITY
 
