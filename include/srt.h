@@ -190,7 +190,9 @@ int srt_draft(const void* ws, int32_t B, const int32_t* prompt_ids, const int32_
  * a context can exceed one split.  A split is 8192 keys, or a smaller power
  * of two (down to 1024) when B * Hkv is small and down to 256 when the whole
  * call leaves CUs idle otherwise, chosen from B, N, Hq / Hkv, Hkv, page and
- * max_pages alone (the results do not depend on it beyond fp32 rounding).  A
+ * max_pages alone, not from the contexts: a block table no wider than they
+ * need serves small batches best (the results do not depend on it beyond fp32
+ * rounding).  A
  * scratch with room for the 1024-key splits only is taken too and makes them.
  * Owned by the caller; contents are overwritten; calls that share a
  * scratch buffer must not overlap.

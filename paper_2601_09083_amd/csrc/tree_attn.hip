@@ -36,14 +36,17 @@
 //     its scores bit by bit.
 //   * Long contexts are split into chunks of keys so the grid has enough
 //     independent work (8192 keys, or a smaller power of two down to 1024
-//     when the batch has few sequences and KV heads); each split writes
-//     unnormalised partial output plus (max, sum) and a small combine
-//     kernel merges them.  A sequence that fits in one split writes bf16
-//     output directly.
+//     when the batch has few sequences and KV heads, 512 or 256 when every
+//     item that the block table has room for gets a CU of its own); each
+//     split writes unnormalised partial output plus (max, sum) and a small
+//     combine kernel merges them.  A sequence that fits in one split writes
+//     bf16 output directly.
 //   * Work is scheduled by a small plan kernel that lists the (sequence, KV
 //     head, split, row block) items that have work, longest first; one
 //     persistent workgroup per CU takes items from an atomic counter, so no
-//     CU idles on empty grid slots and long items do not form a tail.
+//     CU idles on empty grid slots and long items do not form a tail.  Where
+//     the block table has room for no more items than there are CUs, each
+//     has a workgroup and there is no plan kernel.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -100,9 +103,11 @@ struct AttnArgs {
 // plan[2] = number of sequences whose context spans several splits; entry e of
 // them at plan[a.combine_at + 2 e] = sequence | splits << 16 (the host rejects
 // B > 65535 and more than 4095 splits) and [.. + 1] = its query rows per KV
-// head.  (Listing every 8-row group of them here took one thread per sequence
-// 20 to 40 us of stores; the combine kernel works the group out instead.)
+// head; plan[3] = 8-row groups of the widest of them.  (Listing every group
+// here took one thread per sequence 20 to 40 us of stores; the combine kernel
+// works the group out instead.)
 constexpr int kPlanHeader = 64;
+constexpr int kCombineRows = 8;
 constexpr int kPlanKeys = (kChunk / kTile) * kWaves;  // (tiles, waves) classes
 
 __device__ inline int plan_key(int tiles, int waves) {  // 0 = most expensive
@@ -581,10 +586,10 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
   __shared__ int32_t cnt[kPlanKeys], off[kPlanKeys];
   __shared__ int32_t wsum[1024 / SRT_WAVE];
   __shared__ int32_t s_total[1024], s_rows[1024], s_pos[2][1024];
-  __shared__ int32_t ncomb;
+  __shared__ int32_t ncomb, widest;
   const int tid = threadIdx.x;
   for (int k = tid; k < kPlanKeys; k += 1024) cnt[k] = 0;
-  if (tid == 0) ncomb = 0;
+  if (tid == 0) ncomb = widest = 0;
   const int cshift = 31 - __clz(a.chunk);  // chunk is a power of two
   // Visits the item classes of a sequence: f(key, splits).
   auto classes = [&](int total, int rows, auto&& f) {
@@ -634,6 +639,7 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
   const int per_seq_log2 = group > 1 ? __clz(group - 1) - 22 : 10;  // 1024 / (group rounded up to a power of two)
   for (int b0 = 0; b0 < a.B; b0 += 1024) {
     if (a.B > 1024 && b0 + tid < a.B) si = seq_info(a, b0 + tid);
+    int split_rows = 0;
     if (b0 + tid < a.B) {
       const int rows = si.n * a.G;
       s_total[tid] = si.total;
@@ -641,10 +647,16 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
       classes(si.total, rows, [&](int c, int key, int ns) {
         s_pos[c][tid] = atomicAdd(&off[key], ns * a.Hkv * row_blocks(rows));
       });
-      if (si.total > a.chunk)
+      if (si.total > a.chunk) {
         *reinterpret_cast<int2*>(a.plan + a.combine_at + 2 * atomicAdd(&ncomb, 1)) =
             make_int2((b0 + tid) | ((si.total + a.chunk - 1) >> cshift) << 16, rows);
+        split_rows = rows;
+      }
     }
+    // (one atomic a wave: 64 on one word take 1.5 us)
+#pragma unroll
+    for (int d = SRT_WAVE / 2; d >= 1; d >>= 1) split_rows = max(split_rows, __shfl_xor(split_rows, d, SRT_WAVE));
+    if (lane == 0 && split_rows > 0) atomicMax(&widest, split_rows);
     __syncthreads();
     const int i = tid >> per_seq_log2;
     if (b0 + i < a.B && i < group) {
@@ -658,7 +670,10 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
     }
     if (b0 + 1024 < a.B) __syncthreads();
   }
-  if (tid == 0) a.plan[2] = ncomb;
+  if (tid == 0) {
+    a.plan[2] = ncomb;
+    a.plan[3] = (widest + kCombineRows - 1) / kCombineRows;
+  }
 }
 
 // Merges the split partials of sequences that needed more than one split:
@@ -671,11 +686,14 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
 // them in flight: 26 -> 20 us for 256 sequences of up to 32k with trees of 1
 // to 64 nodes, 44 -> 27 with full ones, 26 -> 20 for 8 of 16k-32k with
 // 64-256 nodes (four workgroups per CU, and a list entry for every group).
-constexpr int kCombineRows = 8;
+// The groups of the widest split tree set the stride from one (sequence, KV head)
+// to the next, one more where they are even, so that the first groups do not
+// meet in every 2^n-th workgroup (512 one-node sequences of 8500 keys in a batch
+// with room for 256 nodes: 1860 us a call with the stride of the room, 1610 so).
 template <int D, bool kDirect>
 __global__ __launch_bounds__(kCombineRows * D / 4) void tree_attn_combine_kernel(AttnArgs a) {
   constexpr int Q = D / 4;
-  const int per_head = (a.N * a.G + kCombineRows - 1) / kCombineRows;  // groups of the widest tree
+  const int per_head = kDirect ? (a.N * a.G + kCombineRows - 1) / kCombineRows : a.plan[3] | 1;
   const int n_units = (kDirect ? a.B : a.plan[2]) * a.Hkv * per_head;
   const int RBR = a.RB * kRowsPerBlock;
   const int q = threadIdx.x % Q;
@@ -732,9 +750,14 @@ __global__ __launch_bounds__(kCombineRows * D / 4) void tree_attn_combine_kernel
 // sequences, 64-node trees, 2048: 45.7 against 45.4 (no CU left).  Contexts of
 // up to 768 keys (1024 with 512-key splits) gain little over the combine's cost
 // (16 sequences of 32 heads, 8 KV heads, 64 nodes, capacity 768: 34 us with
-// 512-key splits, 30 with one; 4 of 4 heads, d 64, 8 nodes: 13.7 and 13.1), and past 32 splits the combine's own chain is the longer one
-// (one sequence, 16k keys: 39 us with 63 splits, 25 with 32 or 16).  small =
-// false: without these, for a scratch that has no room for their partials.
+// 512-key splits, 30 with one; 4 of 4 heads, d 64, 8 nodes: 13.7 and 13.1), and
+// past 32 splits the combine's own chain is the longer one (one sequence, 16k
+// keys: 39 us with 63 splits, 25 with 32 or 16).  The rule goes by the block
+// table's width, as the host does not know the contexts: a batch in a table as
+// wide as a 32k limit takes none of these (4 sequences of 700 keys, 8 nodes:
+// 18 us in a table for 8192 keys, 26 before these rules; 1 of 300: 14 us in one for
+// 32768, 17 before, as only the plan kernel goes).  small = false: without
+// these, for a scratch that has no room for their partials.
 int chunk_for(int32_t B, int32_t Hkv, int64_t RB, int32_t page, int32_t max_pages, bool small) {
   const int64_t cap = static_cast<int64_t>(page) * max_pages;
   int chunk = kChunk;

@@ -213,7 +213,8 @@ def test_dominant_keys_late_in_a_split(factor):
 
 @pytest.mark.parametrize("B,N,hkv,G,lo,hi", [
     (1, 5, 1, 3, 900, 1100),      # one sequence, at the edge of one split
-    (3, 256, 2, 5, 1000, 3000),   # 1024 threads shared by 3 sequences; 5 row blocks each
+    (3, 256, 2, 5, 1000, 3000),   # a CU for each of 210 items; 5 row blocks each
+    (3, 256, 4, 7, 1000, 3000),   # 336 items: the plan's 1024 threads shared by 3 sequences
     (65, 3, 2, 1, 1, 2300),       # 128 places for 65 sequences, one to three splits
     (1030, 2, 1, 2, 1, 200),      # more sequences than the plan takes at a time
     (32, 3, 2, 1, 900, 1000),     # a CU for each of 256 items, 256-key splits
@@ -256,6 +257,35 @@ def test_work_list_covers_every_sequence(B, N, hkv, G, lo, hi):
         err = (out[b, :m].double() - ref).abs()
         assert bool((err <= 1e-2 + 2e-2 * ref.abs()).all()), (b, float(err.max()))
         assert bool((out[b, m:] == 7.0).all()), b  # rows past the tree are not written
+
+
+@pytest.mark.parametrize("wide,ctx_lo,ctx_hi", [
+    ("none", 8193, 9000),     # one-node trees only, all of two splits
+    ("one", 8100, 9000),      # one full tree among them
+    ("unsplit", 8100, 9000),  # full trees where one split is enough, one-node trees elsewhere
+    ("all", 8000, 8100),      # no sequence of two splits, though the block table has room
+])
+def test_combine_goes_by_the_split_trees(wide, ctx_lo, ctx_hi):
+    """Room for 256 nodes, 70 sequences of 8192-key splits: the combine's
+    groups follow the widest tree that is split."""
+    B, N, page = 70, 256, 16
+    rng = np.random.default_rng(ctx_lo)
+    ctx = rng.integers(ctx_lo, ctx_hi, size=B)
+    ctx[:2] = ctx_lo, ctx_hi - 1
+    n = np.ones(B, int)
+    if wide == "one":
+        n[1] = N
+    elif wide == "unsplit":
+        n[ctx < 8192 - N] = N
+        n[2], ctx[2] = N, 1000
+    elif wide == "all":
+        n[:] = rng.integers(80, 92, size=B)  # up to 8099 + 91 = 8190 keys
+    say(f"attn: combine of narrow trees in wide rows ({wide})")
+    c = Case(ctx_lo, B, N, 4, 2, 64, ctx, n_nodes=n)
+    bt = torch.full((B, 9300 // page), -1, dtype=torch.int32, device="cuda")
+    bt[:, :c.block_table.shape[1]] = c.block_table[:, :bt.shape[1]]
+    c.block_table = bt
+    c.check(c.run(), f"narrow trees, {wide}")
 
 
 def test_scratch_for_large_splits_only():
