@@ -308,8 +308,9 @@ __global__ __launch_bounds__(kWalkWaves * SRT_WAVE) void accept_walk_kernel(Acce
 // launches between the steps and nothing exchanged between workgroups.  A step
 // is bound by its own chain (row loads, the reduction, one barrier, the child
 // search in LDS), about 2 us, where a step of the level kernels is a launch
-// and their longer chain, 4 to 7 us; what a single CU streams (about 100 GB/s)
-// sets the rule below.  Every wave merges the waves' candidates and looks for
+// and their longer chain, 4 to 7 us; what a single workgroup streams (about
+// 42 GB/s: 12288 entries more and their noise take 2.3 us more a step) sets the
+// rule above.  Every wave merges the waves' candidates and looks for
 // the child by itself, so a step needs one barrier.
 template <bool kNoise>
 __global__ __launch_bounds__(1024) void accept_short_kernel(AcceptArgs a) {

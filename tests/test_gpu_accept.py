@@ -78,7 +78,8 @@ def test_walk_exact(V, sampled, inv_t, boost):
 @pytest.mark.parametrize("V,off_l,off_g", [(8192, 1, 3), (152064, 0, 1), (4096, 2, 0)])
 def test_walk_exact_misaligned_rows(V, off_l, off_g):
     # V a multiple of 4 but logits / noise passed as views 1-3 floats into a
-    # larger buffer: the rows are not 16-byte aligned, so the 4-byte path runs
+    # larger buffer: the rows' 16-byte loads start at any multiple of 4 bytes
+    # (V 8192 and 4096: one workgroup a walk; 152064: the level kernels)
     rng = random.Random(V + off_l)
     B, N, Dmax = 40, 32, 8
     say(f"accept: misaligned rows V={V} logits +{off_l} noise +{off_g} floats")
@@ -203,12 +204,45 @@ def test_many_deep_walks():
         assert (got["n_accepted"] >= 3).all()
 
 
-@pytest.mark.parametrize("Dmax,sampled", [(63, False), (63, True), (62, True)])
-def test_deepest_walk(Dmax, sampled):
+def level_kernels(V, sampled):
+    """Rows longer than one workgroup walks (40960 entries, the noise's included)."""
+    return V * (2 if sampled else 1) > 40960
+
+
+@pytest.mark.parametrize("sampled,V", [(False, 40964), (True, 20483)])
+def test_many_deep_walks_of_long_rows(sampled, V):
+    # as above on the level kernels: 4000 walkers in the lists of the first four
+    # levels, fewer at each of the next
+    B, N, Dmax = 4000, 6, 5
+    assert level_kernels(V, sampled)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    tt = torch.tensor([3, 5, 7, 9, 11, V - 1], dtype=torch.int32).repeat(B, 1)
+    rng = np.random.default_rng(V)
+    stop = rng.integers(3, N, B)
+    logits = torch.randn((B, N, V), generator=g, device="cuda")
+    for u in range(N - 1):
+        on = torch.as_tensor(np.nonzero(stop != u)[0], device="cuda")
+        logits[on, u, int(tt[0, u + 1])] = 20.0
+    gumbel = torch.rand((B, Dmax + 1, V), generator=g, device="cuda") if sampled else None
+    tree = {"tree_tokens": tt.numpy(), "tree_parent": np.tile(np.arange(-1, N - 1, dtype=np.int32), (B, 1)),
+            "n_nodes": np.full(B, N, np.int32)}
+    say(f"accept: {B} deep walks on the level kernels, V={V} sampled={sampled}")
+    got = run(tree, logits, gumbel, 1.0, Dmax)
+    assert (got["n_accepted"] == stop).all()  # by construction; the tokens by the oracle
+    seqs = sorted(rng.choice(B, 400, replace=False))
+    want = oracle_accept_rows(logits, gumbel, 1.0, tree, seqs, Dmax)
+    for b in seqs:
+        assert_accept_equal(got, b, want[b], Dmax)
+
+
+@pytest.mark.parametrize("Dmax,sampled,V", [(63, False, 4096), (63, True, 4096), (62, True, 4096),
+                                            (63, False, 40964), (63, True, 20483), (62, True, 50001)])
+def test_deepest_walk(Dmax, sampled, V):
     # a 64-node chain whose logits lead down it: the walk takes every level up
-    # to the depth cap (all 64 levels when Dmax = 63), the level buffers
-    # alternating between their two halves throughout
-    B, N, V = 3, 64, 4096
+    # to the depth cap (all 64 levels when Dmax = 63); in the rows of more than
+    # 4096 entries the level buffers alternate between their two halves throughout
+    B, N = 3, 64
+    assert level_kernels(V, sampled) == (V > 4096)
     tt = np.zeros((B, N), np.int32)
     for b in range(B):
         tt[b] = (np.arange(N) * 37 + 11 * b) % V

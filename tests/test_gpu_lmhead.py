@@ -11,6 +11,9 @@ fused with the acceptance walk) against the oracle.
 * Real-valued bf16 inputs: every step of the GPU walk must be valid against
   the oracle's fp64 scores within the fp32 summation bound, and nearly all
   walks must equal the oracle's.
+* Heads and passes on both sides of every rule that picks their tiles, rows
+  and lists (128- and 256-row tiles, one or two a workgroup, 64, 128 and 256
+  rows and more sequences than that, scratches below the full size).
 * The 7B-shaped head (V = 152064, d_model = 3584, 256 sequences, N = 64,
   Dmax = 12): all sequences against srt_accept on the materialised logits,
   sampled sequences against the oracle.
@@ -369,9 +372,9 @@ def test_rows_of_a_pass(B, N, Dmax, V, d, sampled):
     (1, 64, 20, 4096, 64, 20, True),      # one sequence: its whole tree in one pass
     (2, 300, 40, 300, 128, 40, False),    # trees longer than a pass's list
     (1, 1100, 63, 257, 64, 63, False),    # more nodes than the staged parents
-    (3, 200, 12, 17, 320, 12, True),      # units of 16 head rows: 2 of them, the last with one row
-    (31, 40, 10, 4113, 192, 10, False),   # uneven quotas, 258 units over 256 workgroups
-    (129, 24, 8, 65553, 64, 8, True),     # 129 walkers: 256-row layout; two tiles a workgroup
+    (3, 200, 12, 17, 320, 12, True),      # fewer head rows than a tile has
+    (31, 40, 10, 4113, 192, 10, False),   # uneven quotas, a last tile of 17 head rows
+    (129, 24, 8, 65553, 64, 8, True),     # 129 walkers: wide tiles of 256 rows, two a workgroup
     (256, 8, 6, 1000, 128, 6, False),     # exactly as many walkers as rows
     (257, 16, 6, 1000, 448, 6, True),     # more walkers than rows: one node each
 ])

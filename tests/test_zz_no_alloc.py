@@ -3,10 +3,12 @@ scratch array, for callers that cannot allocate) against srt_accept (caller
 scratch) through the C ABI: identical outputs, bit for bit, on consecutive
 calls of decreasing size -- the largest batch the array holds, then smaller
 ones with other tree sizes, vocabularies (one not a multiple of 4) and depth
-caps, sampled and greedy -- so that the array's contents from an earlier,
-larger call cannot leak into a later one; and the same walk captured in a
-HIP graph, replayed three times with other no-alloc calls in between (each
-overwriting the shared array), every replay equal to the eager result."""
+caps, sampled and greedy -- once with rows that one workgroup walks (the array
+is not used) and once with longer ones, where the array's contents from an
+earlier, larger call must not leak into a later one; and the same walk
+captured in a HIP graph, replayed three times with other no-alloc calls in
+between (with the longer rows each overwriting the shared array), every replay
+equal to the eager result."""
 import numpy as np
 import pytest
 import torch
@@ -45,13 +47,22 @@ def outputs(B, Dmax):
             "n_emitted": torch.full((B,), -7, dtype=torch.int32, device="cuda")}
 
 
-def test_noalloc_matches_scratch_entry_point():
-    cases = [  # (seed, B, N, V, Dmax, sampled, inv_T)
-        (1, srt.SRT_ACCEPT_NOALLOC_MAX_BATCH, 8, 1024, 4, True, 1.0),
-        (2, 1500, 64, 6000, 10, True, 0.8),
-        (3, 200, 16, 3001, 5, False, 1.0),
-        (4, 37, 256, 2048, 63, True, 1.3),
-    ]
+SHORT = [  # (seed, B, N, V, Dmax, sampled, inv_T)
+    (1, srt.SRT_ACCEPT_NOALLOC_MAX_BATCH, 8, 1024, 4, True, 1.0),
+    (2, 1500, 64, 6000, 10, True, 0.8),
+    (3, 200, 16, 3001, 5, False, 1.0),
+    (4, 37, 256, 2048, 63, True, 1.3),
+]
+LONG = [  # more than 40960 entries of a row and its noise: the walk uses the array
+    (5, srt.SRT_ACCEPT_NOALLOC_MAX_BATCH, 4, 20484, 3, True, 1.0),
+    (6, 700, 16, 24001, 10, True, 0.8),
+    (7, 200, 16, 41003, 5, False, 1.0),
+    (8, 37, 64, 20500, 63, True, 1.3),
+]
+
+
+@pytest.mark.parametrize("cases", [SHORT, LONG], ids=["short-rows", "long-rows"])
+def test_noalloc_matches_scratch_entry_point(cases):
     for seed, B, N, V, Dmax, sampled, inv_t in cases:
         say(f"no-alloc accept: B={B} N={N} V={V} Dmax={Dmax} sampled={sampled}")
         logits, gumbel, tt, tp, nn = problem(seed, B, N, V, Dmax, sampled)
@@ -65,8 +76,9 @@ def test_noalloc_matches_scratch_entry_point():
         say(f"  equal; emitted per sequence {emitted.mean():.2f}, deepest {emitted.max()}")
 
 
-def test_noalloc_under_graph_capture():
-    B, N, V, Dmax = 300, 32, 4096, 8
+@pytest.mark.parametrize("V,other_V", [(4096, 2000), (20484, 50000)], ids=["short-rows", "long-rows"])
+def test_noalloc_under_graph_capture(V, other_V):
+    B, N, Dmax = 300, 32, 8
     logits, gumbel, tt, tp, nn = problem(11, B, N, V, Dmax, True)
     want = srt.srt_accept(logits, gumbel, 1.0, tt, tp, nn, Dmax)
     out = outputs(B, Dmax)
@@ -81,7 +93,7 @@ def test_noalloc_under_graph_capture():
     with torch.cuda.graph(g):
         srt.srt_accept_noalloc(logits, gumbel, 1.0, tt, tp, nn, Dmax, out=out)
     torch.cuda.synchronize()
-    o_l, o_g, o_tt, o_tp, o_nn = problem(12, 64, 16, 2000, 5, False)
+    o_l, o_g, o_tt, o_tp, o_nn = problem(12, 64, 16, other_V, 5, False)
     for r in range(3):
         for v in out.values():
             v.fill_(-7)
