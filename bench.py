@@ -313,45 +313,6 @@ def full_tree_attention(st, cfg, n, calls: int = 10):
             "algorithmic_bytes": nbytes, "algorithmic_flops": flops}
 
 
-FINISH_ROWS = 128  # srt_accept_lmhead finishes the walks in one pass at or below this many subtree nodes
-
-
-def head_passes(tree, out_nodes, emitted, Dmax):
-    """Rows of each product pass srt_accept_lmhead made: level l multiplies
-    the current nodes of the sequences still walking, unless the subtrees of
-    those nodes (down to depth Dmax) hold at most FINISH_ROWS nodes, in which
-    case that one pass covers them all and the walks end there.  Rebuilt
-    from the trees and the returned walks (host bookkeeping)."""
-    tp, nn = tree["tree_parent"], tree["n_nodes"]
-    B, N = tp.shape
-    depth = np.full((B, N), -1, dtype=np.int64)
-    depth[:, 0] = 0
-    for c in range(1, N):
-        p = tp[:, c]
-        ok = (p >= 0) & (p < c) & (c < nn)
-        depth[ok, c] = depth[ok, p[ok]] + 1
-
-    def subtree(b, u):
-        n, cnt = int(nn[b]), 0
-        for c in range(u, n):
-            x = c
-            while x > u:
-                x = int(tp[b, x])
-            cnt += int(x == u and 0 <= depth[b, c] <= Dmax)
-        return cnt
-
-    passes = []
-    for l in range(int(emitted.max())):
-        seqs = np.nonzero(emitted > l)[0]
-        cur = [0 if l == 0 else int(out_nodes[b, l - 1]) for b in seqs]
-        total = sum(subtree(int(b), u) for b, u in zip(seqs, cur))
-        if total <= FINISH_ROWS:
-            passes.append(total)
-            break
-        passes.append(len(seqs))
-    return passes
-
-
 MAX_ROWS = 256  # of a pass of srt_accept_lmhead, beyond the walking sequences' own
 
 

@@ -100,21 +100,6 @@ def test_counter_traffic_ignores_a_stale_kernel(tmp_path, monkeypatch):
     assert bench.counter_traffic("tiny") == 5.0
 
 
-def test_head_passes_per_level_then_one_finishing_pass():
-    # a 200-node chain walked 4 steps deep under Dmax = 130: the subtrees of
-    # the current nodes hold 131, 130, 129 nodes (one row per pass), then 128,
-    # which one finishing pass covers; a second sequence stops after 1 step
-    N, Dmax = 200, 130
-    tp = np.stack([np.arange(-1, N - 1), np.arange(-1, N - 1)]).astype(np.int32)
-    tree = {"tree_parent": tp, "n_nodes": np.array([N, 3], np.int32)}
-    out_nodes = np.full((2, Dmax + 1), -1, np.int32)
-    out_nodes[0, :6] = np.arange(1, 7)
-    emitted = np.array([7, 1])
-    # level 0: both walkers at the root; the first's subtree alone is 131
-    assert bench.head_passes(tree, out_nodes, emitted, Dmax) == [2, 1, 1, 128]
-    assert bench.FINISH_ROWS == 128
-
-
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=120)
