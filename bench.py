@@ -316,15 +316,13 @@ def full_tree_attention(st, cfg, n, calls: int = 10):
 MAX_ROWS = 256  # of a pass of srt_accept_lmhead, beyond the walking sequences' own
 
 
-def pass_fill(B, V, d_model, Dmax):
-    """(rows that srt_accept_lmhead fills a pass up to, nodes up to which a
-    pass takes all that the walks can still reach)."""
-    brief = Dmax <= 2
-    return (64 if brief or (24 < B <= 96 and V >= 24000) else MAX_ROWS,
-            128 if brief and d_model < 1024 else MAX_ROWS)
+def pass_fill(B, V, Dmax):
+    """Rows that srt_accept_lmhead fills a pass up to (MAX_ROWS if these are
+    all the nodes that the walks can still reach)."""
+    return 64 if Dmax <= 2 or (24 < B <= 96 and V >= 24000) else MAX_ROWS
 
 
-def look_passes(tree, out_nodes, emitted, Dmax, V, d_model):
+def look_passes(tree, out_nodes, emitted, Dmax, V):
     """Rows of each product pass srt_accept_lmhead makes: every sequence still
     walking brings the first q nodes (in tree order, depth at most Dmax) of its
     current node's subtree, q the largest number for which the rows fit
@@ -333,7 +331,7 @@ def look_passes(tree, out_nodes, emitted, Dmax, V, d_model):
     goes on until it leaves those nodes.  Rebuilt from the trees and the
     returned walks (host bookkeeping)."""
     tp, nn = tree["tree_parent"], tree["n_nodes"]
-    fill, finish = pass_fill(tp.shape[0], V, d_model, Dmax)
+    fill = pass_fill(tp.shape[0], V, Dmax)
     cur = {b: (0, 0) for b in range(tp.shape[0])}  # sequence -> (node, depth)
     passes = []
     while cur:
@@ -347,7 +345,7 @@ def look_passes(tree, out_nodes, emitted, Dmax, V, d_model):
             lists[b] = list(depth)[:MAX_ROWS]
         size = {b: 1 for b in cur}
         if len(cur) <= MAX_ROWS:
-            rows = MAX_ROWS if sum(len(x) for x in lists.values()) <= finish else max(fill, len(cur))
+            rows = MAX_ROWS if sum(len(x) for x in lists.values()) <= MAX_ROWS else max(fill, len(cur))
             q = 1
             while q < MAX_ROWS and sum(min(len(x), q + 1) for x in lists.values()) <= rows:
                 q += 1
@@ -404,7 +402,7 @@ def fused_head(st, cfg, calls: int, unfused: bool):
     emitted = out["n_emitted"].cpu().numpy().astype(np.int64)
     levels = int(emitted.max())
     walkers = [int((emitted > l).sum()) for l in range(levels)]  # sequences walking at level l
-    passes = look_passes(tree, out["out_nodes"].cpu().numpy(), emitted, cfg.max_depth, V, dm)
+    passes = look_passes(tree, out["out_nodes"].cpu().numpy(), emitted, cfg.max_depth, V)
     row_bytes = dm * 2 + (V * 4 if st.gumbel is not None else 0)  # hidden row + noise row
     nbytes = sum(V * dm * 2 + rows * row_bytes for rows in passes)  # the head once per pass
     flops = sum(2.0 * rows * dm * V for rows in passes)

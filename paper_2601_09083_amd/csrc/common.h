@@ -191,6 +191,19 @@ __device__ inline T shfl_xor(T v, int m) {
   return __shfl_xor(v, m, SRT_WAVE);
 }
 
+// Sum over the wave in every lane, by DPP adds (a few cycles each, where a
+// shuffle goes through the LDS crossbar): within rows of 16 lanes, then lane 15
+// of a row into the next one, then lane 31 into the upper half.
+__device__ inline int wave_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return __builtin_amdgcn_readlane(x, SRT_WAVE - 1);
+}
+
 __device__ inline uint64_t shfl_xor_u64(uint64_t v, int m) {
   const uint32_t lo = __shfl_xor(static_cast<uint32_t>(v), m, SRT_WAVE);
   const uint32_t hi = __shfl_xor(static_cast<uint32_t>(v >> 32), m, SRT_WAVE);

@@ -12,7 +12,7 @@
 //
 // GPU design.  The batch advances in passes; a pass reads the head once.
 //   * Rows of a pass: every sequence still walking brings its current node
-//     and, as long as the pass has room (see Fill), the next nodes of that
+//     and, as long as the pass has room (look_for), the next nodes of that
 //     node's subtree in tree order, the same number for everybody (draft
 //     rank order: likely descendants first).  Each of these rows may spare
 //     the walk a pass of its own.
@@ -76,7 +76,7 @@ struct HeadArgs {
   int32_t* place;           // [B, N] place of a node in its list, or null (L = 1)
   unsigned long long* cand; // [max(B, kLook), n_cand] packed candidates of the pass
   int B, N, L, dm, V, Dmax, n_cand;
-  int look, finish;         // see Fill
+  int look, finish;         // rows that a pass is filled up to; nodes that make it the last
   int units, tiles;         // see Split
   float invT;
 };
@@ -91,17 +91,16 @@ struct Split {
 };
 
 // The line lies where the small tiles need more than one round of the CUs.
-// Small and wide tiles, us: V 32768, d 1024, 256 sequences of 32 nodes, Dmax 8
-// 210 and 224, 8 of 32, Dmax 2 31 and 36 (d 2048, 256 of 64, Dmax 1 104 and 120);
-// V 36000, the same 264 and 235, 39 and 37 (d 2560 433 and 392, 64 and 58);
-// V 65536, d 512 (64 MB) 264 and 200.  The head's bytes make no difference: what
-// decides is how many CUs have a tile, and how full theirs are.
+// Small and wide tiles, us, d 1536: V 32768, 256 sequences of 32 nodes, Dmax 8 222
+// and 256, of 64, Dmax 1 82 and 97, 8 of 32, Dmax 8 42 and 46; V 36000, the same 297
+// and 269, 110 and 102, 55 and 49; V 65536, d 512 (64 MB) 228 and 187, 83 and 77, 43
+// and 38.  The head's bytes make no difference: what decides is how many CUs
+// have a tile, and how full theirs are.
 constexpr int kSmallTiles = kGrid;
 // Passes of more than 64 rows over small heads: workgroups of 128 rows read the
-// head half as often, but up to here those of 64 finish 256 rows in one round of
-// two a CU (us with 64 and with 128 rows, d 4096, 256 sequences of 64 nodes, Dmax
-// 1: V 8192 83 and 108, 16384 105 and 113, 18432 145 and 134, 32768 194 and 167; d
-// 512: 16384 46 and 53, 18432 62 and 59).
+// head half as often, but up to here those of 64 are done with 256 rows in one
+// round of two a CU (us with 64 and with 128 rows, d 3072, 256 sequences of 64
+// nodes, Dmax 1: V 8192 66 and 87, 16384 81 and 89, 24576 114 and 109).
 constexpr int kFlatTiles = kGrid / 2;
 
 inline Split split_for(int64_t V) {
@@ -119,30 +118,22 @@ inline Split split_for(int64_t V) {
   return s;
 }
 
-// Rows that passes are filled up to (look), and nodes up to which a pass takes
-// every one the walks can still reach, so that it is the last (finish; at most
-// kLook).
-// finish: kLook, as such a pass costs less than two smaller ones (us; V 151936,
-// d 1536, 32 sequences of 64 nodes, Dmax 6, greedy: 434 without, 300 with it; 8 of
-// 32, Dmax 2: 209 and 134); 128 where two passes end most walks and the rows'
-// noise (4 V bytes each, against 2 d_model V for the head) weighs most (d 896,
-// 16 sequences of 32, Dmax 2, sampled: 138 with 128, 150 with kLook; d 2048:
-// 272 and 196).
-// look: kLook, as up to there rows cost less than the passes that they spare
-// (256 sequences, Dmax 8, d 1536: 948 us with 64, 853 with 256; 16 sequences of
-// 32, Dmax 8, d 3584: 380 and 360).  64 where they do not: for walks that two or
-// three passes end anyhow (32 sequences, Dmax 2, sampled, d 2048: 334 with 64, 357
-// with 128), and for 25 to 96 sequences, which have a row or two each then, most of
-// them of walks that end at the root (64 sequences of 32, Dmax 8, sampled: d 896
-// 322 and 396, d 1536 452 and 542, d 3584 820 and 967); heads under 24000 rows are
-// too small for the rows to weigh (V 4096, d 1024: 89 and 86).
-struct Fill {
-  int look, finish;
-};
-
-inline Fill fill_for(int B, int V, int d_model, int Dmax) {
-  const bool brief = Dmax <= 2;
-  return {brief || (B > 24 && B <= 96 && V >= 24000) ? 64 : kLook, brief && d_model < 1024 ? 128 : kLook};
+// Rows that passes are filled up to, unless the nodes that the walks can still
+// reach are kLook or fewer: a pass then takes them all and is the last, as it
+// costs less than two smaller ones (us; V 151936, d 1536, 32 sequences of 64
+// nodes, Dmax 6, greedy: 434 without, 300 with it; 8 of 64, Dmax 1: 200 and 162;
+// up to 7% more than two passes for narrow heads, whose rows' noise weighs most:
+// d 896, 16 of 32, Dmax 2, sampled: 133 and 140).
+// kLook, as up to there rows cost less than the passes that they spare (256
+// sequences, Dmax 8, d 1536: 948 us with 64, 853 with 256; 16 of 32, Dmax 8, d
+// 3584: 380 and 360).  64 where they do not: for walks that two or three passes
+// end anyhow (32 sequences of 64, Dmax 2, sampled, d 1536: 224 with 64, 245 with
+// 128, 295 with 256), and for 25 to 96 sequences, which have a row or two each
+// then, most of them of walks that end at the root (64 sequences of 32, Dmax 8,
+// sampled: d 896 322 and 396, d 1536 452 and 542, d 3584 820 and 967); heads under
+// 24000 rows are too small for the rows to weigh (V 4096, d 1024: 89 and 86).
+inline int look_for(int B, int V, int Dmax) {
+  return Dmax <= 2 || (B > 24 && B <= 96 && V >= 24000) ? 64 : kLook;
 }
 
 // Scratch layout: counters, lists, node places, candidates of passes of up to
@@ -290,61 +281,77 @@ struct PassShared {
   int base[kLook];                               // first row of each walker
   alignas(16) int cnt[kLook];                    // its listed nodes
   int seq[kLook];                                // its sequence
-  int rows;                                      // rows at the quota
 };
 
-// Rows of the pass: fills s.base (W <= kLook walkers) and returns their
+// A pass of this many walkers or more brings their current nodes only: rows are
+// neither left to fill, nor can the nodes be few enough to end every walk
+// (unless there are no others).
+__device__ inline int lone_from(const HeadArgs& a) { return max(a.look, a.finish); }
+
+// A thread's walker of the pass: its sequence and listed nodes (loaded beside
+// the number of walkers, unused past it).
+__device__ inline int2 load_walker(const HeadArgs& a, int pass) {
+  const int tid = threadIdx.x;
+  if (tid >= kLook || tid >= a.B) return make_int2(0, 0);
+  const int64_t at = static_cast<int64_t>(pass & 1) * a.B + tid;
+  return make_int2(a.act[at], a.listed ? a.listed[at] : 1);
+}
+
+// Rows of the pass: fills s.base (for fewer than lone_from walkers) and returns their
 // number.  Where all listed nodes are few they are the pass.  Else each walker
 // takes the first min(q, listed) nodes of its list, q the largest number for
 // which the rows fit, and the first walkers with more listed one more each
-// while rows are left.  Every workgroup works this out
-// for itself; the first records it for the walk kernel.
+// while rows are left.  Every workgroup works this out for itself (every wave
+// the number, from the counts in its lanes); the first records it for the walk
+// kernel.  A thread for each q, summing over the counts in LDS, took 12 us for
+// 256 walkers: V 32000, d 1024, a pass over 256 sequences' roots 44 us, 32 so.
 template <typename Shared>
-__device__ inline int pass_rows(const HeadArgs& a, int pass, int W, Shared& s) {
+__device__ inline int pass_rows(const HeadArgs& a, int2 walker, int W, Shared& s) {
   static_assert(kLook == 256 && kLook % SRT_WAVE == 0, "a thread per walker (workgroups have 256 or more)");
   const int tid = threadIdx.x, lane = tid % SRT_WAVE;
   if (tid < kLook) {
-    const int64_t at = static_cast<int64_t>(pass & 1) * a.B + tid;
-    s.seq[tid] = tid < W ? min(max(a.act[at], 0), a.B - 1) : 0;
-    s.cnt[tid] = tid >= W ? 0 : a.listed ? min(max(a.listed[at], 1), a.L) : 1;
+    s.seq[tid] = min(max(walker.x, 0), a.B - 1);
+    s.cnt[tid] = tid < W ? min(max(walker.y, 1), a.L) : 0;
   }
   __syncthreads();
-  // thread t tries the quota t + 1 (the rows grow with it; 1 always fits)
-  int v = 0, all = 0;
-  for (int i = 0; i < W; i += 4) {  // (entries past W are 0)
-    const int4 c4 = *reinterpret_cast<const int4*>(&s.cnt[i]);
-    v += min(c4.x, tid + 1) + min(c4.y, tid + 1) + min(c4.z, tid + 1) + min(c4.w, tid + 1);
-    all += c4.x + c4.y + c4.z + c4.w;
-  }
-  const int look = all <= a.finish ? kLook : max(a.look, W);
-  const int q = __syncthreads_count(tid < kLook && v <= look);
-  if (tid == q - 1) s.rows = v;
-  __syncthreads();
-  const int rows = s.rows;
   constexpr int kPer = kLook / SRT_WAVE;
-  int c[kPer];
+  int c[kPer];  // (counts past W are 0)
 #pragma unroll
   for (int k = 0; k < kPer; ++k) c[k] = s.cnt[lane * kPer + k];
-  // walkers ahead of this lane that have more than q listed, and their rows
-  int more = 0, mine = 0;
+  auto lane_rows = [&](int q) __attribute__((always_inline)) {
+    int x = 0;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    more += c[k] > q;
-    mine += min(c[k], q);
-  }
-  int im = more, ir = mine;
-#pragma unroll
-  for (int off = 1; off < SRT_WAVE; off <<= 1) {
-    const int x = __shfl_up(im, off, SRT_WAVE), y = __shfl_up(ir, off, SRT_WAVE);
-    if (lane >= off) {
-      im += x;
-      ir += y;
+    for (int k = 0; k < kPer; ++k) x += min(c[k], q);
+    return x;
+  };
+  const int look = wave_sum(lane_rows(kLook)) <= a.finish ? kLook : max(a.look, W);
+  int q = 0, rows = 0;  // (the rows grow with q; 1 always fits)
+#pragma unroll 1
+  for (int step = kLook; step >= 1; step >>= 1) {
+    if (q + step > kLook) continue;
+    const int x = wave_sum(lane_rows(q + step));
+    if (x <= look) {
+      q += step;
+      rows = x;
     }
   }
-  const int left = look - rows, all_more = __shfl(im, SRT_WAVE - 1, SRT_WAVE);
-  const int total = rows + min(left, all_more);
-  int ahead = im - more, first = ir - mine;
+  int more = 0;  // walkers of this lane that have more than q listed
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) more += c[k] > q;
+  const int left = look - rows, total = rows + min(left, wave_sum(more));
   if (tid < SRT_WAVE) {
+    // those ahead of this lane, and the rows of the walkers ahead
+    const int mine = lane_rows(q);
+    int im = more, ir = mine;
+#pragma unroll
+    for (int off = 1; off < SRT_WAVE; off <<= 1) {
+      const int x = __shfl_up(im, off, SRT_WAVE), y = __shfl_up(ir, off, SRT_WAVE);
+      if (lane >= off) {
+        im += x;
+        ir += y;
+      }
+    }
+    int ahead = im - more, first = ir - mine;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
       const int i = lane * kPer + k;
@@ -359,8 +366,7 @@ __device__ inline int pass_rows(const HeadArgs& a, int pass, int W, Shared& s) {
   return total;
 }
 
-// Offsets of rows m0 .. m0 + TM - 1 of the pass (a thread per row).  Beyond
-// kLook walkers every one brings its current node only.
+// Offsets of rows m0 .. m0 + TM - 1 of the pass (a thread per row).
 template <int TM, typename Shared>
 __device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_rows, int m0, Shared& s) {
   const int r = m0 + static_cast<int>(threadIdx.x);
@@ -368,7 +374,7 @@ __device__ inline void row_offsets(const HeadArgs& a, int pass, int W, int n_row
   int64_t ho = 0, go = 0;
   if (r < n_rows) {
     int b, j = 0;
-    if (W <= kLook) {  // the walker whose rows hold r
+    if (W < lone_from(a)) {  // the walker whose rows hold r
       int lo = 0, hi = W - 1;
       while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
@@ -617,9 +623,10 @@ template <bool kNoise>
 __global__ __launch_bounds__(512, 1) void head_pass_kernel(HeadArgs a, int pass) {
   using Shared = PassShared<256, 256>;  // 151 of the CU's 160 KB
   __shared__ __attribute__((aligned(16))) Shared s;
+  const int2 walker = load_walker(a, pass);
   const int W = a.n_act[pass];
   if (W <= 0) return;
-  const int n_rows = W <= kLook ? pass_rows(a, pass, W, s) : W;
+  const int n_rows = W < lone_from(a) ? pass_rows(a, walker, W, s) : W;
   const int g = blockIdx.x, shares = gridDim.x;
   for (int m0 = 0; m0 < n_rows; m0 += 256) {
     row_offsets<256>(a, pass, W, n_rows, m0, s);
@@ -651,9 +658,10 @@ __global__ __launch_bounds__(256, 2) void head_small_kernel(HeadArgs a, int pass
   constexpr int TM = kTall ? 128 : 64;
   using Shared = PassShared<128, TM>;  // 79 KB or less, two workgroups a CU
   __shared__ __attribute__((aligned(16))) Shared s;
+  const int2 walker = load_walker(a, pass);
   const int W = a.n_act[pass];
   if (W <= 0) return;
-  const int n_rows = W <= kLook ? pass_rows(a, pass, W, s) : W;
+  const int n_rows = W < lone_from(a) ? pass_rows(a, walker, W, s) : W;
   const int tm = n_rows > 64 ? TM : 64;
   const int n_mb = (n_rows + tm - 1) / tm;
   const int i = blockIdx.x / kXcds;
@@ -727,7 +735,7 @@ __global__ __launch_bounds__(kWalkThreads) void head_walk_kernel(HeadArgs a, int
       s_par[c] = a.tree_parent[tr + c];
       s_tok[c] = a.tree_tokens[tr + c];
     }
-  const int2 span = W <= kLook ? a.span[slot] : make_int2(slot, 1);
+  const int2 span = W < lone_from(a) ? a.span[slot] : make_int2(slot, 1);
   const int2 first = a.list[static_cast<int64_t>(b) * a.L];
   int u = min(max(first.x, 0), a.N - 1);
   int at = 0;                               // u's place in the list
@@ -824,9 +832,8 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.V = V;
   a.Dmax = Dmax;
   a.L = L.L;
-  const Fill fill = fill_for(B, V, d_model, Dmax);
-  a.look = std::min(fill.look, L.rows);
-  a.finish = std::min(fill.finish, L.rows);
+  a.look = std::min(look_for(B, V, Dmax), L.rows);
+  a.finish = L.rows;
   a.n_cand = n_cand;
   a.units = sp.units;
   a.tiles = sp.tiles;

@@ -115,9 +115,9 @@ def test_look_passes_fill_the_pass_and_end_with_the_walk():
     out_nodes = np.full((2, Dmax + 1), -1, np.int32)
     out_nodes[0, :299] = np.arange(1, 300)
     one = {"tree_parent": tp[:1], "n_nodes": np.array([N], np.int32)}
-    assert bench.look_passes(one, out_nodes[:1], np.array([300]), Dmax, 50000, 256) == [256, 44]
+    assert bench.look_passes(one, out_nodes[:1], np.array([300]), Dmax, 50000) == [256, 44]
     two = {"tree_parent": tp, "n_nodes": np.array([N, 10], np.int32)}
-    assert bench.look_passes(two, out_nodes, np.array([300, 1]), Dmax, 50000, 256) == [256, 54]
+    assert bench.look_passes(two, out_nodes, np.array([300, 1]), Dmax, 50000) == [256, 54]
 
 
 def test_look_passes_with_less_room():
@@ -130,10 +130,10 @@ def test_look_passes_with_less_room():
     out_nodes = np.full((B, Dmax + 1), -1, np.int32)
     out_nodes[0, :10] = np.arange(1, 11)
     emitted = np.array([11] + [1] * (B - 1))
-    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 50000, 256) == [64, 18]
-    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 8000, 256) == [256, 13]
-    # short walks: 64 rows; up to 128 or 256 reachable nodes are one pass
-    brief = {"tree_parent": np.tile([-1, 0, 0, 1, 1, 2], (B, 1)).astype(np.int32), "n_nodes": np.full(B, 6, np.int32)}
-    assert bench.look_passes(brief, out_nodes, np.ones(B, int), 2, 8000, 256) == [64]
-    assert bench.look_passes(brief, out_nodes, np.ones(B, int), 2, 8000, 1024) == [240]
-    assert bench.look_passes({k: v[:21] for k, v in brief.items()}, out_nodes, np.ones(21, int), 2, 8000, 256) == [126]
+    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 50000) == [64, 18]
+    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 8000) == [256, 13]
+    # short walks: 64 rows, unless all reachable nodes are 256 or fewer
+    brief = {"tree_parent": np.tile([-1, 0, 0, 1, 1, 2], (B + 3, 1)).astype(np.int32), "n_nodes": np.full(B + 3, 6, np.int32)}
+    out = np.full((B + 3, 3), -1, np.int32)
+    assert bench.look_passes(brief, out, np.ones(B + 3, int), 2, 8000) == [64]
+    assert bench.look_passes({k: v[:42] for k, v in brief.items()}, out[:42], np.ones(42, int), 2, 8000) == [252]

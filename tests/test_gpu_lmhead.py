@@ -342,9 +342,11 @@ def test_both_divisions_of_the_head(V, d, split, B, N, Dmax, sampled):
     (97, 8, 7, 24000, 64, False),
     (16, 16, 15, 500, 64, True),     # 256 nodes in all: one pass
     (17, 16, 15, 500, 64, False),    # 272: 256 of them, then what is left
-    (8, 16, 2, 500, 64, True),       # short walks: 128 nodes, one pass
-    (9, 16, 2, 500, 64, False),      # 144: 64 rows
-    (16, 16, 2, 500, 1024, True),    # 256 nodes and a wider head: one pass
+    (16, 16, 2, 500, 64, True),      # short walks: 256 nodes, one pass
+    (17, 16, 2, 500, 64, False),     # 272: 64 rows
+    (254, 3, 2, 500, 64, True),      # 254 to 256 walkers of 762 and more nodes, a row each
+    (255, 3, 4, 500, 64, False),
+    (256, 3, 4, 500, 64, True),
     (70, 5, 1, 500, 128, False),     # 70 walkers in passes of 64 rows: their own nodes
 ])
 def test_rows_of_a_pass(B, N, Dmax, V, d, sampled):
