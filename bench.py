@@ -316,13 +316,19 @@ def full_tree_attention(st, cfg, n, calls: int = 10):
 MAX_ROWS = 256  # of a pass of srt_accept_lmhead, beyond the walking sequences' own
 
 
-def pass_fill(B, V, Dmax):
+def pass_fill(B, N, V, d_model, Dmax):
     """Rows that srt_accept_lmhead fills a pass up to (MAX_ROWS if these are
     all the nodes that the walks can still reach)."""
-    return 64 if Dmax <= 2 or (24 < B <= 96 and V >= 24000) else MAX_ROWS
+    if Dmax <= 2:
+        return 64
+    if B * N <= 2 * MAX_ROWS or V * d_model <= 20 << 20 or (B > 128 and (N <= 16 or (Dmax > 6 and N <= 64))):
+        return MAX_ROWS
+    if Dmax <= 6:
+        return 64 if B <= 64 else 128
+    return MAX_ROWS if V * d_model <= 48 << 20 else 128
 
 
-def look_passes(tree, out_nodes, emitted, Dmax, V):
+def look_passes(tree, out_nodes, emitted, Dmax, V, d_model):
     """Rows of each product pass srt_accept_lmhead makes: every sequence still
     walking brings the first q nodes (in tree order, depth at most Dmax) of its
     current node's subtree, q the largest number for which the rows fit
@@ -331,7 +337,7 @@ def look_passes(tree, out_nodes, emitted, Dmax, V):
     goes on until it leaves those nodes.  Rebuilt from the trees and the
     returned walks (host bookkeeping)."""
     tp, nn = tree["tree_parent"], tree["n_nodes"]
-    fill = pass_fill(tp.shape[0], V, Dmax)
+    fill = pass_fill(*tp.shape, V, d_model, Dmax)
     cur = {b: (0, 0) for b in range(tp.shape[0])}  # sequence -> (node, depth)
     passes = []
     while cur:
@@ -402,7 +408,7 @@ def fused_head(st, cfg, calls: int, unfused: bool):
     emitted = out["n_emitted"].cpu().numpy().astype(np.int64)
     levels = int(emitted.max())
     walkers = [int((emitted > l).sum()) for l in range(levels)]  # sequences walking at level l
-    passes = look_passes(tree, out["out_nodes"].cpu().numpy(), emitted, cfg.max_depth, V)
+    passes = look_passes(tree, out["out_nodes"].cpu().numpy(), emitted, cfg.max_depth, V, dm)
     row_bytes = dm * 2 + (V * 4 if st.gumbel is not None else 0)  # hidden row + noise row
     nbytes = sum(V * dm * 2 + rows * row_bytes for rows in passes)  # the head once per pass
     flops = sum(2.0 * rows * dm * V for rows in passes)

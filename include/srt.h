@@ -290,9 +290,11 @@ int srt_accept_noalloc(int32_t B, int32_t N, int32_t V, int32_t Dmax, const floa
  * long as it has room, at the next nodes of those nodes' subtrees in tree
  * order, and the walks go on through the computed nodes (same results: a
  * node's dot product does not depend on the pass).  R, the rows that a pass
- * has room for, is 64 or 256, chosen from B, V and Dmax alone; up to 256 nodes
- * that are all the walks can still reach are one pass.  min(Dmax + 1, ceil(N / max(1, R / B)))
- * passes are enqueued; one with no walking sequence exits at once.
+ * has room for, is 64, 128 or 256, chosen from the sizes alone (B, N, V, d_model
+ * and Dmax); up to 256 nodes that are all the walks can still reach are one
+ * pass.  With q = max(1, R / B) nodes a sequence, the least of Dmax + 1,
+ * ceil(N / q) and 1 + ceil((N - floor(256 / B)) / q), but at least one pass, are
+ * enqueued; one with no walking sequence exits at once.
  * Layouts: hidden [B, N, d_model] bf16 bits (the final hidden state of each
  * tree node), w_head [V, d_model] bf16 bits, both 16-byte aligned; gumbel
  * [B, Dmax+1, V] fp32 or NULL (greedy; inv_temperature then unused, else it

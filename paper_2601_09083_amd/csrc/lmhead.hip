@@ -22,7 +22,8 @@
 //     through the nodes of the pass; where it leaves them it lists the new
 //     current node's subtree for the next pass.
 // A walk that leaves a pass with quota q stands at least q places further in
-// its tree, so ceil(N / q) passes always suffice and no more are enqueued.
+// its tree, so ceil(N / q) passes always suffice, or one more than leave every
+// tree with so few nodes that they are the last pass; no more are enqueued.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -46,9 +47,7 @@ constexpr int kKC = 64;                  // d_model elements per step (one 128-b
 constexpr int kRowBytes = kKC * 2 + 16;  // padded LDS row (conflict-free operand reads)
 // Rows that a pass is filled up to, at most.  One pass over a 152064 x 3584 head takes
 // 221 us for 64 rows, 260 for 128 and 380 for 256 (sampled; reading the head
-// alone takes 190), and the walks of 256 sequences, 13 levels deep, take 6
-// passes when filled to 256 rows, 9 when filled to 128 (2.36 against 2.59 ms)
-// and 11 passes (2.70 ms) one level at a time with a last pass over what is left.
+// alone takes 190); see look_for for what they save.
 constexpr int kLook = 256;
 constexpr int kMaxLevels = 64;           // Dmax + 1 <= 64
 constexpr int kGrid = 256;               // workgroups of a pass over a large head: one per CU
@@ -124,16 +123,33 @@ inline Split split_for(int64_t V) {
 // nodes, Dmax 6, greedy: 434 without, 300 with it; 8 of 64, Dmax 1: 200 and 162;
 // up to 7% more than two passes for narrow heads, whose rows' noise weighs most:
 // d 896, 16 of 32, Dmax 2, sampled: 133 and 140).
-// kLook, as up to there rows cost less than the passes that they spare (256
-// sequences, Dmax 8, d 1536: 948 us with 64, 853 with 256; 16 of 32, Dmax 8, d
-// 3584: 380 and 360).  64 where they do not: for walks that two or three passes
-// end anyhow (32 sequences of 64, Dmax 2, sampled, d 1536: 224 with 64, 245 with
-// 128, 295 with 256), and for 25 to 96 sequences, which have a row or two each
-// then, most of them of walks that end at the root (64 sequences of 32, Dmax 8,
-// sampled: d 896 322 and 396, d 1536 452 and 542, d 3584 820 and 967); heads under
-// 24000 rows are too small for the rows to weigh (V 4096, d 1024: 89 and 86).
-inline int look_for(int B, int V, int Dmax) {
-  return Dmax <= 2 || (B > 24 && B <= 96 && V >= 24000) ? 64 : kLook;
+// Rows after the first 64 cost products and noise (kLook) and are lost on walks
+// that end before them; what they save are the later passes of deep walks.
+// Time of a call with 64, 128 and 256 rows to that of a pass per level, over
+// 2912 batches (1 to 256 sequences of up to 128 nodes, Dmax 1 to 12, eight heads of
+// 8192 x 1024 to 151936 x 3584; geometric mean, and the worst):
+// - Dmax <= 2, which two or three passes end anyhow: 0.91 (1.25), 0.93 (1.34),
+//   1.02 (1.77);
+// - room for at most 512 tree nodes (drafted trees fill half of it as a rule: the
+//   first pass is the last): 0.64 (1.11), 0.63 (1.08), 0.62 (1.04);
+// - light heads, whose rows cost less than a pass's launches: 0.78, 0.75, 0.70;
+// - more than 128 sequences of small or deep trees, which fill several passes
+//   in any case: 0.86, 0.79, 0.77 (trees of over 64 nodes: 0.90, 0.84, 0.90);
+// - shallow walks of up to 64 sequences: 0.91 (1.13), 0.96 (1.26), 1.09 (1.58),
+//   of more: 0.87, 0.85, 0.93 (1.34) (us: 16 sequences of 64, Dmax 3, sampled, V
+//   151936, d 2560: 335, 359, 439, with a pass per level 334);
+// - deep ones over large heads: 0.78, 0.75 (1.11), 0.81 (1.33); over those in
+//   between 0.81, 0.75, 0.75, and 256 rows are fewer passes.
+constexpr int64_t kLightHead = int64_t(20) << 20;  // elements
+constexpr int64_t kLargeHead = int64_t(48) << 20;
+
+inline int look_for(int64_t B, int64_t N, int64_t V, int64_t d_model, int Dmax) {
+  if (Dmax <= 2) return 64;
+  const int64_t head = V * d_model;
+  if (B * N <= 2 * kLook || head <= kLightHead) return kLook;
+  if (B > 128 && (N <= 16 || (Dmax > 6 && N <= 64))) return kLook;
+  if (Dmax <= 6) return B <= 64 ? 64 : 128;
+  return head <= kLargeHead ? kLook : 128;
 }
 
 // Scratch layout: counters, lists, node places, candidates of passes of up to
@@ -832,7 +848,7 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   a.V = V;
   a.Dmax = Dmax;
   a.L = L.L;
-  a.look = std::min(look_for(B, V, Dmax), L.rows);
+  a.look = std::min(look_for(B, N, V, d_model, Dmax), L.rows);
   a.finish = L.rows;
   a.n_cand = n_cand;
   a.units = sp.units;
@@ -845,7 +861,9 @@ extern "C" int srt_accept_lmhead(int32_t B, int32_t N, int32_t d_model, int32_t 
   // A walker's quota is at least look / B (see pass_rows), and a walk that
   // leaves a pass has moved that many places on in its tree.
   const int quota = std::max(1, std::min(a.L, a.look / B));
-  const int passes = std::min(Dmax + 1, (N - 1) / quota + 1);
+  // Once every tree has at most finish / B nodes left, the pass is the last.
+  const int moves = (std::max(0, N - a.finish / B) + quota - 1) / quota;
+  const int passes = std::min({Dmax + 1, (N - 1) / quota + 1, moves + 1});
   for (int pass = 0; pass < passes && st == SRT_OK; ++pass) {
     if (sp.wide) {
       if (gumbel) head_pass_kernel<true><<<sp.grid, 512, 0, s>>>(a, pass);

@@ -115,25 +115,29 @@ def test_look_passes_fill_the_pass_and_end_with_the_walk():
     out_nodes = np.full((2, Dmax + 1), -1, np.int32)
     out_nodes[0, :299] = np.arange(1, 300)
     one = {"tree_parent": tp[:1], "n_nodes": np.array([N], np.int32)}
-    assert bench.look_passes(one, out_nodes[:1], np.array([300]), Dmax, 50000) == [256, 44]
+    assert bench.look_passes(one, out_nodes[:1], np.array([300]), Dmax, 50000, 320) == [256, 44]
     two = {"tree_parent": tp, "n_nodes": np.array([N, 10], np.int32)}
-    assert bench.look_passes(two, out_nodes, np.array([300, 1]), Dmax, 50000) == [256, 54]
+    assert bench.look_passes(two, out_nodes, np.array([300, 1]), Dmax, 50000, 320) == [256, 54]
 
 
 def test_look_passes_with_less_room():
-    # 40 sequences of 20-node chains, the first walked 10 steps deep, the others
+    # 40 sequences of 20-node chains, the first walked 6 steps deep, the others
     # stopping at the root: 64 rows leave 24 of the walkers a second node; then
-    # the first walker's remaining subtree is one pass.  A small head has room
-    # for 256 rows: six nodes each and 16 of the walkers a seventh
-    B, N, Dmax = 40, 20, 19
+    # the first walker's remaining subtree (up to depth 6) is one pass.  Deeper
+    # trees and a large head have 128 rows, light heads 256
+    B, N, Dmax = 40, 20, 6
     tree = {"tree_parent": np.tile(np.arange(-1, N - 1), (B, 1)).astype(np.int32), "n_nodes": np.full(B, N, np.int32)}
     out_nodes = np.full((B, Dmax + 1), -1, np.int32)
-    out_nodes[0, :10] = np.arange(1, 11)
-    emitted = np.array([11] + [1] * (B - 1))
-    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 50000) == [64, 18]
-    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 8000) == [256, 13]
+    out_nodes[0, :6] = np.arange(1, 7)
+    emitted = np.array([7] + [1] * (B - 1))
+    assert bench.look_passes(tree, out_nodes, emitted, Dmax, 50000, 2048) == [64, 5]
+    deep = np.full((B, N), -1, np.int32)
+    deep[0, :10] = np.arange(1, 11)
+    emitted[0] = 11
+    assert bench.look_passes(tree, deep, emitted, N - 1, 50000, 2048) == [128, 16]
+    assert bench.look_passes(tree, deep, emitted, N - 1, 8000, 2048) == [256, 13]
     # short walks: 64 rows, unless all reachable nodes are 256 or fewer
     brief = {"tree_parent": np.tile([-1, 0, 0, 1, 1, 2], (B + 3, 1)).astype(np.int32), "n_nodes": np.full(B + 3, 6, np.int32)}
     out = np.full((B + 3, 3), -1, np.int32)
-    assert bench.look_passes(brief, out, np.ones(B + 3, int), 2, 8000) == [64]
-    assert bench.look_passes({k: v[:42] for k, v in brief.items()}, out[:42], np.ones(42, int), 2, 8000) == [252]
+    assert bench.look_passes(brief, out, np.ones(B + 3, int), 2, 8000, 64) == [64]
+    assert bench.look_passes({k: v[:42] for k, v in brief.items()}, out[:42], np.ones(42, int), 2, 8000, 64) == [252]

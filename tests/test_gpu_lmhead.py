@@ -335,19 +335,27 @@ def test_both_divisions_of_the_head(V, d, split, B, N, Dmax, sampled):
 
 
 @pytest.mark.parametrize("B,N,Dmax,V,d,sampled", [
-    (40, 20, 19, 24000, 64, False),  # 64 rows: 24 of 40 walkers bring a second node
-    (40, 20, 19, 23999, 64, True),   # 256 rows
-    (24, 16, 9, 24000, 64, False),   # 24 and 97 sequences: 256 rows
-    (25, 16, 9, 24000, 64, True),
-    (97, 8, 7, 24000, 64, False),
-    (16, 16, 15, 500, 64, True),     # 256 nodes in all: one pass
-    (17, 16, 15, 500, 64, False),    # 272: 256 of them, then what is left
-    (16, 16, 2, 500, 64, True),      # short walks: 256 nodes, one pass
-    (17, 16, 2, 500, 64, False),     # 272: 64 rows
-    (254, 3, 2, 500, 64, True),      # 254 to 256 walkers of 762 and more nodes, a row each
+    (16, 16, 15, 500, 64, True),        # 256 nodes in all: one pass
+    (17, 16, 15, 500, 64, False),       # 272: 256 of them, then what is left
+    (16, 16, 2, 500, 64, True),         # short walks: 256 nodes, one pass
+    (17, 16, 2, 500, 64, False),        # 272: 64 rows
+    (254, 3, 2, 500, 64, True),         # 254 to 256 walkers of 762 and more nodes, a row each
     (255, 3, 4, 500, 64, False),
     (256, 3, 4, 500, 64, True),
-    (70, 5, 1, 500, 128, False),     # 70 walkers in passes of 64 rows: their own nodes
+    (70, 5, 1, 500, 128, False),        # 70 walkers in passes of 64 rows: their own nodes
+    (40, 20, 6, 20480, 1024, False),    # a light head: 256 rows; one of a row more: 64
+    (40, 20, 6, 20481, 1024, True),     # (24 of 40 walkers bring a second node)
+    (16, 32, 6, 20481, 1024, False),    # 512 and 527 nodes: 256 and 64 rows
+    (17, 31, 6, 20481, 1024, True),
+    (64, 9, 3, 20481, 1024, False),     # 64 and 65 sequences: 64 and 128 rows
+    (65, 9, 3, 20481, 1024, True),
+    (40, 20, 7, 20481, 1024, True),     # deeper: 256 rows
+    (40, 20, 7, 24576, 2048, False),    # until the head is large: 128
+    (40, 20, 7, 24577, 2048, True),
+    (129, 16, 4, 20481, 1024, False),   # 129 sequences of 16 and 17 nodes: 256 and 128 rows,
+    (129, 17, 4, 20481, 1024, True),
+    (129, 17, 7, 24577, 2048, False),   # when deeper 256 up to 64 nodes
+    (129, 65, 7, 24577, 2048, True),
 ])
 def test_rows_of_a_pass(B, N, Dmax, V, d, sampled):
     """Full trees on both sides of every rule that gives a pass its rows."""
@@ -364,10 +372,49 @@ def test_rows_of_a_pass(B, N, Dmax, V, d, sampled):
                             tree_parent=tree["tree_parent"], n_nodes=tree["n_nodes"], plant_p=0.9)
     gumbel = torch.randint(-3, 4, (B, Dmax + 1, V), device="cuda").float() if sampled else None
     got = run_fused(hidden, w, gumbel, 1.0, tree, Dmax)
-    want = oracle_rows(hidden, w, gumbel, 1.0, tree, range(B), Dmax)
-    for b in range(B):
+    assert_same(got, run_materialised(hidden, w, gumbel, 1.0, tree, Dmax), B)
+    seqs = range(B) if V <= 500 else sorted(rng.choice(B, 4, replace=False).tolist()) + [int(np.argmax(got["n_accepted"]))]
+    want = oracle_rows(hidden, w, gumbel, 1.0, tree, seqs, Dmax)
+    for b in seqs:
         assert_accept_equal(got, b, want[b], Dmax)
     assert got["n_accepted"].max() >= 1
+
+
+@pytest.mark.parametrize("B,N,Dmax,V,d", [
+    (40, 20, 19, 24577, 2048),   # 128 rows, quotas of 3
+    (24, 30, 29, 24577, 2048),   # of 5
+    (2, 260, 63, 24577, 2048),   # of 64
+    (4, 130, 6, 20481, 1024),    # 64 rows, quotas of 16
+    (10, 60, 6, 20481, 1024),
+    (100, 20, 19, 500, 64),      # 256 rows, quotas of 2
+    (256, 8, 7, 500, 64),        # of 1
+    (257, 8, 7, 500, 64),        # more walkers than rows
+])
+@pytest.mark.parametrize("step", [1, "quota", "past"])
+def test_enough_passes_for_every_walk(B, N, Dmax, V, d, step):
+    """Every walk follows its tree to the end and moves no further in a pass
+    than it must: the path's next node is the next one, the last one of the
+    pass or the first one after it, with the nodes between below it too."""
+    look = 256 if V == 500 else 128 if Dmax > 6 else 64
+    quota = max(1, look // B)
+    s = {1: 1, "quota": max(1, quota - 1), "past": quota}[step]
+    say(f"lmhead enough passes: B={B} N={N} Dmax={Dmax} V={V} d={d} step={s}")
+    par = np.full(N, -1, np.int32)
+    path = list(range(0, min(N, Dmax * s + 1), s))
+    for i in range(1, N):
+        par[i] = path[min((i - 1) // s, len(path) - 1)] if len(path) <= Dmax or i <= path[-1] else path[-2]
+    rng = np.random.default_rng(B + N)
+    tree = {"tree_parent": np.tile(par, (B, 1)), "n_nodes": np.full(B, N, np.int32),
+            "tree_tokens": np.stack([rng.permutation(V)[:N] for _ in range(B)]).astype(np.int32)}
+    hidden, w = W.make_head(B, N, d, V, device="cuda", seed=B + N, kind="int")
+    for u, c in zip(path, path[1:]):  # the path's next token wins (scores of 4 d against about sqrt(16 d))
+        hidden[:, u] = w[torch.as_tensor(tree["tree_tokens"][:, c], device="cuda").long()]
+    got = run_fused(hidden, w, None, 1.0, tree, Dmax)
+    assert (got["n_accepted"] >= len(path) - 1).all()
+    assert (got["out_nodes"][:, :len(path) - 1] == path[1:]).all()
+    want = oracle_rows(hidden, w, None, 1.0, tree, (0, B - 1), Dmax)
+    for b in (0, B - 1):
+        assert_accept_equal(got, b, want[b], Dmax)
 
 
 @pytest.mark.parametrize("B,N,Dmax,V,d,deep,sampled", [
