@@ -107,6 +107,7 @@ struct AttnArgs {
 // here took one thread per sequence 20 to 40 us of stores; the combine kernel
 // works the group out instead.)
 constexpr int kPlanHeader = 64;
+constexpr int kFewItems = 8;  // of a sequence, up to which its thread of the plan kernel lists them
 constexpr int kCombineRows = 8;
 constexpr int kPlanKeys = (kChunk / kTile) * kWaves;  // (tiles, waves) classes
 
@@ -634,7 +635,11 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
   // class lists (and in the list of split sequences), then all threads, the
   // same number for each sequence, write the items.  (One thread per sequence
   // wrote them in up to 280 stores one after the other: 20 us for 256
-  // sequences of up to 32k, 46 for 8 with 256-node trees; now 6 and 5.)
+  // sequences of up to 32k, 46 for 8 with 256-node trees; now 6 and 5.)  Where
+  // none can have more than kFewItems the thread writes them at once, without
+  // the exchange through LDS (512 sequences of one item: 19.1 us a call with it, 18.4
+  // so; 256 of 4: 42.7 and 41.8).
+  const bool few = a.total <= kFewItems * a.B;
   const int group = min(a.B, 1024);
   const int per_seq_log2 = group > 1 ? __clz(group - 1) - 22 : 10;  // 1024 / (group rounded up to a power of two)
   for (int b0 = 0; b0 < a.B; b0 += 1024) {
@@ -645,7 +650,17 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
       s_total[tid] = si.total;
       s_rows[tid] = rows;
       classes(si.total, rows, [&](int c, int key, int ns) {
-        s_pos[c][tid] = atomicAdd(&off[key], ns * a.Hkv * row_blocks(rows));
+        const int rbs = row_blocks(rows);
+        int at = atomicAdd(&off[key], ns * a.Hkv * rbs);
+        if (!few) {
+          s_pos[c][tid] = at;
+          return;
+        }
+        const int s0 = c == 0 ? 0 : si.total >> cshift;
+        for (int s = s0; s < s0 + ns; ++s)
+          for (int g = 0; g < a.Hkv; ++g)
+            for (int rb = 0; rb < rbs; ++rb, ++at)
+              *reinterpret_cast<int2*>(a.plan + kPlanHeader + 2 * at) = make_int2(b0 + tid, g | (s << 8) | (rb << 20));
       });
       if (si.total > a.chunk) {
         *reinterpret_cast<int2*>(a.plan + a.combine_at + 2 * atomicAdd(&ncomb, 1)) =
@@ -653,10 +668,12 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
         split_rows = rows;
       }
     }
-    // (one atomic a wave: 64 on one word take 1.5 us)
+    if (a.S > 1) {  // (one atomic a wave: 64 on one word take 1.5 us)
 #pragma unroll
-    for (int d = SRT_WAVE / 2; d >= 1; d >>= 1) split_rows = max(split_rows, __shfl_xor(split_rows, d, SRT_WAVE));
-    if (lane == 0 && split_rows > 0) atomicMax(&widest, split_rows);
+      for (int d = SRT_WAVE / 2; d >= 1; d >>= 1) split_rows = max(split_rows, __shfl_xor(split_rows, d, SRT_WAVE));
+      if (lane == 0 && split_rows > 0) atomicMax(&widest, split_rows);
+    }
+    if (few) continue;
     __syncthreads();
     const int i = tid >> per_seq_log2;
     if (b0 + i < a.B && i < group) {
@@ -670,6 +687,7 @@ __global__ __launch_bounds__(1024) void tree_attn_plan_kernel(AttnArgs a) {
     }
     if (b0 + 1024 < a.B) __syncthreads();
   }
+  if (few) __syncthreads();
   if (tid == 0) {
     a.plan[2] = ncomb;
     a.plan[3] = (widest + kCombineRows - 1) / kCombineRows;

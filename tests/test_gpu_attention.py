@@ -223,6 +223,10 @@ def test_dominant_keys_late_in_a_split(factor):
     (1, 7, 1, 4, 8100, 8150),     # 32 splits of 256 keys
     (1, 7, 1, 4, 8200, 8300),     # 17 splits of 512 keys
     (2, 256, 1, 5, 1, 1100),      # five row blocks, splits without keys
+    (65, 3, 4, 1, 1, 1100),       # up to 8 items a sequence: its thread lists them
+    (65, 3, 3, 1, 1, 2300),       # up to 9: all threads do
+    (1030, 2, 9, 1, 1, 60),
+    (1030, 2, 2, 1, 1000, 1100),  # 4 items, two splits, more sequences than at a time
 ])
 def test_work_list_covers_every_sequence(B, N, hkv, G, lo, hi):
     """Every (sequence, KV head, split, row block) is worked on exactly once:
